@@ -134,7 +134,7 @@ size_t query_ws(const scope_shape *s, int c_q, void *base, QueryWs *w) {
   const int cpad = scope::km_cpad(c_q);
   q.ubf = cv.take<uint16_t>(static_cast<size_t>(s->heads) * cpad * 2 * scope::km_dxp(s->d));
   q.nu = cv.take<float>(static_cast<size_t>(s->heads) * cpad);
-  q.bnd = cv.take<float>(static_cast<size_t>(s->heads) * cpad * 2);
+  q.bnd = cv.take<float>(static_cast<size_t>(s->heads) * cpad);
   q.split = cv.take<float>(scope::km_split_floats(c_q, s->d, s->heads, s->n));
   if (w) *w = q;
   return cv.used;
@@ -162,7 +162,7 @@ size_t key_ws(const scope_shape *s, const int32_t *c_m, void *base, KeyWs *w) {
     const int cpad = scope::km_cpad(C);
     k.ubf[m] = cv.take<uint16_t>(H * cpad * 2 * scope::km_dxp(dx));
     k.nu[m] = cv.take<float>(H * cpad);
-    k.bnd[m] = cv.take<float>(H * cpad * 2);
+    k.bnd[m] = cv.take<float>(H * cpad);
   }
   size_t split = 0;
   for (int m = 0; m < 3; ++m) {
@@ -294,7 +294,7 @@ size_t part_key_ws(const scope_shape *s, const scope_partition *p, void *base,
     const int cpad = scope::km_cpad(g.C[m]);
     k.ubf[m] = cv.take<uint16_t>(H * cpad * 2 * scope::km_dxp(g.len[m]));
     k.nu[m] = cv.take<float>(H * cpad);
-    k.bnd[m] = cv.take<float>(H * cpad * 2);
+    k.bnd[m] = cv.take<float>(H * cpad);
   }
   size_t split = 0;
   for (int m = 0; m < g.M; ++m) {
@@ -409,7 +409,10 @@ int32_t cluster_queries(const scope_shape *shape, const void *q, int32_t c_q, in
   p.bnd = w.bnd;
   set_split(p, w.split);
   const scope::AccPlan plan = query_plan(shape, c_q);
-  if (!warm) SCOPE_TRY(scope::km_init(p, init_idx, c_q, dev_status, s));
+  // the grouping histogram is built with atomics by the last assignment
+  const size_t hist = p.mfma ? static_cast<size_t>(p.heads) * scope::km_nchunks(n) * c_q : 0;
+  SCOPE_TRY(scope::km_init(&p, 1, warm, init_idx, c_q, 0, dev_status, p.chunk_hist, hist,
+                           scope::DeviceArgs{}, s));
   // the returned grouping is that of the last assignment, taken before the
   // last update
   for (int it = 0; it < iters; ++it) {
@@ -418,8 +421,8 @@ int32_t cluster_queries(const scope_shape *shape, const void *q, int32_t c_q, in
     if (last) SCOPE_TRY(scope::km_group(p, s));
     SCOPE_TRY(scope::km_accum(plan, q, p.bf16, p.x_head_stride, d, n, shape->heads,
                               assign, p.a_head_stride, 0, w.slab, w.cslab,
-                              q_centroids, p.u_head_stride, it == 0 ? dev_status : nullptr,
-                              s));
+                              it == 0 ? dev_status : nullptr, s));
+    SCOPE_TRY(scope::km_finish(plan, &p, 1, !last, w.slab, w.cslab, s));
   }
   return SCOPE_OK;
 }
@@ -476,21 +479,18 @@ int32_t cluster_key_subspaces(const scope_shape *shape, const void *k, const int
     pm.bnd = w.bnd[m];
     set_split(pm, w.split);
     ucol += static_cast<size_t>(c_m[m]) * pm.dx;
-    const int32_t *init = init_idx ? init_idx + static_cast<size_t>(m) * init_stride : nullptr;
-    // init rows of head h, subspace m live at init_idx[(h*3 + m)*init_stride]
-    if (!warm) SCOPE_TRY(scope::km_init(pm, init, 3 * init_stride, dev_status, s));
   }
   const scope::AccPlan plan = key_plan(shape, c_m);
   // the three assignments in one pass over K when the codebooks fit the LDS
   // together, else one pass per subspace
   const bool fused = scope::km_assign3_ok(p);
-  bool args_stored = false;
+  scope::DeviceArgs args{};
+  if (fused) scope::km_assign3_args(p, w.args3, &args);
+  // init rows of head h, subspace m live at init_idx[(h*3 + m)*init_stride]
+  SCOPE_TRY(scope::km_init(p, 3, warm, init_idx, 3 * init_stride, init_stride, dev_status,
+                           nullptr, 0, args, s));
   auto assign_all = [&]() -> hipError_t {
-    if (fused) {
-      const hipError_t e = scope::km_assign3(p, w.args3, !args_stored, s);
-      args_stored = true;
-      return e;
-    }
+    if (fused) return scope::km_assign3(p, w.args3, s);
     for (int m = 0; m < 3; ++m) {
       const hipError_t e = scope::km_assign(p[m], false, s);
       if (e != hipSuccess) return e;
@@ -501,7 +501,8 @@ int32_t cluster_key_subspaces(const scope_shape *shape, const void *k, const int
     SCOPE_TRY(assign_all());
     SCOPE_TRY(scope::km_accum(plan, k, p[0].bf16, p[0].x_head_stride, d, n, shape->heads,
                               w.assign3, static_cast<size_t>(3) * n, n, w.slab, w.cslab,
-                              k_centroids, per_head, it == 0 ? dev_status : nullptr, s));
+                              it == 0 ? dev_status : nullptr, s));
+    SCOPE_TRY(scope::km_finish(plan, p, 3, true, w.slab, w.cslab, s));
   }
   SCOPE_TRY(assign_all());
   SCOPE_TRY(scope::km_pack_codes(w.assign3, static_cast<size_t>(3) * n, n, n,
@@ -696,15 +697,16 @@ int32_t scope_cluster_key_partition(const scope_shape *shape, const void *k,
     pm.bnd = w.bnd[m];
     set_split(pm, w.split);
     ucol += static_cast<size_t>(g.C[m]) * pm.dx;
-    // rows of head h, subspace m at init_idx[(h*M + m)*init_stride]
-    const int32_t *init = init_idx ? init_idx + static_cast<size_t>(m) * init_stride : nullptr;
-    SCOPE_TRY(scope::km_init(pm, init, M * init_stride, dev_status, s));
   }
+  // rows of head h, subspace m at init_idx[(h*M + m)*init_stride]
+  SCOPE_TRY(scope::km_init(p, M, false, init_idx, M * init_stride, init_stride, dev_status,
+                           nullptr, 0, scope::DeviceArgs{}, s));
   for (int it = 0; it < iters; ++it) {
     for (int m = 0; m < M; ++m) SCOPE_TRY(scope::km_assign(p[m], false, s));
     SCOPE_TRY(scope::km_accum(plan, x, bf16, p[0].x_head_stride, d, n, shape->heads,
                               w.assign, static_cast<size_t>(M) * n, n, w.slab, w.cslab,
-                              k_centroids, g.per_head, it == 0 ? dev_status : nullptr, s));
+                              it == 0 ? dev_status : nullptr, s));
+    SCOPE_TRY(scope::km_finish(plan, p, M, true, w.slab, w.cslab, s));
   }
   for (int m = 0; m < M; ++m) SCOPE_TRY(scope::km_assign(p[m], false, s));
   SCOPE_TRY(scope::km_codes16(w.assign, static_cast<size_t>(shape->heads) * M * n, codes, s));

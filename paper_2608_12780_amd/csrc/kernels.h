@@ -33,7 +33,7 @@ struct KmProblem {
   int cpad, dxp;          // centroids padded to 32, channels padded to 16
   uint16_t *ubf;          // [heads][cpad][2 * dxp]: bf16 hi then lo terms
   float *nu;              // [heads][cpad]
-  float *bnd;             // [heads][cpad][2]: per-row bound parts
+  float *bnd;             // [heads][cpad]: bound on the two terms' residual
   // codebooks beyond the LDS: per chunk and point the four smallest packed
   // scores ([parts][heads][n][4]) and the point's norm bound ([heads][n])
   float *part, *pnx;
@@ -52,19 +52,33 @@ constexpr int kAssignBlock = 256;  // points per assign block == grouping chunk
 
 inline int km_nchunks(int n) { return (n + kAssignBlock - 1) / kAssignBlock; }
 
-hipError_t km_init(const KmProblem &p, const int32_t *init, int init_stride,
-                   int32_t *status, hipStream_t s);
+// Launch arguments that later kernels of the call read from device memory,
+// as 32-bit words stored to dst (words == 0: none).
+constexpr int kArgWords = 160;
+struct DeviceArgs {
+  uint32_t *dst;
+  int words;
+  uint32_t w[kArgWords];
+};
+
+// The starting centroids of the call's subspaces p[0..nsub) (one set of rows,
+// centroids back to back) in one launch: the rows init[h * init_hs + m *
+// init_ms + r] of X (init null: the default rows), or with `warm` those in
+// p[].u; matrix-core codebooks are prepared for the first assignment.  The
+// same launch clears zero[0..zero_count) and stores args.
+hipError_t km_init(const KmProblem *p, int nsub, bool warm, const int32_t *init, int init_hs,
+                   int init_ms, int32_t *status, int32_t *zero, size_t zero_count,
+                   const DeviceArgs &args, hipStream_t s);
 hipError_t km_assign(const KmProblem &p, bool with_hist, hipStream_t s);
 hipError_t km_group(const KmProblem &p, hipStream_t s);
 // The three key subspaces' assignments in one pass over the rows (matrix
 // cores; codebooks side by side in LDS): applies when km_assign3_ok.
 bool km_assign3_ok(const KmProblem (&p)[3]);
-// scratch: km_assign3_scratch_bytes() of device memory (its arguments)
+// scratch: km_assign3_scratch_bytes() of device memory that hold the launch's
+// arguments; km_assign3_args fills in what km_init stores there
 size_t km_assign3_scratch_bytes();
-// store_args: write the launch arguments to the scratch (once per call; the
-// later passes of the call reuse them)
-hipError_t km_assign3(const KmProblem (&p)[3], void *scratch, bool store_args,
-                      hipStream_t s);
+void km_assign3_args(const KmProblem (&p)[3], void *scratch, DeviceArgs *args);
+hipError_t km_assign3(const KmProblem (&p)[3], void *scratch, hipStream_t s);
 
 // Centroid update by one streaming pass over the rows.  Up to kMaxSub
 // subspaces of the same rows (channels col0[m] .. col0[m]+dx[m], C[m]
@@ -76,6 +90,21 @@ constexpr int kAccCnt = 1024;            // int32 cluster counts per block
 constexpr int kAccMaxPieces = 4;
 constexpr int kAccMaxWindows = 16;
 constexpr int kMaxSub = 8;               // subspaces of a key partition
+
+// One subspace's codebook as the kernels that write centroids see it.
+struct Codebook {
+  int C, cpad, rows;    // centroids, padded, and the rows that are written
+  int dx, dxp, col0;
+  int ucol, ccol;       // float offset and first cluster within a head
+  uint16_t *ubf;        // matrix-core codebook, norms and bounds, or null
+  float *nu, *bnd;
+};
+struct Codebooks {
+  float *u;             // centroids of head 0
+  size_t u_hs;
+  Codebook c[kMaxSub];
+};
+
 constexpr int kAccTargetBlocks = 256;    // blocks per launch, about one per CU
 struct AccPiece {
   int m, sub0, width;   // channels sub0 .. sub0+width of subspace m
@@ -103,7 +132,11 @@ size_t km_accum_cslab_bytes(const AccPlan &p, int heads);
 hipError_t km_accum(const AccPlan &plan, const void *x, bool bf16, size_t x_hs,
                     int ld, int n, int heads, const int32_t *assign,
                     size_t a_hs, size_t a_ss, long long *slab, int32_t *cslab,
-                    float *U, size_t u_hs, int32_t *status, hipStream_t s);
+                    int32_t *status, hipStream_t s);
+// The new centroids of p[0..nsub) from the blocks' sums; `prepare`: their
+// matrix-core codebooks too (not needed after a call's last update).
+hipError_t km_finish(const AccPlan &plan, const KmProblem *p, int nsub, bool prepare,
+                     const long long *slab, const int32_t *cslab, hipStream_t s);
 hipError_t km_pack_codes(const int32_t *a3, size_t a_head_stride,
                          size_t a_sub_stride, int n, int heads,
                          uint32_t *codes, hipStream_t s);

@@ -5,8 +5,8 @@
 //   update: exact int64 sums of rint(x * 2^24) over the members, one fp64
 //           division by count * 2^24, rounded to fp32; empty clusters keep
 //           their centroid.
-// This file: initialisation, the VALU assignment, and the grouping of the
-// final query assignment (per-chunk cluster histograms -> column scan ->
+// This file: the VALU assignment, and the grouping of the final query
+// assignment (per-chunk cluster histograms -> column scan ->
 // stable scatter into the cluster-grouped permutation);
 // also the packing of key codes and the channel gather of general key
 // partitions.
@@ -18,26 +18,6 @@
 namespace scope {
 
 namespace {
-
-template <typename T>
-__global__ void km_init_kernel(const T *X, size_t x_hs, int ld, int col0,
-                               int dx, int n, int C, const int32_t *init,
-                               int init_stride, float *U, size_t u_hs,
-                               int32_t *status) {
-  const int r = blockIdx.x, h = blockIdx.y;
-  const int def = static_cast<int>(((2LL * r + 1) * n) / (2LL * C));
-  int row = def;
-  if (init) {
-    row = init[static_cast<size_t>(h) * init_stride + r];
-    if (row < 0 || row >= n) {
-      if (threadIdx.x == 0 && status) atomicOr(status, kStatusBadInit);
-      row = def;
-    }
-  }
-  const T *src = X + h * x_hs + static_cast<size_t>(row) * ld + col0;
-  float *dst = U + h * u_hs + static_cast<size_t>(r) * dx;
-  for (int c = threadIdx.x; c < dx; c += blockDim.x) dst[c] = load_elem(src, c);
-}
 
 // One point per thread, its channels held in registers (zero padded to DXP:
 // a trailing fma(0, 0, acc) leaves the score unchanged).  Centroids are
@@ -275,22 +255,6 @@ hipError_t assign_dispatch(const KmProblem &p, bool with_hist, hipStream_t s) {
 }
 
 }  // namespace
-
-hipError_t km_init(const KmProblem &p, const int32_t *init, int init_stride,
-                   int32_t *status, hipStream_t s) {
-  const dim3 grid(p.C, p.heads);
-  if (p.bf16)
-    hipLaunchKernelGGL(km_init_kernel<uint16_t>, grid, dim3(64), 0, s,
-                       static_cast<const uint16_t *>(p.x), p.x_head_stride,
-                       p.ld, p.col0, p.dx, p.n, p.C, init, init_stride, p.u,
-                       p.u_head_stride, status);
-  else
-    hipLaunchKernelGGL(km_init_kernel<float>, grid, dim3(64), 0, s,
-                       static_cast<const float *>(p.x), p.x_head_stride, p.ld,
-                       p.col0, p.dx, p.n, p.C, init, init_stride, p.u,
-                       p.u_head_stride, status);
-  return hipGetLastError();
-}
 
 hipError_t km_assign_mfma(const KmProblem &p, bool with_hist, hipStream_t s);
 

@@ -35,6 +35,7 @@
 // others); chunk histograms for the grouping are accumulated with global
 // atomics.
 #include <math.h>
+#include <string.h>
 
 #include "common.h"
 #include "kernels.h"
@@ -51,13 +52,6 @@ constexpr int kWavesPerBlock = 16;
 constexpr int kUbfLds = 69632;            // two-term bf16 codebook elements in LDS
 constexpr int kMaxCpad = 1024;
 constexpr int kWaveCand = 64;             // candidate pairs per wave
-
-__device__ __forceinline__ uint16_t to_bf16(float f) {
-  bf16x2 r;
-  r[0] = static_cast<__bf16>(f);
-  r[1] = static_cast<__bf16>(0.0f);
-  return static_cast<uint16_t>(__builtin_bit_cast(uint32_t, r) & 0xFFFFu);
-}
 
 // Channels c0 .. c0+7 of one bf16 row as four packed pairs, zero from dx on
 // and for invalid rows.  A whole group is one 16-byte load when the rows are
@@ -121,110 +115,6 @@ __device__ __forceinline__ uint32_t asc_key(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// Per pass: two-term bf16 codebook [cpad][2*DXP] (hi then lo, zero padded),
-// canonical squared norms (FLT_MAX for padding rows, which never win), and
-// per-row bound parts [cpad][2] = (|u - hi - lo|, max(|u|, |hi| + |lo|)),
-// evaluated in fp64; the assignment kernel takes the per-head maxima.  One
-// wave per row: lanes split the channels, lane 0 keeps the norm's fma chain
-// in channel order.
-template <int DXP>
-__device__ __forceinline__ void km_prep_row(const float *__restrict__ U, size_t u_hs, int C,
-                                            int cpad, int dx, uint16_t *ubf, float *nu,
-                                            float *bnd) {
-  const int h = blockIdx.y, lane = threadIdx.x & 63;
-  const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (r >= cpad) return;
-  uint16_t *dst = ubf + (static_cast<size_t>(h) * cpad + r) * (2 * DXP);
-  const size_t row = static_cast<size_t>(h) * cpad + r;
-  if (r >= C) {
-    for (int c = lane; c < 2 * DXP; c += 64) dst[c] = 0;
-    if (lane == 0) {
-      nu[row] = 0x1.fffffep127f;
-      bnd[2 * row + 0] = 0.0f;
-      bnd[2 * row + 1] = 0.0f;
-    }
-    return;
-  }
-  const float *u = U + h * u_hs + static_cast<size_t>(r) * dx;
-  double e2 = 0.0, n2 = 0.0, h2 = 0.0, l2 = 0.0;
-  float xs[(DXP + 63) / 64];  // channel lane + 64 j of the row, 0 past dx
-#pragma unroll
-  for (int j = 0; j < (DXP + 63) / 64; ++j) {
-    const int c = lane + 64 * j;
-    xs[j] = c < dx ? u[c] : 0.0f;
-  }
-#pragma unroll
-  for (int j = 0; j < (DXP + 63) / 64; ++j) {
-    const int c = lane + 64 * j;
-    if (c >= DXP) break;
-    uint16_t bh = 0, bl = 0;
-    if (c < dx) {
-      const float x = xs[j];
-      bh = to_bf16(x);
-      const float rest = x - bf16_to_f32(bh);  // exact
-      bl = to_bf16(rest);
-      const double df = static_cast<double>(rest) - static_cast<double>(bf16_to_f32(bl));
-      const double fh = bf16_to_f32(bh), fl = bf16_to_f32(bl);
-      e2 += df * df;
-      n2 += static_cast<double>(x) * static_cast<double>(x);
-      h2 += fh * fh;
-      l2 += fl * fl;
-    }
-    dst[c] = bh;
-    dst[DXP + c] = bl;
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    e2 += __shfl_xor(e2, o);
-    n2 += __shfl_xor(n2, o);
-    h2 += __shfl_xor(h2, o);
-    l2 += __shfl_xor(l2, o);
-  }
-  // the canonical norm: one fma per channel in channel order, each channel
-  // taken from the lane that loaded it
-  float nr = 0.0f;
-#pragma unroll
-  for (int j = 0; j < (DXP + 63) / 64; ++j) {
-    const int cend = dx - 64 * j < 64 ? dx - 64 * j : 64;
-    for (int c = 0; c < cend; ++c) {
-      const float v = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(xs[j]), c));
-      nr = fmaf(v, v, nr);
-    }
-  }
-  if (lane == 0) {
-    nu[row] = nr;
-    bnd[2 * row + 0] = static_cast<float>(sqrt(e2));
-    bnd[2 * row + 1] = static_cast<float>(fmax(sqrt(n2), sqrt(h2) + sqrt(l2)));
-  }
-}
-
-template <int DXP>
-__global__ __launch_bounds__(256) void km_prep_kernel(
-    const float *__restrict__ U, size_t u_hs, int C, int cpad, int dx,
-    uint16_t *ubf, float *nu, float *bnd) {
-  km_prep_row<DXP>(U, u_hs, C, cpad, dx, ubf, nu, bnd);
-}
-
-// The three subspaces' codebooks in one launch (blockIdx.z = subspace).
-struct Prep3 {
-  const float *U[3];
-  size_t u_hs[3];
-  int C[3], cpad[3], dx[3];
-  uint16_t *ubf[3];
-  float *nu[3], *bnd[3];
-};
-
-template <int D0, int D1, int D2>
-__global__ __launch_bounds__(256) void km_prep3_kernel(Prep3 P) {
-  const int m = blockIdx.z;
-  if (m == 0)
-    km_prep_row<D0>(P.U[0], P.u_hs[0], P.C[0], P.cpad[0], P.dx[0], P.ubf[0], P.nu[0], P.bnd[0]);
-  else if (m == 1)
-    km_prep_row<D1>(P.U[1], P.u_hs[1], P.C[1], P.cpad[1], P.dx[1], P.ubf[1], P.nu[1], P.bnd[1]);
-  else
-    km_prep_row<D2>(P.U[2], P.u_hs[2], P.C[2], P.cpad[2], P.dx[2], P.ubf[2], P.nu[2], P.bnd[2]);
-}
-
 // Keeps the compiler from moving this wave's LDS accesses across the call
 // (the LDS completes one wave's operations in issue order).
 __device__ __forceinline__ void wave_sync() {
@@ -233,26 +123,29 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The bound constants of one head's codebook (maxima of the per-row parts,
-// with a small upward slack on top of their fp64 evaluation).
+// The bound constants of one head's codebook.
 struct FilterBound {
   float E, Nmax, numax;
 };
 
+// From the largest residual bound and the largest canonical norm.  Nmax bounds
+// |u| (the norm's fma chain is within 2^-16 of |u|^2, or 2^-143 where it
+// underflows) and |hi| + |lo| <= (1 + 2^-8)^2 |u|.
+__device__ __forceinline__ FilterBound filter_bound(float e_max, float nu_max) {
+  const float un = sqrtf(nu_max) * 1.001f + 1e-21f;
+  return FilterBound{e_max + 1e-30f, un * 1.008f, nu_max * 1.001f};
+}
+
 // The head's bound constants from the per-wave maxima in red.
 template <int NW>
 __device__ __forceinline__ FilterBound reduce_bound(const float (*red)[NW]) {
-  float E = 0.0f, Nmax = 0.0f, numax = 0.0f;
+  float E = 0.0f, numax = 0.0f;
 #pragma unroll
   for (int i = 0; i < NW; ++i) {
     E = fmaxf(E, red[0][i]);
-    Nmax = fmaxf(Nmax, red[1][i]);
-    numax = fmaxf(numax, red[2][i]);
+    numax = fmaxf(numax, red[1][i]);
   }
-  E = E * 1.001f + 1e-30f;
-  Nmax *= 1.001f;
-  numax *= 1.001f;
-  return FilterBound{E, Nmax, numax};
+  return filter_bound(E, numax);
 }
 
 // Stages head h's two-term codebook (16-byte pieces of each row; LDS row
@@ -275,9 +168,8 @@ __device__ __forceinline__ FilterBound stage_codebook(uint16_t *Us, float *nus, 
     *reinterpret_cast<uint4 *>(&Us[r * US + 8 * q]) =
         *reinterpret_cast<const uint4 *>(ub + static_cast<size_t>(r) * (2 * DXP) + 8 * q);
   }
-  // the head's bound constants: maxima of the per-row parts, with a small
-  // upward slack on top of their fp64 evaluation
-  float e_max = 0.0f, n_max = 0.0f, nu_max = 0.0f;
+  // the head's bound constants: maxima over the rows
+  float e_max = 0.0f, nu_max = 0.0f;
   for (int r = t; r < cpad; r += 64 * NW) {
     const size_t row = static_cast<size_t>(h) * cpad + r;
     const float v = nu[row];
@@ -287,18 +179,15 @@ __device__ __forceinline__ FilterBound stage_codebook(uint16_t *Us, float *nus, 
     // -FLT_MAX / 2 and never win
     nhs[r] = -0.5f * v;
     if (r < C) {
-      e_max = fmaxf(e_max, bnd[2 * row + 0]);
-      n_max = fmaxf(n_max, bnd[2 * row + 1]);
+      e_max = fmaxf(e_max, bnd[row]);
       nu_max = fmaxf(nu_max, fabsf(v));
     }
   }
   e_max = wave_max(e_max);
-  n_max = wave_max(n_max);
   nu_max = wave_max(nu_max);
   if (lane == 0) {
     red[0][w] = e_max;
-    red[1][w] = n_max;
-    red[2][w] = nu_max;
+    red[1][w] = nu_max;
   }
   __syncthreads();
   return reduce_bound<NW>(red);
@@ -548,7 +437,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void km_assign_mfma_kernel(
   __shared__ uint32_t cand[kWavesPerBlock][kWaveCand];
   __shared__ unsigned long long best[kWavesPerBlock][32];
   __shared__ int ncand[kWavesPerBlock];
-  __shared__ float red[3][kWavesPerBlock];
+  __shared__ float red[2][kWavesPerBlock];
   __shared__ int next_slice;
   const int w = threadIdx.x >> 6;
   const SliceArgs A{X, x_hs, ld, col0, dx, n, C, cpad, U, u_hs, assign, a_hs, chunk_hist, nchunks};
@@ -605,7 +494,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void km_assign_mfma3_kernel(
   __shared__ uint32_t cand[kWavesPerBlock][kWaveCand];
   __shared__ unsigned long long best[kWavesPerBlock][32];
   __shared__ int ncand[kWavesPerBlock];
-  __shared__ float red[3][3][kWavesPerBlock];
+  __shared__ float red[3][2][kWavesPerBlock];
   __shared__ int next_unit;
   const int w = threadIdx.x >> 6;
   const int nslices = (n + 31) / 32;
@@ -783,28 +672,24 @@ __global__ __launch_bounds__(256) void km_assign_decide_kernel(
     const float *__restrict__ bnd, int C, int cpad, int nparts,
     const float *__restrict__ part, const float *__restrict__ pnx, float kappa,
     int32_t *assign, size_t a_hs, int32_t *chunk_hist, int nchunks) {
-  __shared__ float red[3][4];
+  __shared__ float red[2][4];
   const int h = blockIdx.y, t = threadIdx.x, lane = t & 63, w = t >> 6;
   // the head's bound constants, as in the assignment kernel
-  float e_max = 0.0f, n_max = 0.0f, nu_max = 0.0f;
+  float e_max = 0.0f, nu_max = 0.0f;
   for (int r = t; r < C; r += 256) {
     const size_t row = static_cast<size_t>(h) * cpad + r;
-    e_max = fmaxf(e_max, bnd[2 * row + 0]);
-    n_max = fmaxf(n_max, bnd[2 * row + 1]);
+    e_max = fmaxf(e_max, bnd[row]);
     nu_max = fmaxf(nu_max, fabsf(nu[row]));
   }
   e_max = wave_max(e_max);
-  n_max = wave_max(n_max);
   nu_max = wave_max(nu_max);
   if (lane == 0) {
     red[0][w] = e_max;
-    red[1][w] = n_max;
-    red[2][w] = nu_max;
+    red[1][w] = nu_max;
   }
   __syncthreads();
-  const float E = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3])) * 1.001f + 1e-30f;
-  const float Nmax = fmaxf(fmaxf(red[1][0], red[1][1]), fmaxf(red[1][2], red[1][3])) * 1.001f;
-  const float numax = fmaxf(fmaxf(red[2][0], red[2][1]), fmaxf(red[2][2], red[2][3])) * 1.001f;
+  const FilterBound FB = reduce_bound<4>(red);
+  const float E = FB.E, Nmax = FB.Nmax, numax = FB.numax;
   const int i = blockIdx.x * 256 + t;
   if (i >= n) return;
   const int ib = 32 - __clz(cpad - 1);
@@ -861,26 +746,10 @@ __global__ __launch_bounds__(256) void km_assign_decide_kernel(
     atomicAdd(&chunk_hist[(static_cast<size_t>(h) * nchunks + (i / kAssignBlock)) * C + arg], 1);
 }
 
-__global__ void km_zero_kernel(int32_t *p, size_t count) {
-  for (size_t i = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < count;
-       i += static_cast<size_t>(gridDim.x) * blockDim.x)
-    p[i] = 0;
-}
-
 template <int DXP>
 hipError_t launch_mfma(const KmProblem &p, bool with_hist, hipStream_t s) {
-  hipLaunchKernelGGL(km_prep_kernel<DXP>, dim3((p.cpad + 3) / 4, p.heads), dim3(256), 0, s, p.u,
-                     p.u_head_stride, p.C, p.cpad, p.dx, p.ubf, p.nu, p.bnd);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  hipError_t e = hipSuccess;
   const int nch = km_nchunks(p.n);
-  if (with_hist) {
-    const size_t cnt = static_cast<size_t>(p.heads) * nch * p.C;
-    hipLaunchKernelGGL(km_zero_kernel, dim3(static_cast<unsigned>((cnt + 255) / 256 < 4096 ? (cnt + 255) / 256 : 4096)),
-                       dim3(256), 0, s, p.chunk_hist, cnt);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
   // persistent blocks, one per CU (the codebook fills most of the LDS),
   // each over a contiguous range of (head, 32-point slice) pairs
   const long long slices = static_cast<long long>(p.heads) * ((p.n + 31) / 32);
@@ -917,29 +786,9 @@ hipError_t launch_mfma(const KmProblem &p, bool with_hist, hipStream_t s) {
   return hipGetLastError();
 }
 
-__global__ void store_sub3_kernel(Sub3 S, Sub3 *dst) { *dst = S; }
-
+// The launch arguments of the one-pass assignment (device memory).
 template <int D0, int D1, int D2>
-hipError_t launch_mfma3(const KmProblem (&p)[3], Sub3 *dev_args, bool store_args,
-                        hipStream_t s) {
-  // the three codebooks' two-term splits, norms and bound parts
-  Prep3 P{};
-  int cmax = 0;
-  for (int m = 0; m < 3; ++m) {
-    P.U[m] = p[m].u;
-    P.u_hs[m] = p[m].u_head_stride;
-    P.C[m] = p[m].C;
-    P.cpad[m] = p[m].cpad;
-    P.dx[m] = p[m].dx;
-    P.ubf[m] = p[m].ubf;
-    P.nu[m] = p[m].nu;
-    P.bnd[m] = p[m].bnd;
-    cmax = p[m].cpad > cmax ? p[m].cpad : cmax;
-  }
-  hipLaunchKernelGGL((km_prep3_kernel<D0, D1, D2>), dim3((cmax + 3) / 4, p[0].heads, 3),
-                     dim3(256), 0, s, P);
-  hipError_t e0 = hipGetLastError();
-  if (e0 != hipSuccess) return e0;
+Sub3 sub3_args(const KmProblem (&p)[3]) {
   Sub3 S{};
   int uoff = 0, noff = 0;
   const int dxp[3] = {D0, D1, D2};
@@ -956,6 +805,11 @@ hipError_t launch_mfma3(const KmProblem (&p)[3], Sub3 *dev_args, bool store_args
     uoff += q.cpad * (2 * dxp[m] + 8);
     noff += q.cpad;
   }
+  return S;
+}
+
+template <int D0, int D1, int D2>
+hipError_t launch_mfma3(const KmProblem (&p)[3], const Sub3 *dev_args, hipStream_t s) {
   const long long slices = static_cast<long long>(p[0].heads) * ((p[0].n + 31) / 32);
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
@@ -963,13 +817,6 @@ hipError_t launch_mfma3(const KmProblem (&p)[3], Sub3 *dev_args, bool store_args
     cus = 256;
   const int blocks = static_cast<int>(slices < static_cast<long long>(cus) * kWavesPerBlock
                                           ? (slices + kWavesPerBlock - 1) / kWavesPerBlock : cus);
-  // the arguments go to device memory, so each wave group loads only its
-  // own; they hold only pointers and sizes, so one store per call suffices
-  if (store_args) {
-    hipLaunchKernelGGL(store_sub3_kernel, dim3(1), dim3(1), 0, s, S, dev_args);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
   hipLaunchKernelGGL((km_assign_mfma3_kernel<D0, D1, D2>), dim3(blocks), dim3(64 * kWavesPerBlock),
                      0, s, dev_args, p[0].n, p[0].heads);
   return hipGetLastError();
@@ -995,13 +842,22 @@ bool km_assign3_ok(const KmProblem (&p)[3]) {
 
 size_t km_assign3_scratch_bytes() { return sizeof(Sub3); }
 
-hipError_t km_assign3(const KmProblem (&p)[3], void *scratch, bool store_args,
-                      hipStream_t s) {
-  Sub3 *args = static_cast<Sub3 *>(scratch);
+void km_assign3_args(const KmProblem (&p)[3], void *scratch, DeviceArgs *args) {
+  static_assert(sizeof(Sub3) % 4 == 0 && sizeof(Sub3) <= 4 * kArgWords, "arguments fit DeviceArgs");
   const int a = p[0].dxp, b = p[1].dxp;
-  if (a == 16 && b == 64) return launch_mfma3<16, 64, 64>(p, args, store_args, s);
-  if (a == 48) return launch_mfma3<48, 48, 48>(p, args, store_args, s);
-  return launch_mfma3<16, 32, 32>(p, args, store_args, s);
+  const Sub3 S = a == 16 && b == 64 ? sub3_args<16, 64, 64>(p)
+                 : a == 48 ? sub3_args<48, 48, 48>(p) : sub3_args<16, 32, 32>(p);
+  args->dst = static_cast<uint32_t *>(scratch);
+  args->words = static_cast<int>(sizeof(Sub3) / 4);
+  memcpy(args->w, &S, sizeof(Sub3));
+}
+
+hipError_t km_assign3(const KmProblem (&p)[3], void *scratch, hipStream_t s) {
+  const Sub3 *args = static_cast<const Sub3 *>(scratch);
+  const int a = p[0].dxp, b = p[1].dxp;
+  if (a == 16 && b == 64) return launch_mfma3<16, 64, 64>(p, args, s);
+  if (a == 48) return launch_mfma3<48, 48, 48>(p, args, s);
+  return launch_mfma3<16, 32, 32>(p, args, s);
 }
 
 int km_cpad(int C) { return (C + 31) / 32 * 32; }

@@ -13,7 +13,7 @@
 // allow, else 2.  All three key subspaces fit one window, so
 // one pass over K updates T, H and W together; the query codebook is split
 // over two windows.  Each block writes its sums to a slab laid out like the
-// centroids; a second kernel reduces the slabs and divides.
+// centroids; km_finish_kernel reduces the slabs and divides.
 #include <math.h>
 
 #include "common.h"
@@ -181,28 +181,6 @@ __global__ __launch_bounds__(kAccThreads) void km_accum_kernel(
   }
 }
 
-// U[h][pos] = sum over blocks / (count * 2^24), for every centroid element
-// pos of the slab layout; an empty cluster keeps its centroid.
-__global__ __launch_bounds__(256) void km_accum_finalize_kernel(
-    const AccPlan plan, int blocks, const long long *__restrict__ slab,
-    const int32_t *__restrict__ cslab, float *U, size_t u_hs) {
-  const int pos = blockIdx.x * 256 + threadIdx.x, h = blockIdx.y;
-  if (pos >= plan.S) return;
-  int m = 0;
-  while (m + 1 < plan.nsub && pos >= plan.ucol[m + 1]) ++m;
-  const int r = (pos - plan.ucol[m]) / plan.dx[m];
-  long long tot = 0;
-  int cnt = 0;
-  for (int b = 0; b < blocks; ++b) {
-    const size_t hb = static_cast<size_t>(h) * blocks + b;
-    tot += slab[hb * plan.S + pos];
-    cnt += cslab[hb * plan.SC + plan.ccol[m] + r];
-  }
-  if (cnt <= 0) return;
-  const double den = static_cast<double>(cnt) * 16777216.0;
-  U[h * u_hs + pos] = static_cast<float>(static_cast<double>(tot) / den);
-}
-
 }  // namespace
 
 bool km_accum_plan(int nsub, const int *col0, const int *dx, const int *C,
@@ -289,7 +267,7 @@ size_t km_accum_cslab_bytes(const AccPlan &p, int heads) {
 hipError_t km_accum(const AccPlan &plan, const void *x, bool bf16, size_t x_hs,
                     int ld, int n, int heads, const int32_t *assign,
                     size_t a_hs, size_t a_ss, long long *slab, int32_t *cslab,
-                    float *U, size_t u_hs, int32_t *status, hipStream_t s) {
+                    int32_t *status, hipStream_t s) {
   const dim3 grid(plan.blocks, plan.nwin, heads);
   const bool check = status != nullptr;
   int ce = 0;  // ceil(log2 n)
@@ -330,10 +308,6 @@ hipError_t km_accum(const AccPlan &plan, const void *x, bool bf16, size_t x_hs,
 #undef SCOPE_ACCUM_T
 #undef SCOPE_ACCUM_K
 #undef SCOPE_ACCUM
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(km_accum_finalize_kernel, dim3((plan.S + 255) / 256, heads),
-                     dim3(256), 0, s, plan, plan.blocks, slab, cslab, U, u_hs);
   return hipGetLastError();
 }
 
