@@ -27,7 +27,7 @@ struct KmProblem {
   int32_t *chunk_hist;    // [heads][nchunks][C]
   int32_t *chunk_rel;     // [heads][nchunks][C]
   int heads;
-  // matrix-core assignment (bf16 inputs): bf16 copy of the centroids,
+  // matrix-core assignment: two-term bf16 copy of the centroids,
   // their squared norms and the error-bound constants, refreshed per pass
   bool mfma;
   int cpad, dxp;          // centroids padded to 32, channels padded to 16
@@ -39,8 +39,8 @@ struct KmProblem {
   float *part, *pnx;
 };
 
-// Whether the matrix-core assignment applies: bf16 rows at even offsets and
-// at most 1024 centroids (codebooks beyond the LDS are streamed in chunks).
+// Whether the matrix-core assignment applies: fp32 rows, or bf16 rows at even
+// offsets, and at most 1024 centroids (codebooks beyond the LDS are streamed in chunks).
 bool km_mfma_ok(bool bf16, int ld, int col0, int dx, int C);
 int km_parts(int C, int dx);
 // floats of KmProblem::part and ::pnx together (0 when the codebook fits)

@@ -19,14 +19,16 @@ namespace scope {
 
 namespace {
 
+// The vector-unit assignment, for bf16 rows with an odd offset, width or row
+// length, which the matrix-core assignment's paired loads do not take.
 // One point per thread, its channels held in registers (zero padded to DXP:
 // a trailing fma(0, 0, acc) leaves the score unchanged).  Centroids are
 // staged through LDS transposed, CB at a time, and read as wave-wide
 // broadcasts.  Scores are compared in ascending centroid order with a
 // strict '<', so ties go to the lowest index.
-template <typename T, int DXP>
+template <int DXP>
 __global__ __launch_bounds__(kAssignBlock) void km_assign_kernel(
-    const T *__restrict__ X, size_t x_hs, int ld, int col0, int dx, int n,
+    const uint16_t *__restrict__ X, size_t x_hs, int ld, int col0, int dx, int n,
     const float *__restrict__ U, size_t u_hs, int C, int32_t *assign,
     size_t a_hs, int32_t *chunk_hist, int nchunks) {
   constexpr int CB = 64;
@@ -36,7 +38,7 @@ __global__ __launch_bounds__(kAssignBlock) void km_assign_kernel(
   const int h = blockIdx.y, t = threadIdx.x;
   const int i = blockIdx.x * kAssignBlock + t;
   const bool valid = i < n;
-  const T *xrow = X + h * x_hs + static_cast<size_t>(valid ? i : 0) * ld + col0;
+  const uint16_t *xrow = X + h * x_hs + static_cast<size_t>(valid ? i : 0) * ld + col0;
   float xr[DXP];
 #pragma unroll
   for (int c = 0; c < DXP; ++c) xr[c] = (c < dx) ? load_elem(xrow, c) : 0.0f;
@@ -235,14 +237,13 @@ __global__ void gather_channels_kernel(const T *__restrict__ src, T *dst,
   dst[i] = src[r * d + map.chan[t]];
 }
 
-template <typename T>
 hipError_t assign_dispatch(const KmProblem &p, bool with_hist, hipStream_t s) {
   const dim3 grid(km_nchunks(p.n), p.heads);
-  const T *x = static_cast<const T *>(p.x);
+  const uint16_t *x = static_cast<const uint16_t *>(p.x);
   int32_t *hist = with_hist ? p.chunk_hist : nullptr;
   const int nch = km_nchunks(p.n);
 #define SCOPE_ASSIGN(DXP)                                                      \
-  hipLaunchKernelGGL((km_assign_kernel<T, DXP>), grid, dim3(kAssignBlock), 0, s, \
+  hipLaunchKernelGGL((km_assign_kernel<DXP>), grid, dim3(kAssignBlock), 0, s, \
                      x, p.x_head_stride, p.ld, p.col0, p.dx, p.n, p.u,          \
                      p.u_head_stride, p.C, p.assign, p.a_head_stride, hist, nch)
   if (p.dx <= 16) SCOPE_ASSIGN(16);
@@ -260,8 +261,7 @@ hipError_t km_assign_mfma(const KmProblem &p, bool with_hist, hipStream_t s);
 
 hipError_t km_assign(const KmProblem &p, bool with_hist, hipStream_t s) {
   if (p.mfma) return km_assign_mfma(p, with_hist, s);
-  return p.bf16 ? assign_dispatch<uint16_t>(p, with_hist, s)
-                : assign_dispatch<float>(p, with_hist, s);
+  return assign_dispatch(p, with_hist, s);
 }
 
 hipError_t km_group(const KmProblem &p, hipStream_t s) {
