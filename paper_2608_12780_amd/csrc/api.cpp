@@ -192,10 +192,31 @@ size_t select_ws(const scope_shape *s, int c_q, void *base, SelectWs *w) {
   return cv.used;
 }
 
-size_t attn_ws(const scope_shape *s, int c_q, void *base, int4 **items) {
+// The work list is all that the call cannot do without; a workspace that also
+// holds the rest (scope_workspace_size covers it) lets it copy fp32 K and V to
+// bf16 and split slots.  *list: the bytes of the list alone.
+size_t attn_ws(const scope_shape *s, int c_q, void *base, size_t bytes, size_t *list,
+               scope::AttnScratch *w) {
   Carver cv(base);
-  int4 *it = cv.take<int4>(2 * static_cast<size_t>(s->heads) * scope::attn_items_per_head(s->n, c_q));
-  if (items) *items = it;
+  const size_t H = static_cast<size_t>(s->heads);
+  scope::AttnScratch a{};
+  a.items = cv.take<int4>(2 * H * scope::attn_items_per_head(s->n, c_q));
+  if (list) *list = cv.used;
+  const bool bf16 = s->dtype == SCOPE_BF16;
+  const bool copies = scope::attention_copies_kv(s->n, s->d, bf16);
+  if (copies) a.kv16 = cv.take<uint16_t>(2 * H * s->n * s->d);
+  // the register-staged fp32 kernel has neither order nor pieces
+  if ((bf16 || copies) && scope::attention_ordered(s->heads, s->n, s->d, c_q)) {
+    a.pieces = scope::attention_pieces(s->heads, s->n, s->d, c_q);
+    a.order = cv.take<int4>(scope::attention_order_entries(s->heads, s->n, c_q, a.pieces));
+    a.part = cv.take<float>(a.pieces * scope::attention_piece_floats(s->d));
+  }
+  if (bytes < cv.used) {
+    a.kv16 = nullptr;
+    a.order = nullptr;
+    a.pieces = 0;
+  }
+  if (w) *w = a;
   return cv.used;
 }
 
@@ -350,7 +371,7 @@ int32_t scope_workspace_size(const scope_shape *shape, int32_t c_q,
   size_t need = query_ws(shape, c_q, nullptr, nullptr);
   size_t k = key_ws(shape, c_m, nullptr, nullptr);
   size_t s = select_ws(shape, c_q, nullptr, nullptr);
-  size_t a = attn_ws(shape, c_q, nullptr, nullptr);
+  size_t a = attn_ws(shape, c_q, nullptr, 0, nullptr, nullptr);
   if (k > need) need = k;
   if (s > need) need = s;
   if (a > need) need = a;
@@ -631,7 +652,7 @@ int32_t scope_partition_workspace_size(const scope_shape *shape, int32_t c_q,
   for (size_t x : {part_key_ws(shape, part, nullptr, nullptr),
                    part_table_ws(shape, c_q, nullptr, nullptr),
                    select_ws(shape, c_q, nullptr, nullptr),
-                   attn_ws(shape, c_q, nullptr, nullptr)})
+                   attn_ws(shape, c_q, nullptr, 0, nullptr, nullptr)})
     if (x > need) need = x;
   *bytes = need;
   return SCOPE_OK;
@@ -830,12 +851,12 @@ int32_t scope_sparse_attention_noalloc(const scope_shape *shape, const void *q,
   const size_t entries = 2 * static_cast<size_t>(shape->heads) *
                          scope::attn_items_per_head(shape->n, c_q);
   if (entries > scope::kAttnScratchItems) return SCOPE_ERR_SCRATCH_LIMIT;
-  int4 *list = nullptr;
-  SCOPE_TRY(scope::attention_scratch(&list));
+  scope::AttnScratch w{};  // the list alone: no split slots, no copies
+  SCOPE_TRY(scope::attention_scratch(&w.items));
   SCOPE_TRY(scope::attention_run(shape->heads, shape->n, shape->d,
                                  shape->dtype == SCOPE_BF16, q, k, v, o, c_q,
                                  offsets, perm, sel_counts, sel_idx,
-                                 attention_scale(shape, scale), list,
+                                 attention_scale(shape, scale), w,
                                  static_cast<hipStream_t>(stream)));
   return SCOPE_OK;
 }
@@ -850,14 +871,15 @@ int32_t scope_sparse_attention(const scope_shape *shape, const void *q,
   int32_t st = check_attention(shape, q, k, v, c_q, offsets, perm, sel_counts,
                                sel_idx, scale, o);
   if (st) return st;
-  const size_t need = attn_ws(shape, c_q, nullptr, nullptr);
-  if ((st = check_ws(workspace, ws_bytes, need))) return st;
-  int4 *items = nullptr;
-  attn_ws(shape, c_q, workspace, &items);
+  size_t list = 0;
+  attn_ws(shape, c_q, nullptr, 0, &list, nullptr);
+  if ((st = check_ws(workspace, ws_bytes, list))) return st;
+  scope::AttnScratch w{};
+  attn_ws(shape, c_q, workspace, ws_bytes, nullptr, &w);
   SCOPE_TRY(scope::attention_run(shape->heads, shape->n, shape->d,
                                  shape->dtype == SCOPE_BF16, q, k, v, o, c_q,
                                  offsets, perm, sel_counts, sel_idx,
-                                 attention_scale(shape, scale), items,
+                                 attention_scale(shape, scale), w,
                                  static_cast<hipStream_t>(stream)));
   return SCOPE_OK;
 }

@@ -15,10 +15,10 @@
 // (ds_read_b64_tr_b16).  K/V tiles are double buffered: the next tiles'
 // gathers are in flight during the MFMAs.  bf16 gathers go through buffer
 // resources, whose range checks turn every out-of-range index into a zero
-// read instead of a fault.  At d = 128 with bf16 inputs (attn_kernel_dma)
-// the buffer unit writes the gathered rows straight into LDS; fp32 inputs
-// (rounded to bf16 on the way) and d = 64 stage rows through registers
-// (attn_kernel).
+// read instead of a fault, and the buffer unit writes the gathered rows
+// straight into LDS (attn_kernel_dma).  fp32 inputs are rounded to bf16: K and
+// V by one pass into the workspace, or without workspace row by row through
+// registers (attn_kernel).
 #include <math.h>
 
 #include <mutex>
@@ -67,17 +67,18 @@ __device__ __forceinline__ uint4 load8(const void *base, size_t elem) {
   }
 }
 
-// Work items run in list order: heads one after the other and, within a
+// Work slots run in list order: heads one after the other and, within a
 // head, by estimated cost, largest first, with a cluster's row chunks
 // adjacent.  All XCDs work on the same head at a time, so one head's K/V
 // (60 MB at 118800 x 128 bf16) is what the 256 MB memory-side cache has to
-// hold.
+// hold.  (Where several heads' fit there, attn_plan_kernel gives the order.)
 //
-// Block b runs on XCD b mod 8.  Runs of kRun consecutive work items (the
+// Block b runs on XCD b mod 8.  Runs of kRun consecutive work slots (the
 // chunks of one cluster, which gather the same K/V rows) go to one XCD so
-// that they share its L2; windows of 8 * kRun items still follow the list
+// that they share its L2; windows of 8 * kRun slots still follow the list
 // order.  A partial last window keeps the identity map.
 constexpr int kXcds = 8, kRun = 4;
+constexpr uint64_t kMemorySideCache = 256ull << 20;
 __device__ __forceinline__ int xcd_item(int b, int total) {
   constexpr int W = kXcds * kRun;
   const int w0 = b / W * W;
@@ -86,7 +87,9 @@ __device__ __forceinline__ int xcd_item(int b, int total) {
   return w0 + (r % kXcds) * kRun + r / kXcds;
 }
 
-template <int D, bool BF16IN>
+// fp32 inputs without workspace for bf16 copies of K and V: rows are rounded
+// to bf16 on the way through registers.
+template <int D>
 __global__ __launch_bounds__(kNW * 64) void attn_kernel(
     int n, int c_q, int items_per_head, int total_items,
     const void *__restrict__ qv, const void *__restrict__ kv,
@@ -136,7 +139,7 @@ __global__ __launch_bounds__(kNW * 64) void attn_kernel(
     }
 #pragma unroll
     for (int s = 0; s < D / 16; ++s)
-      qf[qb][s] = as_bf16x8(qvalid[qb] ? load8<BF16IN>(qv, hoff + static_cast<size_t>(qi[qb]) * D + 16 * s + 8 * hf)
+      qf[qb][s] = as_bf16x8(qvalid[qb] ? load8<false>(qv, hoff + static_cast<size_t>(qi[qb]) * D + 16 * s + 8 * hf)
                                        : make_uint4(0, 0, 0, 0));
   }
   const bool wave_active = w * 32 * kQB < rows;
@@ -171,15 +174,6 @@ __global__ __launch_bounds__(kNW * 64) void attn_kernel(
   // 16-key step; lane L then holds 4 consecutive keys of channel L%32
   const int tr_off = (4 * (lane >> 5) + ((lane & 15) >> 2)) * KSV + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
   const void *src = is_v ? vv : kv;
-  // bf16 inputs are gathered through buffer resources: out-of-range offsets
-  // (index slots past the key set, any bad row) read as zero in hardware,
-  // so no index needs clamping; the host guarantees n * D * 2 < 2^32
-  const __amdgpu_buffer_rsrc_t rsel = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<int32_t *>(sel), static_cast<short>(0), r * 4, 0x00020000);
-  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t *>(static_cast<const uint16_t *>(src) + hoff), static_cast<short>(0),
-      static_cast<int>(static_cast<uint32_t>(n) * (D * 2)), 0x00020000);
-
   // Software pipeline, two tiles deep: step T requests the row indices of
   // tile T+3 first and the rows of tile T+2 after its compute, so waiting for
   // indices never waits for rows in flight (vector loads complete in order)
@@ -191,22 +185,14 @@ __global__ __launch_bounds__(kNW * 64) void attn_kernel(
   auto load_sel = [&](int tile, int (&sx)[NR]) {
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
-      if constexpr (BF16IN)
-        sx[i] = __builtin_amdgcn_raw_buffer_load_b32(rsel, (tile * kBN + key0 + i % RK) * 4, 0, 0);
-      else
-        sx[i] = sel[min(tile * kBN + key0 + i % RK, n - 1)];
+      sx[i] = sel[min(tile * kBN + key0 + i % RK, n - 1)];
     }
   };
   auto load_rows = [&](const int (&sx)[NR], uint4 (&dx)[NR]) {
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
-      if constexpr (BF16IN) {
-        const auto v4 = __builtin_amdgcn_raw_buffer_load_b128(rsrc, sx[i] * (D * 2) + 16 * c8, 0, 0);
-        dx[i] = make_uint4(v4[0], v4[1], v4[2], v4[3]);
-      } else {
-        const int row = min(max(sx[i], 0), n - 1);
-        dx[i] = load8<BF16IN>(src, hoff + static_cast<size_t>(row) * D + 8 * c8);
-      }
+      const int row = min(max(sx[i], 0), n - 1);
+      dx[i] = load8<false>(src, hoff + static_cast<size_t>(row) * D + 8 * c8);
     }
   };
   auto store_rows = [&](int buf, const uint4 (&dx)[NR]) {
@@ -361,36 +347,68 @@ __global__ __launch_bounds__(kNW * 64) void attn_kernel(
         const size_t at = hoff + static_cast<size_t>(qi[qb]) * D + dim;
         const float o0 = oacc[qb][db][4 * i + 0] * inv, o1 = oacc[qb][db][4 * i + 1] * inv;
         const float o2 = oacc[qb][db][4 * i + 2] * inv, o3 = oacc[qb][db][4 * i + 3] * inv;
-        if (BF16IN) {
-          *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(ov) + at) =
-              make_uint2(pack_bf16(o0, o1), pack_bf16(o2, o3));
-        } else {
-          *reinterpret_cast<float4 *>(static_cast<float *>(ov) + at) = make_float4(o0, o1, o2, o3);
-        }
+        *reinterpret_cast<float4 *>(static_cast<float *>(ov) + at) = make_float4(o0, o1, o2, o3);
       }
   }
 }
 
-// bf16 inputs at d = 128: the same computation with the K/V rows gathered
-// straight into LDS by the buffer unit (one 1 KB load per 4 rows, no
-// staging registers).  Rows land unpadded, so 16-byte slots are
-// XOR-swizzled: slot = chunk ^ (row mod 16) in K tiles (16-row b128 reads)
-// and chunk ^ 4 (row mod 4) in V tiles (4-row transposing reads).  A work
-// slot may hold two chunks (A, B) of different clusters: A's waves come
-// first, each chunk has its own tiles, and every wave gathers its share of
-// both.  The four tile buffers (K and V, two steps) are distinct LDS
-// objects, each holding the tiles of both chunks, so the compiler's waits
-// for the loads into one never hold up the reads of another.
-using DmaTile = uint16_t[2][kBN * 128];
+// Split slots: a slot's keys cut into `split` pieces, each run by a block of its
+// own, joined by attn_merge_kernel.  A slot of fewer than kSplitTiles tiles
+// stays whole (small calls keep bit for bit the result of the call without
+// workspace), and a piece has at least kPieceTiles.
+constexpr int kSplitTiles = 64, kPieceTiles = 8;
+template <int D>
+constexpr int kPieceFloats = kBM * (D + 2);
+__device__ __forceinline__ int key_tiles(const int4 &e) { return e.z > 0 ? (e.w + kBN - 1) / kBN : 0; }
+__device__ __forceinline__ int slot_split(const int4 &ia, const int4 &ib, int want) {
+  const int nt = max(key_tiles(ia), key_tiles(ib));
+  return nt < kSplitTiles ? 1 : min(want, nt / kPieceTiles);
+}
+// Cuts the entry to piece i of `split`; returns its first key.
+__device__ __forceinline__ int key_range(int4 *e, int i, int split) {
+  const int nt = key_tiles(*e);
+  const int t0 = nt * i / split, t1 = nt * (i + 1) / split;
+  const int k0 = t0 * kBN;
+  e->w = max(min(e->w - k0, (t1 - t0) * kBN), 0);
+  return k0;
+}
 
-template <bool PAIRED>
+// The same computation with bf16 K/V rows gathered straight into LDS by the
+// buffer unit (one 1 KB load per 4 rows at d = 128, per 8 rows at d = 64; no
+// staging registers).  fp32 inputs come here too, their K and V rounded to
+// bf16 in the workspace by one pass before (Q is rounded on load, O written in
+// fp32): the same values as rounding each gathered row.  Rows land unpadded,
+// so 16-byte slots are XOR-swizzled.  d = 128 (a row is all 64 banks): slot =
+// chunk ^ (row mod 16) in K tiles (16-row b128 reads) and chunk ^ 4 (row mod
+// 4) in V tiles (4-row transposing reads).  d = 64 (two rows span the banks):
+// chunk ^ (row / 2 mod 8) in K tiles, chunk ^ 4 (row / 2 mod 2) in V tiles.  A
+// work slot may hold two chunks (A, B) of different clusters: A's waves come
+// first, each chunk has its own tiles, and every wave gathers its share of
+// both.  The four tile buffers (K and V, two steps) are distinct LDS objects,
+// each holding the tiles of both chunks, so the compiler's waits for the loads
+// into one never hold up the reads of another.
+template <int D>
+using DmaTile = uint16_t[2][kBN * D];
+
+//
+// ia, ib: the slot's entries with r the keys of this block, which start at
+// key ka, kb of the clusters' lists.  part: null, or the piece's place for its
+// unnormalised results: O as [D / 4][kBM] float4 over the block's query slots
+// (32 w + lane), then [kBM] (running max, row sum).
+template <int D, bool BF16IO, bool PAIRED>
 __device__ __forceinline__ void attn_dma_body(
-    int n, int c_q, int h, int4 ia, int4 ib, const void *__restrict__ qv,
+    int n, int c_q, int h, int4 ia, int4 ib, int ka, int kb, float *part,
+    const void *__restrict__ qv,
     const void *__restrict__ kv, const void *__restrict__ vv, void *ov,
     const int32_t *__restrict__ offsets, const int32_t *__restrict__ perm,
-    const int32_t *__restrict__ sel_idx, float scale_log2, DmaTile &K0, DmaTile &K1,
-    DmaTile &V0, DmaTile &V1) {
-  constexpr int D = 128;
+    const int32_t *__restrict__ sel_idx, float scale_log2, DmaTile<D> &K0, DmaTile<D> &K1,
+    DmaTile<D> &V0, DmaTile<D> &V1) {
+  constexpr int CH = D / 8;        // 16-byte chunks per row
+  constexpr int RPL = 64 / CH;     // rows per gather load
+  constexpr int NG = 8 / RPL;      // gather loads per wave, tile and matrix
+  // the 16-byte slot of a row's chunk 0 (chunk c: slot ^ c)
+  auto k_swz = [](int row) { return D == 128 ? row & 15 : (row >> 1) & 7; };
+  auto v_swz = [](int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); };
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int l32 = lane & 31, hf = lane >> 5;
   const size_t hoff = static_cast<size_t>(h) * n * D;
@@ -412,7 +430,7 @@ __device__ __forceinline__ void attn_dma_body(
   bf16x8 qf[D / 16];
 #pragma unroll
   for (int s = 0; s < D / 16; ++s)
-    qf[s] = as_bf16x8(qvalid ? load8<true>(qv, hoff + static_cast<size_t>(qi) * D + 16 * s + 8 * hf)
+    qf[s] = as_bf16x8(qvalid ? load8<BF16IO>(qv, hoff + static_cast<size_t>(qi) * D + 16 * s + 8 * hf)
                              : make_uint4(0, 0, 0, 0));
   const bool wave_active = wl * 32 < rows;
 
@@ -427,53 +445,53 @@ __device__ __forceinline__ void attn_dma_body(
   const int ntA = (ia.w + kBN - 1) / kBN, ntB = PAIRED ? (ib.w + kBN - 1) / kBN : 0;
   const int ntiles = ntA > ntB ? ntA : ntB;
   const int nt_own = (r + kBN - 1) / kBN;
-  auto sel_rsrc = [&](const int4 &e) {
+  auto sel_rsrc = [&](const int4 &e, int k0) {
     return __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<int32_t *>(sel_idx + (static_cast<size_t>(h) * c_q + e.x) * n),
+        const_cast<int32_t *>(sel_idx + (static_cast<size_t>(h) * c_q + e.x) * n + k0),
         static_cast<short>(0), e.w * 4, 0x00020000);
   };
-  const __amdgpu_buffer_rsrc_t rselA = sel_rsrc(ia);
-  const __amdgpu_buffer_rsrc_t rselB = sel_rsrc(PAIRED ? ib : ia);
+  const __amdgpu_buffer_rsrc_t rselA = sel_rsrc(ia, ka);
+  const __amdgpu_buffer_rsrc_t rselB = PAIRED ? sel_rsrc(ib, kb) : rselA;
   const int nbytes = static_cast<int>(static_cast<uint32_t>(n) * (D * 2));
   const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint16_t *>(static_cast<const uint16_t *>(kv) + hoff), static_cast<short>(0), nbytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint16_t *>(static_cast<const uint16_t *>(vv) + hoff), static_cast<short>(0), nbytes, 0x00020000);
 
-  // gathers: wave w brings rows 8w .. 8w+7 of each chunk's tile, four rows
-  // (1 KB) per load; lane L covers row 8w + 4i + L/16, slot L%16, and
+  // gathers: wave w brings rows 8w .. 8w+7 of each chunk's tile, RPL rows
+  // (1 KB) per load; lane L covers row 8w + RPL i + L/CH, slot L%CH, and
   // fetches the chunk that the swizzle puts there.  Past the end of a
   // chunk's key list its index loads read zeros, so its gathers fetch row 0
   // (the pairing matches key counts, so few such tiles).
   struct Idx {
-    int a[2], b[2];
+    int a[NG], b[NG];
   };
   auto load_idx = [&](int tile, Idx &ix) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int at = (tile * kBN + 8 * w + 4 * i + (lane >> 4)) * 4;
+    for (int i = 0; i < NG; ++i) {
+      const int at = (tile * kBN + 8 * w + RPL * i + lane / CH) * 4;
       ix.a[i] = __builtin_amdgcn_raw_buffer_load_b32(rselA, at, 0, 0);
       ix.b[i] = PAIRED ? __builtin_amdgcn_raw_buffer_load_b32(rselB, at, 0, 0) : 0;
     }
   };
   auto gather_k = [&](uint16_t (*kbuf)[kBN * D], const Idx &ix) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int row = 8 * w + 4 * i + (lane >> 4), s = lane & 15;
-      const int col = 16 * (s ^ (row & 15));
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, kbuf[0] + (8 * w + 4 * i) * D, 16, ix.a[i] * (D * 2) + col, 0, 0, 0);
+    for (int i = 0; i < NG; ++i) {
+      const int row = 8 * w + RPL * i + lane / CH, s = lane % CH;
+      const int col = 16 * (s ^ k_swz(row));
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, kbuf[0] + (8 * w + RPL * i) * D, 16, ix.a[i] * (D * 2) + col, 0, 0, 0);
       if constexpr (PAIRED)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, kbuf[1] + (8 * w + 4 * i) * D, 16, ix.b[i] * (D * 2) + col, 0, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, kbuf[1] + (8 * w + RPL * i) * D, 16, ix.b[i] * (D * 2) + col, 0, 0, 0);
     }
   };
   auto gather_v = [&](uint16_t (*vbuf)[kBN * D], const Idx &ix) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int row = 8 * w + 4 * i + (lane >> 4), s = lane & 15;
-      const int col = 16 * (s ^ (4 * (row & 3)));
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, vbuf[0] + (8 * w + 4 * i) * D, 16, ix.a[i] * (D * 2) + col, 0, 0, 0);
+    for (int i = 0; i < NG; ++i) {
+      const int row = 8 * w + RPL * i + lane / CH, s = lane % CH;
+      const int col = 16 * (s ^ v_swz(row));
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, vbuf[0] + (8 * w + RPL * i) * D, 16, ix.a[i] * (D * 2) + col, 0, 0, 0);
       if constexpr (PAIRED)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, vbuf[1] + (8 * w + 4 * i) * D, 16, ix.b[i] * (D * 2) + col, 0, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, vbuf[1] + (8 * w + RPL * i) * D, 16, ix.b[i] * (D * 2) + col, 0, 0, 0);
     }
   };
 
@@ -481,7 +499,7 @@ __device__ __forceinline__ void attn_dma_body(
   // 16-key step, chunk 4db + 2((L/16)%2) + (L%4)/2, half L%2
   const int rl = 4 * (lane >> 5) + ((lane & 15) >> 2);
   const int vch = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
-  const int vsw = 4 * (rl & 3);
+  const int vsw = v_swz(rl);
   const int vhalf = 4 * (lane & 1);   // elements
 
   // tile T of this wave's chunk from kt/vt0; the gathers of tile T+1 into
@@ -499,12 +517,12 @@ __device__ __forceinline__ void attn_dma_body(
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
       for (int e = 0; e < 16; ++e) sacc[kb][e] = 0.0f;
-    const int krow = l32;  // + 32 kb; the swizzle sees row mod 16 only
+    const int krow = l32;  // + 32 kb, which the swizzle does not see
 #pragma unroll
     for (int s = 0; s < D / 16; ++s)
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb) {
-        const int slot = (2 * s + hf) ^ (krow & 15);
+        const int slot = (2 * s + hf) ^ k_swz(krow);
         const bf16x8 a = as_bf16x8(*reinterpret_cast<const uint4 *>(
             &kt[(kb * 32 + krow) * D + 8 * slot]));
         sacc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[s], sacc[kb], 0, 0, 0);
@@ -512,7 +530,7 @@ __device__ __forceinline__ void attn_dma_body(
     // each K operand is read from LDS two MFMAs ahead of its use
     __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
 #pragma unroll
-    for (int i = 0; i < 14; ++i) {
+    for (int i = 0; i < D / 8 - 2; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
       __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
     }
@@ -625,6 +643,19 @@ __device__ __forceinline__ void attn_dma_body(
 
   // lanes l and l^32 hold the two halves of one query's row sum
   const float l_tot = l_run + __shfl_xor(l_run, 32);
+  if (part) {
+    if (!wave_active) return;
+    float4 *po = reinterpret_cast<float4 *>(part) + 32 * w + l32;
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        po[(8 * db + 2 * i + hf) * kBM] = make_float4(oacc[db][4 * i + 0], oacc[db][4 * i + 1],
+                                                      oacc[db][4 * i + 2], oacc[db][4 * i + 3]);
+    if (hf == 0)
+      *reinterpret_cast<float2 *>(part + D * kBM + 2 * (32 * w + l32)) = make_float2(m_run, l_tot);
+    return;
+  }
   if (!qvalid) return;
   const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
 #pragma unroll
@@ -635,33 +666,317 @@ __device__ __forceinline__ void attn_dma_body(
       const size_t at = hoff + static_cast<size_t>(qi) * D + dim;
       const float o0 = oacc[db][4 * i + 0] * inv, o1 = oacc[db][4 * i + 1] * inv;
       const float o2 = oacc[db][4 * i + 2] * inv, o3 = oacc[db][4 * i + 3] * inv;
-      *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(ov) + at) =
-          make_uint2(pack_bf16(o0, o1), pack_bf16(o2, o3));
+      if constexpr (BF16IO)
+        *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(ov) + at) =
+            make_uint2(pack_bf16(o0, o1), pack_bf16(o2, o3));
+      else
+        *reinterpret_cast<float4 *>(static_cast<float *>(ov) + at) = make_float4(o0, o1, o2, o3);
     }
 }
 
-__global__ __launch_bounds__(kNW * 64) void attn_kernel_dma(
+// d = 128: 192 registers, one block (two waves per SIMD) per CU.  d = 64 is
+// bound by the softmax's vector instructions (per tile and wave about 880
+// cycles against 512 of MFMA), so two blocks share a CU.
+template <int D, bool BF16IO>
+__global__ __launch_bounds__(kNW * 64)
+__attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2))) void attn_kernel_dma(
     int n, int c_q, int items_per_head, int total_items,
     const void *__restrict__ qv, const void *__restrict__ kv,
     const void *__restrict__ vv, void *ov, const int32_t *__restrict__ offsets,
     const int32_t *__restrict__ perm, const int32_t *__restrict__ sel_idx,
-    const int4 *__restrict__ items, float scale_log2) {
-  __shared__ __attribute__((aligned(16))) DmaTile K0;
-  __shared__ __attribute__((aligned(16))) DmaTile K1;
-  __shared__ __attribute__((aligned(16))) DmaTile V0;
-  __shared__ __attribute__((aligned(16))) DmaTile V1;
-  const int item = xcd_item(static_cast<int>(blockIdx.x), total_items);
-  if (item >= total_items) return;
+    const int4 *__restrict__ items, const int4 *__restrict__ order, float *part, float scale_log2) {
+  __shared__ __attribute__((aligned(16))) DmaTile<D> K0;
+  __shared__ __attribute__((aligned(16))) DmaTile<D> K1;
+  __shared__ __attribute__((aligned(16))) DmaTile<D> V0;
+  __shared__ __attribute__((aligned(16))) DmaTile<D> V1;
+  int item, piece = 0, split = 1;
+  float *po = nullptr;
+  if (order) {
+    const int4 e = order[blockIdx.x];  // (slot, piece, pieces, place)
+    item = e.x;
+    piece = e.y;
+    split = e.z;
+    if (split > 1) po = part + static_cast<size_t>(e.w) * kPieceFloats<D>;
+  } else {
+    item = xcd_item(static_cast<int>(blockIdx.x), total_items);
+  }
+  if (item < 0 || item >= total_items) return;
   const int h = item / items_per_head;
-  const int4 ia = items[2 * item], ib = items[2 * item + 1];
+  int4 ia = items[2 * item], ib = items[2 * item + 1];
   if (ia.z <= 0) return;
+  int ka = 0, kb = 0;
+  if (split > 1) {
+    ka = key_range(&ia, piece, split);
+    kb = key_range(&ib, piece, split);
+  }
   // one block-uniform branch: a lone chunk gathers one set of tiles
   if (ib.z > 0)
-    attn_dma_body<true>(n, c_q, h, ia, ib, qv, kv, vv, ov, offsets, perm, sel_idx, scale_log2,
-                        K0, K1, V0, V1);
+    attn_dma_body<D, BF16IO, true>(n, c_q, h, ia, ib, ka, kb, po, qv, kv, vv, ov, offsets, perm,
+                                   sel_idx, scale_log2, K0, K1, V0, V1);
   else
-    attn_dma_body<false>(n, c_q, h, ia, ib, qv, kv, vv, ov, offsets, perm, sel_idx, scale_log2,
-                         K0, K1, V0, V1);
+    attn_dma_body<D, BF16IO, false>(n, c_q, h, ia, ib, ka, kb, po, qv, kv, vv, ov, offsets, perm,
+                                    sel_idx, scale_log2, K0, K1, V0, V1);
+}
+
+// Joins the pieces of one split slot: per query the largest running max, the
+// sums rescaled to it in piece order, and the normalised result.  Thread t
+// holds query slot t % kBM and every kMergeGroups-th group of 4 channels.
+constexpr int kMergeGroups = 4;
+template <int D, bool BF16IO>
+__global__ __launch_bounds__(kBM *kMergeGroups) void attn_merge_kernel(
+    int n, int c_q, int items_per_head, const int32_t *__restrict__ offsets,
+    const int32_t *__restrict__ perm, const int4 *__restrict__ items,
+    const int4 *__restrict__ merges, const float *__restrict__ part, void *ov) {
+  const int4 e = merges[blockIdx.x];  // (slot, -, pieces, first place)
+  const int split = e.z;
+  if (split <= 1) return;
+  const int h = e.x / items_per_head;
+  const int4 ia = items[2 * static_cast<size_t>(e.x)], ib = items[2 * static_cast<size_t>(e.x) + 1];
+  const int slot = threadIdx.x % kBM, g0 = threadIdx.x / kBM;
+  // the query of this slot: A's waves first, then B's
+  const int wa = (ia.z + 31) >> 5;
+  const int4 it = (slot >> 5) >= wa ? ib : ia;
+  const int ql = slot - ((slot >> 5) >= wa ? 32 * wa : 0);
+  if (ql >= it.z) return;
+  const int pb = offsets[static_cast<size_t>(h) * (c_q + 1) + it.x] + it.y + ql;
+  const int qi = min(max(perm[static_cast<size_t>(h) * n + min(max(pb, 0), n - 1)], 0), n - 1);
+  const float *p0 = part + static_cast<size_t>(e.w) * kPieceFloats<D>;
+  const size_t step = kPieceFloats<D>;
+  float m = -INFINITY, l = 0.0f;
+  for (int i = 0; i < split; ++i) {
+    const float2 ml = *reinterpret_cast<const float2 *>(p0 + i * step + D * kBM + 2 * slot);
+    if (ml.y > 0.0f) {
+      const float mn = fmaxf(m, ml.x);
+      l = l * __builtin_amdgcn_exp2f(m - mn) + ml.y * __builtin_amdgcn_exp2f(ml.x - mn);
+      m = mn;
+    }
+  }
+  const float inv = l > 0.0f ? 1.0f / l : 0.0f;
+  float4 o[D / 4 / kMergeGroups];
+#pragma unroll
+  for (int k = 0; k < D / 4 / kMergeGroups; ++k) o[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  for (int i = 0; i < split; ++i) {
+    const float2 ml = *reinterpret_cast<const float2 *>(p0 + i * step + D * kBM + 2 * slot);
+    const float w = ml.y > 0.0f ? __builtin_amdgcn_exp2f(ml.x - m) : 0.0f;
+    const float4 *po = reinterpret_cast<const float4 *>(p0 + i * step) + slot;
+#pragma unroll
+    for (int k = 0; k < D / 4 / kMergeGroups; ++k) {
+      const float4 v = po[(g0 + kMergeGroups * k) * kBM];
+      o[k].x = fmaf(v.x, w, o[k].x);
+      o[k].y = fmaf(v.y, w, o[k].y);
+      o[k].z = fmaf(v.z, w, o[k].z);
+      o[k].w = fmaf(v.w, w, o[k].w);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < D / 4 / kMergeGroups; ++k) {
+    const size_t to = (static_cast<size_t>(h) * n + qi) * D + 4 * (g0 + kMergeGroups * k);
+    const float4 v = make_float4(o[k].x * inv, o[k].y * inv, o[k].z * inv, o[k].w * inv);
+    if constexpr (BF16IO)
+      *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(ov) + to) =
+          make_uint2(pack_bf16(v.x, v.y), pack_bf16(v.z, v.w));
+    else
+      *reinterpret_cast<float4 *>(static_cast<float *>(ov) + to) = v;
+  }
+}
+
+// K and V rounded to bf16, 8 elements per thread.
+__global__ __launch_bounds__(256) void to_bf16_kernel(const float *__restrict__ k, const float *__restrict__ v,
+                                                      uint16_t *kb, uint16_t *vb, size_t count) {
+  const float *src = blockIdx.y ? v : k;
+  uint16_t *dst = blockIdx.y ? vb : kb;
+  for (size_t i = 8 * (static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x); i < count;
+       i += 8 * 256 * static_cast<size_t>(gridDim.x))
+    *reinterpret_cast<uint4 *>(dst + i) = load8<false>(src, i);
+}
+
+// A slot's estimated cost: its key tiles times the per-tile time of its wave
+// count (about 1.45x for 5-8 waves against 1-4) and of a second chunk's gathers
+// (about 1.15x).
+constexpr uint32_t kTileCost = 171u;
+__device__ __forceinline__ uint32_t slot_cost(const int4 &a, const int4 &b) {
+  const int ta = key_tiles(a), tb = key_tiles(b);
+  const int waves = (a.z + 31) / 32 + (b.z > 0 ? (b.z + 31) / 32 : 0);
+  const uint32_t per = waves > 4 ? (b.z > 0 ? 196u : kTileCost) : (b.z > 0 ? 135u : 118u);
+  return static_cast<uint32_t>(ta > tb ? ta : tb) * per;
+}
+
+// The block order of a call whose heads' K and V fit the memory-side cache
+// together, or eight of them at a time (attention_pieces).  Block b runs on
+// XCD b mod 8, whatever the XCDs' loads, so each XCD is given a queue of its
+// own: the list of all heads' slots cut into eight runs of equal cost.  An XCD
+// then works on one or two heads, whose rows its L2 serves to the 32 (d = 64:
+// 64) blocks that sweep them at about the same pace, instead of on a share of
+// every head in turn.
+//
+// Within a queue the slots run by cost, largest first, and where the queue is
+// short its last round, partly empty, would be a large part of the launch: the
+// first w rounds of slots run whole, and the rest are cut along their keys
+// into ns pieces, the same key range of all of them before the next.  w and ns
+// are those of the shortest estimated time; a piece costs about kPieceCost
+// tiles on top (its start and its partial results), and the pieces of a whole
+// last round are worth kRoundSlack of it (unequal slots fill a round badly).
+// Nothing is split from kSplitRounds rounds on, where the last matters little.
+// Measured, list order -> here: 5 heads x 32760 tokens, d = 128: dense (2.5
+// rounds of slots) 2614 -> 2402 us, 128 clusters 1685 -> 1416 us; 40 heads
+// (nothing split) 12.95 -> 12.00 ms; 16 heads x 19721, d = 64, 96 clusters
+// 1202 -> 1030 us; dense 4224 tokens, one head 108 -> 68 us.
+//
+// One block per XCD, `slots` the most slots of a queue.  order[8 j + x], j <
+// slots + max_pieces: (slot, piece, pieces, place of
+// the partial results), slot -1: nothing; merges[8 s + x], s < max_merges:
+// (slot, 0, pieces, first place), pieces <= 1: nothing.
+constexpr int kPlanThreads = 1024;
+constexpr int kPlanSlots = 4096;      // slots of one queue (sorted in LDS)
+constexpr int kSplitRounds = 8, kMaxSplit = 16;
+constexpr float kPieceCost = 5.0f, kRoundSlack = 0.15f;
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+__global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
+    int total_items, int slots, int resident, int max_pieces, const int4 *__restrict__ items,
+    int4 *order, int4 *merges, int max_merges) {
+  __shared__ unsigned long long key[kPlanSlots];
+  __shared__ unsigned long long wsum[kPlanThreads / 64];
+  __shared__ unsigned long long q_cost;
+  __shared__ int used, wcnt[kPlanThreads / 64], in_queue[kXcds];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, x = blockIdx.x;
+  if (t == 0) {
+    used = 0;
+    q_cost = 0;
+  }
+  if (t < kXcds) in_queue[t] = 0;
+  auto cost_at = [&](int i) -> uint32_t {
+    const int4 a = items[2 * static_cast<size_t>(i)], b = items[2 * static_cast<size_t>(i) + 1];
+    return a.z > 0 ? max(slot_cost(a, b), 1u) : 0u;
+  };
+  // the cost before each slot of the list; this queue takes those whose cost
+  // before lies in its eighth, or where that would overfill one of the queues
+  // (very uneven slots) its eighth of their number
+  const int per = (total_items + kPlanThreads - 1) / kPlanThreads;
+  const int i0 = min(t * per, total_items), i1 = min(i0 + per, total_items);
+  unsigned long long mine = 0;
+#pragma unroll 4
+  for (int i = i0; i < i1; ++i) mine += cost_at(i);
+  const unsigned long long incl = wave_incl_scan(mine);
+  if (lane == 63) wsum[w] = incl;
+  __syncthreads();
+  unsigned long long before = incl - mine, total = 0;
+  for (int k = 0; k < kPlanThreads / 64; ++k) {
+    if (k < w) before += wsum[k];
+    total += wsum[k];
+  }
+  unsigned long long bound[kXcds];  // the ends of the eighths
+#pragma unroll
+  for (int k = 0; k < kXcds; ++k) bound[k] = total * (k + 1) / kXcds;
+  int nth = 0;  // used slots of this thread
+  unsigned long long at_cost = before;
+  for (int i = i0; i < i1; ++i) {
+    const uint32_t c = cost_at(i);
+    if (c) {
+      int k = 0;
+#pragma unroll
+      for (int j = 0; j < kXcds - 1; ++j) k += at_cost >= bound[j] ? 1 : 0;
+      atomicAdd(&in_queue[k], 1);
+      ++nth;
+    }
+    at_cost += c;
+  }
+  const int nincl = wave_incl_scan(nth);
+  if (lane == 63) wcnt[w] = nincl;
+  __syncthreads();
+  int nbefore = nincl - nth, ntotal = 0;
+  bool fits = true;
+  for (int k = 0; k < kPlanThreads / 64; ++k) {
+    if (k < w) nbefore += wcnt[k];
+    ntotal += wcnt[k];
+  }
+  for (int k = 0; k < kXcds; ++k) fits = fits && in_queue[k] <= slots;
+  const int eighth = (ntotal + kXcds - 1) / kXcds;
+  const unsigned long long lo = x ? bound[x - 1] : 0, hi = bound[x];
+  unsigned long long taken = 0;
+  for (int i = i0; i < i1; ++i) {
+    const uint32_t c = cost_at(i);
+    if (!c) continue;
+    if (fits ? before >= lo && before < hi : nbefore / eighth == x) {
+      // descending cost, then ascending slot: unique keys, so the order does
+      // not depend on where the slots were put
+      const int at = atomicAdd(&used, 1);
+      if (at < slots) key[at] = (static_cast<unsigned long long>(c) << 32) | static_cast<uint32_t>(~i);
+      taken += c;
+    }
+    before += c;
+    ++nbefore;
+  }
+  if (taken) atomicAdd(&q_cost, taken);
+  __syncthreads();
+  const int n = min(used, slots);
+  int size = 64;
+  while (size < n) size <<= 1;
+  for (int i = n + t; i < size; i += kPlanThreads) key[i] = 0;
+  __syncthreads();
+  for (int k = 2; k <= size; k <<= 1)
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      for (int p = t; p < size / 2; p += kPlanThreads) {
+        const int i = 2 * (p & ~(j - 1)) + (p & (j - 1));
+        const unsigned long long u = key[i], v = key[i + j];
+        if (((i & k) == 0) == (u < v)) {
+          key[i] = v;
+          key[i + j] = u;
+        }
+      }
+      // pairs at most 64 apart stay within the 128 keys of one wave (as does
+      // the next step, of half the distance)
+      if (j > 64 || (j == 1 && k >= 128)) __syncthreads();
+      else wave_fence();
+    }
+  __syncthreads();
+  // one candidate (w, ns) per thread: w = the full rounds less 0, 1 or 2, ns =
+  // 2 .. kMaxSplit; 63: nothing split
+  const int cap = resident / kXcds, full = n / cap;
+  const float tiles = n > 0 ? static_cast<float>(q_cost) / (static_cast<float>(kTileCost) * n) : 0.0f;
+  // every wave works out the same candidates
+  float e = INFINITY;
+  {
+    const int wr = full - lane / 16, ns = lane % 16 + 2, tail = n - wr * cap;
+    if (lane == 63) {
+      e = (static_cast<float>((n + cap - 1) / cap) + kRoundSlack) * tiles;
+    } else if (lane < 48 && ns <= kMaxSplit && wr >= 0 && tail > 0 && tail <= max_merges &&
+               tail * ns <= max_pieces && tiles >= static_cast<float>(ns * kPieceTiles) &&
+               n < kSplitRounds * cap) {
+      e = wr * tiles + static_cast<float>((tail * ns + cap - 1) / cap) * (tiles / ns + kPieceCost);
+    }
+  }
+  const float e_min = -wave_max(-e);
+  const int best = __ffsll(static_cast<long long>(__ballot(e == e_min))) - 1;
+  const int ns = best == 63 ? 1 : best % 16 + 2;
+  const int whole = best == 63 ? n : (full - best / 16) * cap, tail = n - whole;
+  auto slot_at = [&](int p) { return static_cast<int>(~static_cast<uint32_t>(key[p])); };
+  auto pieces_of = [&](int slot) {
+    return slot_split(items[2 * static_cast<size_t>(slot)], items[2 * static_cast<size_t>(slot) + 1], ns);
+  };
+  const int place0 = x * max_pieces;
+  for (int j = t; j < slots + max_pieces; j += kPlanThreads) {
+    int4 e = make_int4(-1, 0, 1, 0);
+    if (j < whole) {
+      e.x = slot_at(j);
+    } else if (j - whole < tail * ns) {
+      const int i = (j - whole) / tail, s = (j - whole) - i * tail;
+      const int slot = slot_at(whole + s), split = pieces_of(slot);
+      if (i < split) e = make_int4(slot, i, split, place0 + s * ns + i);
+    }
+    order[kXcds * static_cast<size_t>(j) + x] = e;
+  }
+  for (int s = t; s < max_merges; s += kPlanThreads) {
+    int4 e = make_int4(-1, 0, 0, 0);
+    if (s < tail) {
+      const int slot = slot_at(whole + s);
+      e = make_int4(slot, 0, pieces_of(slot), place0 + s * ns);
+    }
+    merges[kXcds * static_cast<size_t>(s) + x] = e;
+  }
 }
 
 // Work list of one head.  Every cluster's queries are cut into chunks of kBM
@@ -711,19 +1026,12 @@ __global__ __launch_bounds__(1024) void attn_items_kernel(
       }
     }
   };
-  // the staged slots, largest estimated cost first: a slot costs its key
-  // tiles times the per-tile time of its wave count (about 1.45x for 5-8
-  // waves against 1-4) and of a second chunk's gathers (about 1.15x).  The
-  // first `used` slots hold chunks; the empty ones after them stay in place.
+  // the staged slots, largest estimated cost first.  The first `used` slots hold chunks; the empty ones after them stay in place.
   auto emit_sorted = [&](int used) {
     if (!sorted) return;
     __syncthreads();
     for (int i = t; i < used; i += 1024) {
-      const int4 a = staged[2 * i], b = staged[2 * i + 1];
-      const int ta = (a.w + kBN - 1) / kBN, tb = b.z > 0 ? (b.w + kBN - 1) / kBN : 0;
-      const int waves = (a.z + 31) / 32 + (b.z > 0 ? (b.z + 31) / 32 : 0);
-      const uint32_t per = waves > 4 ? (b.z > 0 ? 196u : 171u) : (b.z > 0 ? 135u : 118u);
-      const uint32_t k = static_cast<uint32_t>(ta > tb ? ta : tb) * per;
+      const uint32_t k = slot_cost(staged[2 * i], staged[2 * i + 1]);
       // descending cost, then ascending slot: one unsigned comparison
       cost[i] = (static_cast<unsigned long long>(k) << 32) | static_cast<uint32_t>(~i);
     }
@@ -880,26 +1188,65 @@ __global__ __launch_bounds__(1024) void attn_items_kernel(
   emit_sorted(min(full_tot + total, items_per_head));
 }
 
+// Blocks that the chip holds at once (256 CUs; two blocks per CU at d = 64).
+int resident_blocks(int d) { return d == 64 ? 512 : 256; }
+
+// Slots that one XCD's queue holds: half as many again as its share.
+int queue_slots(int total_items) { return (total_items + total_items / 2 + kXcds - 1) / kXcds; }
+
+template <int D, bool BF16IO>
+hipError_t launch_dma(int heads, int n, const void *q, const void *k, const void *v, void *o,
+                      int c_q, const int32_t *offsets, const int32_t *perm, const int32_t *sel_idx,
+                      int iph, float scale_log2, const AttnScratch &w, hipStream_t s) {
+  const int total = iph * heads;
+  if (!w.order) {
+    hipLaunchKernelGGL((attn_kernel_dma<D, BF16IO>), dim3(total), dim3(kNW * 64), 0, s, n, c_q,
+                       iph, total, q, k, v, o, offsets, perm, sel_idx, w.items,
+                       static_cast<const int4 *>(nullptr), w.part, scale_log2);
+    return hipGetLastError();
+  }
+  const int slots = queue_slots(total), queue = slots + w.pieces / kXcds;
+  const int merges = w.pieces / kXcds / 2;
+  hipLaunchKernelGGL(attn_plan_kernel, dim3(kXcds), dim3(kPlanThreads), 0, s, total, slots,
+                     resident_blocks(D), w.pieces / kXcds, w.items, w.order,
+                     w.order + static_cast<size_t>(kXcds) * queue, merges);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((attn_kernel_dma<D, BF16IO>), dim3(kXcds * queue), dim3(kNW * 64), 0, s, n, c_q,
+                     iph, total, q, k, v, o, offsets, perm, sel_idx, w.items, w.order, w.part,
+                     scale_log2);
+  e = hipGetLastError();
+  if (e != hipSuccess || !w.pieces) return e;
+  hipLaunchKernelGGL((attn_merge_kernel<D, BF16IO>), dim3(kXcds * merges), dim3(kBM * kMergeGroups),
+                     0, s, n, c_q, iph, offsets, perm, w.items,
+                     w.order + static_cast<size_t>(kXcds) * queue, w.part, o);
+  return hipGetLastError();
+}
+
 template <int D>
 hipError_t launch_attn(int heads, int n, bool bf16, const void *q,
                        const void *k, const void *v, void *o, int c_q,
                        const int32_t *offsets, const int32_t *perm,
-                       const int32_t *sel_idx, const int4 *items, int iph,
-                       float scale_log2, hipStream_t s) {
+                       const int32_t *sel_idx, int iph, float scale_log2,
+                       const AttnScratch &w, hipStream_t s) {
+  if (bf16)
+    return launch_dma<D, true>(heads, n, q, k, v, o, c_q, offsets, perm, sel_idx, iph, scale_log2,
+                               w, s);
+  if (w.kv16) {
+    const size_t count = static_cast<size_t>(heads) * n * D;
+    uint16_t *v16 = w.kv16 + count;
+    const size_t blocks = (count / 8 + 255) / 256;
+    hipLaunchKernelGGL(to_bf16_kernel, dim3(blocks < 2048 ? static_cast<unsigned>(blocks) : 2048u, 2),
+                       dim3(256), 0, s, static_cast<const float *>(k), static_cast<const float *>(v),
+                       w.kv16, v16, count);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_dma<D, false>(heads, n, q, w.kv16, v16, o, c_q, offsets, perm, sel_idx, iph,
+                                scale_log2, w, s);
+  }
   const int total = iph * heads;
-  const dim3 grid(total), block(kNW * 64);
-  if (bf16 && D == 128)
-    hipLaunchKernelGGL(attn_kernel_dma, grid, block, 0, s, n, c_q, iph,
-                       total, q, k, v, o, offsets, perm, sel_idx, items,
-                       scale_log2);
-  else if (bf16)
-    hipLaunchKernelGGL((attn_kernel<D, true>), grid, block, 0, s, n, c_q, iph,
-                       total, q, k, v, o, offsets, perm, sel_idx, items,
-                       scale_log2);
-  else
-    hipLaunchKernelGGL((attn_kernel<D, false>), grid, block, 0, s, n, c_q, iph,
-                       total, q, k, v, o, offsets, perm, sel_idx, items,
-                       scale_log2);
+  hipLaunchKernelGGL(attn_kernel<D>, dim3(total), dim3(kNW * 64), 0, s, n, c_q, iph,
+                     total, q, k, v, o, offsets, perm, sel_idx, w.items, scale_log2);
   return hipGetLastError();
 }
 
@@ -944,24 +1291,62 @@ hipError_t attention_items(int heads, int n, int c_q, bool pair, const int32_t *
   return hipGetLastError();
 }
 
+// Below 1024 tokens the copy's launch costs more than it saves (Tiny layer,
+// 256 tokens: 282 us with the copy, 279 us without; 8 heads x 6417 tokens,
+// d = 128: 1154 us with, 1219 us without).
+bool attention_copies_kv(int n, int d, bool bf16) {
+  return !bf16 && (d == 64 || d == 128) && n >= 1024 &&
+         static_cast<uint64_t>(n) * d * 2 < (1ull << 32);
+}
+
+// Dense calls (one cluster) from the length on from which lists are split.
+// Sparse calls keep about half of the keys and have more slots; up to 16,384
+// tokens the order gains less than its two launches cost (8 heads x 9504
+// tokens, 40 clusters: 280 us with, 277 us without; 16 heads x 19721, d = 64:
+// 985 us with, 1027 us without).
+bool attention_ordered(int heads, int n, int d, int c_q) {
+  if ((d != 64 && d != 128) || n < kSplitTiles * kBN * (c_q > 1 ? 4 : 1)) return false;
+  const int at_once = heads < kXcds ? heads : kXcds;
+  if (static_cast<uint64_t>(at_once) * n * d * 4 > kMemorySideCache) return false;
+  const long long total = static_cast<long long>(heads) * attn_items_per_head(n, c_q);
+  return total <= (1 << 20) && queue_slots(static_cast<int>(total)) <= kPlanSlots;
+}
+
+// Three rounds of pieces where even the fewest slots (all chunks full) fill
+// fewer than kSplitRounds rounds; else none.
+int attention_pieces(int heads, int n, int d, int c_q) {
+  if (!attention_ordered(heads, n, d, c_q)) return 0;
+  const int cap = resident_blocks(d);
+  if (static_cast<long long>(heads) * ((n + kBM - 1) / kBM) >= static_cast<long long>(kSplitRounds) * cap)
+    return 0;
+  return 3 * cap;
+}
+
+size_t attention_order_entries(int heads, int n, int c_q, int pieces) {
+  return static_cast<size_t>(kXcds) * queue_slots(heads * attn_items_per_head(n, c_q)) + pieces +
+         pieces / 2;
+}
+
+size_t attention_piece_floats(int d) { return d == 64 ? kPieceFloats<64> : kPieceFloats<128>; }
+
 hipError_t attention_run(int heads, int n, int d, bool bf16, const void *q,
                          const void *k, const void *v, void *o, int c_q,
                          const int32_t *offsets, const int32_t *perm,
                          const int32_t *sel_counts, const int32_t *sel_idx,
-                         float scale, int4 *items, hipStream_t s) {
+                         float scale, const AttnScratch &w, hipStream_t s) {
   const int iph = attn_items_per_head(n, c_q);
   // remainder chunks share blocks only in the LDS-DMA kernel
-  const int pair = bf16 && d == 128 ? 1 : 0;
+  const int pair = bf16 || w.kv16 ? 1 : 0;
   hipLaunchKernelGGL(attn_items_kernel, dim3(heads), dim3(1024), 0, s, n, c_q,
-                     iph, pair, offsets, sel_counts, items);
+                     iph, pair, offsets, sel_counts, w.items);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const float sl2 = scale * 1.4426950408889634f;
   if (d == 128)
     return launch_attn<128>(heads, n, bf16, q, k, v, o, c_q, offsets, perm,
-                            sel_idx, items, iph, sl2, s);
+                            sel_idx, iph, sl2, w, s);
   return launch_attn<64>(heads, n, bf16, q, k, v, o, c_q, offsets, perm,
-                         sel_idx, items, iph, sl2, s);
+                         sel_idx, iph, sl2, w, s);
 }
 
 }  // namespace scope
