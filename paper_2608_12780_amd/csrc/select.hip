@@ -785,6 +785,7 @@ __global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_waves_per_eu(8))) 
 constexpr uint32_t kFreeSlot = 0xFFFFFFFFu;
 constexpr int kPartSlots = 16384;   // LDS table of one part: 128 KB
 constexpr int kSlotBits = 14;       // log2(kPartSlots)
+constexpr int kPartFull = -1;       // count of a part whose table filled up
 constexpr int kGatherBlocks = 16;   // blocks per head that assemble the lists
 // Every part reads all of a head's codes, so the build costs parts x n
 // reads; beyond kMaxDistinctKeys keys the passes visit every key.
@@ -793,20 +794,16 @@ constexpr int kMaxDistinctKeys = 262144;
 
 __device__ __forceinline__ uint32_t code_hash(uint32_t code) { return code * 0x9E3779B1u; }
 
-__global__ void code_parts_clear_kernel(int *overflow, int heads) {
-  for (int h = blockIdx.x * blockDim.x + threadIdx.x; h < heads; h += gridDim.x * blockDim.x)
-    overflow[h] = 0;
-}
-
 __global__ __launch_bounds__(kSelBlock) void code_parts_kernel(
-    const uint32_t *__restrict__ codes, int n, int parts, int upitch, uint32_t *stage_codes,
-    uint32_t *stage_mult, uint32_t *stage_rank, int *part_count, uint32_t *key_slot,
-    int *overflow) {
-  __shared__ uint32_t lk[kPartSlots];
-  __shared__ uint32_t lc[kPartSlots];
+    const uint32_t *__restrict__ codes, int n, int parts, int slots, int upitch,
+    uint32_t *stage_codes, uint32_t *stage_mult, uint32_t *stage_rank, int *part_count,
+    uint32_t *key_slot) {
+  extern __shared__ uint32_t table[];  // slots codes, then their counts
+  uint32_t *lk = table, *lc = table + slots;
+  __shared__ uint2 pending[kSelBlock / 64][128];  // per wave: (code, key)
   __shared__ int full;
   const int p = blockIdx.x, h = blockIdx.y;
-  for (int i = threadIdx.x; i < kPartSlots; i += kSelBlock) {
+  for (int i = threadIdx.x; i < slots; i += kSelBlock) {
     lk[i] = kFreeSlot;
     lc[i] = 0;
   }
@@ -814,50 +811,81 @@ __global__ __launch_bounds__(kSelBlock) void code_parts_kernel(
   __syncthreads();
   const uint32_t *hc = codes + static_cast<size_t>(h) * n;
   uint32_t *ks = key_slot + static_cast<size_t>(h) * upitch;
+  // A key's count goes into the table with all lanes of its wave at work: a
+  // wave collects the codes of its part in LDS and inserts them 64 at a time.
+  // (With every wave inserting its few matching lanes as it met them, one
+  // probe loop per 64 keys scanned, the kernel took 127 us for 24 heads x
+  // 118800 keys and 159 us for 40 x 32760; so it takes 57 us and, with the
+  // smaller tables below, 29 us.)
+  const int lane = threadIdx.x & 63;
+  uint2 *queue = pending[threadIdx.x >> 6];
+  auto insert = [&](uint2 e) {
+    if (*const_cast<volatile int *>(&full)) return;  // the head falls back anyway
+    const uint32_t code = e.x;
+    // double hashing: the step is odd, so the probes visit every slot, and
+    // tables 80% full take no long runs
+    const uint32_t hv = code_hash(code);
+    const uint32_t step = (hv >> 16) | 1u;
+    uint32_t slot = hv & (slots - 1);
+    for (int probe = 0; probe < slots; ++probe) {
+      const uint32_t prev = atomicCAS(&lk[slot], kFreeSlot, code);
+      if (prev == kFreeSlot || prev == code) {
+        atomicAdd(&lc[slot], 1u);
+        ks[e.y] = (static_cast<uint32_t>(p) << kSlotBits) | slot;
+        return;
+      }
+      slot = (slot + step) & (slots - 1);
+    }
+    full = 1;
+  };
+  auto wave_sync = [] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  int held = 0;  // entries of the wave's queue, at most 63 between steps
   // four codes per thread in flight (clamped positions; the extra ones are
   // skipped below)
   constexpr int kG = 4;
-  for (int j0 = threadIdx.x; j0 < n; j0 += kG * kSelBlock) {
+  for (int j0 = threadIdx.x - lane; j0 < n; j0 += kG * kSelBlock) {
     uint32_t cv[kG];
 #pragma unroll
-    for (int g = 0; g < kG; ++g) cv[g] = hc[min(j0 + g * kSelBlock, n - 1)];
+    for (int g = 0; g < kG; ++g) cv[g] = hc[min(j0 + g * kSelBlock + lane, n - 1)];
 #pragma unroll
     for (int g = 0; g < kG; ++g) {
-      const int j = j0 + g * kSelBlock;
+      const int j = j0 + g * kSelBlock + lane;
       const uint32_t code = cv[g] & 0x3FFFFFFFu;
-      const uint32_t hv = code_hash(code);
-      if (j >= n || static_cast<int>((static_cast<uint64_t>(hv) * parts) >> 32) != p) continue;
-      uint32_t slot = hv & (kPartSlots - 1);
-      bool done = false;
-      for (int probe = 0; probe < kPartSlots; ++probe) {
-        const uint32_t prev = atomicCAS(&lk[slot], kFreeSlot, code);
-        if (prev == kFreeSlot || prev == code) {
-          atomicAdd(&lc[slot], 1u);
-          ks[j] = (static_cast<uint32_t>(p) << kSlotBits) | slot;
-          done = true;
-          break;
-        }
-        slot = (slot + 1u) & (kPartSlots - 1);
+      const bool own = j < n && static_cast<int>((static_cast<uint64_t>(code_hash(code)) * parts) >> 32) == p;
+      const uint64_t mask = __ballot(own);
+      const int at = held + static_cast<int>(__builtin_amdgcn_mbcnt_hi(
+                                static_cast<uint32_t>(mask >> 32),
+                                __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u)));
+      if (own) queue[at] = make_uint2(code, static_cast<uint32_t>(j));
+      held += __popcll(mask);
+      if (held >= 64) {
+        wave_sync();
+        const uint2 e = queue[lane], rest = queue[64 + lane];
+        wave_sync();
+        held -= 64;
+        if (lane < held) queue[lane] = rest;
+        insert(e);
       }
-      if (!done) full = 1;
     }
   }
+  wave_sync();
+  if (lane < held) insert(queue[lane]);
   __syncthreads();
   if (full) {
-    if (threadIdx.x == 0) atomicOr(&overflow[h], 1);
+    if (threadIdx.x == 0) part_count[static_cast<size_t>(h) * parts + p] = kPartFull;
     return;
   }
-  // the part's pairs, in slot order
-  constexpr int per = kPartSlots / kSelBlock;
+  // the part's pairs: thread t's slots t, t + 1024, ... one after the other
   uint32_t mine = 0;
-#pragma unroll
-  for (int k = 0; k < per; ++k) mine += lk[threadIdx.x * per + k] != kFreeSlot;
+  for (int i = threadIdx.x; i < slots; i += kSelBlock) mine += lk[i] != kFreeSlot;
   uint32_t total;
   uint32_t at = block_excl_scan<uint32_t>(mine, &total);
-  const size_t base = (static_cast<size_t>(h) * parts + p) * kPartSlots;
-#pragma unroll
-  for (int k = 0; k < per; ++k) {
-    const int i = threadIdx.x * per + k;
+  const size_t base = (static_cast<size_t>(h) * parts + p) * slots;
+  for (int i = threadIdx.x; i < slots; i += kSelBlock) {
     if (lk[i] != kFreeSlot) {
       stage_codes[base + at] = lk[i];
       stage_mult[base + at] = lc[i];
@@ -872,18 +900,28 @@ __global__ __launch_bounds__(kSelBlock) void code_parts_kernel(
 // each key's (part, slot) turned into its index in that list; or one entry
 // per key (its own index) after an overflow.
 __global__ __launch_bounds__(kSelBlock) void code_parts_gather_kernel(
-    const uint32_t *__restrict__ codes, int n, int parts, int upitch,
+    const uint32_t *__restrict__ codes, int n, int parts, int slots, int upitch,
     const uint32_t *__restrict__ stage_codes, const uint32_t *__restrict__ stage_mult,
-    const uint32_t *__restrict__ stage_rank, const int *__restrict__ part_count,
-    const int *__restrict__ overflow, uint32_t *ucodes, uint32_t *umult, int *ucount,
+    const uint32_t *__restrict__ stage_rank, const int *__restrict__ part_count, uint32_t *ucodes, uint32_t *umult, int *ucount,
     uint32_t *uidx) {
   __shared__ int pbase[kMaxParts + 1];
+  __shared__ int overflow;
   const int g = blockIdx.x, h = blockIdx.y;
   const int first = g * kSelBlock + threadIdx.x, stride = gridDim.x * kSelBlock;
   uint32_t *uc = ucodes + static_cast<size_t>(h) * n;
   uint32_t *um = umult + static_cast<size_t>(h) * n;
   uint32_t *ui = uidx + static_cast<size_t>(h) * upitch;
-  if (overflow[h]) {
+  if (threadIdx.x < 64) {  // parts <= kMaxParts < 64
+    const int q = threadIdx.x;
+    const int cnt = q < parts ? part_count[static_cast<size_t>(h) * parts + q] : 0;
+    const int incl = wave_incl_scan(cnt);
+    if (q < parts) pbase[q + 1] = incl;
+    if (q == 0) pbase[0] = 0;
+    const bool over = __ballot(cnt == kPartFull) != 0;
+    if (q == 0) overflow = over;
+  }
+  __syncthreads();
+  if (overflow) {
     for (int j = first; j < n; j += stride) {
       uc[j] = codes[static_cast<size_t>(h) * n + j] & 0x3FFFFFFFu;
       um[j] = 1u;
@@ -892,19 +930,11 @@ __global__ __launch_bounds__(kSelBlock) void code_parts_gather_kernel(
     if (g == 0 && threadIdx.x == 0) ucount[h] = n;
     return;
   }
-  if (threadIdx.x == 0) {
-    int off = 0;
-    for (int q = 0; q < parts; ++q) {
-      pbase[q] = off;
-      off += part_count[static_cast<size_t>(h) * parts + q];
-    }
-    pbase[parts] = off;
-  }
-  __syncthreads();
-  for (int q = 0; q < parts; ++q) {
+  // the blocks share the parts' lists, then the keys
+  for (int q = g; q < parts; q += gridDim.x) {
     const int cnt = pbase[q + 1] - pbase[q];
-    const size_t base = (static_cast<size_t>(h) * parts + q) * kPartSlots;
-    for (int i = first; i < cnt; i += stride) {
+    const size_t base = (static_cast<size_t>(h) * parts + q) * slots;
+    for (int i = threadIdx.x; i < cnt; i += kSelBlock) {
       if (pbase[q] + i < n) {
         uc[pbase[q] + i] = stage_codes[base + i];
         um[pbase[q] + i] = stage_mult[base + i];
@@ -914,9 +944,9 @@ __global__ __launch_bounds__(kSelBlock) void code_parts_gather_kernel(
   for (int j = first; j < n; j += stride) {
     const uint32_t e = ui[j];
     const int q = min(static_cast<int>(e >> kSlotBits), parts - 1);
-    const uint32_t slot = e & (kPartSlots - 1);
+    const int slot = min(static_cast<int>(e & (kPartSlots - 1)), slots - 1);
     ui[j] = static_cast<uint32_t>(pbase[q]) +
-            stage_rank[(static_cast<size_t>(h) * parts + q) * kPartSlots + slot];
+            stage_rank[(static_cast<size_t>(h) * parts + q) * slots + slot];
   }
   if (g == 0 && threadIdx.x == 0) ucount[h] = pbase[parts] < n ? pbase[parts] : n;
 }
@@ -928,14 +958,29 @@ __global__ void fixexp_kernel(const float *y, uint64_t *out, int64_t count) {
 
 }  // namespace
 
-int code_parts(int n) {
-  // tables at most 80% full even if every key has its own code: at 720p
-  // (n = 118800) 10 parts, so 24 heads' blocks run in one round on 256 CUs
-  const long long p = (5LL * n + 4LL * kPartSlots - 1) / (4LL * kPartSlots);
-  return p < 1 ? 1 : static_cast<int>(p);
+// The parts of a head and their tables: at most 80% full even if every key has
+// its own code.  Tables are halved while the blocks still fit the 256 CUs in
+// one round (24 heads x 118800: 10 parts of 16384 slots; 40 x 32760: 5 of 8192):
+// more blocks share the insertions, and a small head does not clear and list
+// 16384 slots.  With 16384 throughout 40 x 32760 took 65 us, 5 x 32760 67 us and
+// 3 x 2185 10.7 us; so (and with double hashing) 29, 17 and 6.4 us.
+struct CodeParts {
+  int parts, slots;
+};
+static CodeParts code_parts(int heads, int n) {
+  auto parts_of = [&](int slots) {
+    const long long p = (5LL * n + 4LL * slots - 1) / (4LL * slots);
+    return p < 1 ? 1LL : p;
+  };
+  int slots = kPartSlots;
+  while (slots > 512 && parts_of(slots / 2) <= kMaxParts && parts_of(slots / 2) * heads <= 256)
+    slots /= 2;
+  return CodeParts{static_cast<int>(parts_of(slots)), slots};
 }
 
-bool use_distinct_codes(int n) { return n <= kMaxDistinctKeys && code_parts(n) <= kMaxParts; }
+static bool use_distinct_codes(int n) {
+  return n <= kMaxDistinctKeys && 5LL * n <= 4LL * kPartSlots * kMaxParts;
+}
 
 // Row pitch of the per-key index arrays: n rounded up to 4 entries, so the
 // final kernel reads four keys' indices per 16-byte load.
@@ -943,9 +988,10 @@ static size_t key_pitch(int n) { return (static_cast<size_t>(n) + 3) & ~static_c
 
 size_t select_dedup_words(int heads, int n) {
   if (!use_distinct_codes(n)) return 0;
-  const size_t parts = static_cast<size_t>(code_parts(n));
+  const CodeParts cp = code_parts(heads, n);
+  const size_t parts = static_cast<size_t>(cp.parts);
   return static_cast<size_t>(heads) *
-         (key_pitch(n) + 3 * parts * kPartSlots + parts + 2 * static_cast<size_t>(n) + 2);
+         (key_pitch(n) + 3 * parts * cp.slots + parts + 2 * static_cast<size_t>(n) + 2);
 }
 
 hipError_t select_run(int heads, int n, int c_q, const Subspaces &sub, int d,
@@ -968,9 +1014,10 @@ hipError_t select_run(int heads, int n, int c_q, const Subspaces &sub, int d,
   if (distinct) {
     // the head's distinct codes, their multiplicities and each key's index
     // among them (the index array first: 16-byte aligned like the scratch)
-    const int parts = code_parts(n);
+    const CodeParts part = code_parts(heads, n);
+    const int parts = part.parts, slots = part.slots;
     const int upitch = static_cast<int>(key_pitch(n));
-    const size_t stage = static_cast<size_t>(heads) * parts * kPartSlots;
+    const size_t stage = static_cast<size_t>(heads) * parts * slots;
     uint32_t *uidx = dedup;
     uint32_t *stage_codes = uidx + static_cast<size_t>(heads) * upitch;
     uint32_t *stage_mult = stage_codes + stage;
@@ -979,15 +1026,11 @@ hipError_t select_run(int heads, int n, int c_q, const Subspaces &sub, int d,
     uint32_t *umult = ucodes + static_cast<size_t>(heads) * n;
     int *part_count = reinterpret_cast<int *>(umult + static_cast<size_t>(heads) * n);
     int *ucount = part_count + static_cast<size_t>(heads) * parts;
-    int *overflow = ucount + heads;
-    hipLaunchKernelGGL(code_parts_clear_kernel, dim3((heads + 255) / 256), dim3(256), 0, s,
-                       overflow, heads);
-    hipLaunchKernelGGL(code_parts_kernel, dim3(parts, heads), dim3(kSelBlock), 0, s, codes32, n,
-                       parts, upitch, stage_codes, stage_mult, stage_rank, part_count, uidx,
-                       overflow);
+    hipLaunchKernelGGL(code_parts_kernel, dim3(parts, heads), dim3(kSelBlock),
+                       static_cast<size_t>(slots) * 8, s, codes32, n, parts, slots, upitch, stage_codes, stage_mult, stage_rank, part_count, uidx);
     hipLaunchKernelGGL(code_parts_gather_kernel, dim3(kGatherBlocks, heads), dim3(kSelBlock), 0, s,
-                       codes32, n, parts, upitch, stage_codes, stage_mult, stage_rank, part_count,
-                       overflow, ucodes, umult, ucount, uidx);
+                       codes32, n, parts, slots, upitch, stage_codes, stage_mult, stage_rank, part_count,
+                       ucodes, umult, ucount, uidx);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     cb.ucodes = ucodes;
