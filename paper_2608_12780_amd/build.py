@@ -11,7 +11,7 @@ CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libscope.so")
 SOURCES = ["api.cpp", "kmeans.hip", "kmeans_mfma.hip", "kmeans_update.hip",
-           "kmeans_codebook.hip", "score.hip",
+           "kmeans_codebook.hip", "kmeans_lloyd.hip", "score.hip",
            "select.hip",
            "attention.hip", "peaks.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

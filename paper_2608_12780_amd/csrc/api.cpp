@@ -429,20 +429,33 @@ int32_t cluster_queries(const scope_shape *shape, const void *q, int32_t c_q, in
   p.nu = w.nu;
   p.bnd = w.bnd;
   set_split(p, w.split);
-  const scope::AccPlan plan = query_plan(shape, c_q);
+  scope::AccPlan plan = query_plan(shape, c_q);
   // the grouping histogram is built with atomics by the last assignment
   const size_t hist = p.mfma ? static_cast<size_t>(p.heads) * scope::km_nchunks(n) * c_q : 0;
   SCOPE_TRY(scope::km_init(&p, 1, warm, init_idx, c_q, 0, dev_status, p.chunk_hist, hist,
                            scope::DeviceArgs{}, s));
   // the returned grouping is that of the last assignment, taken before the
   // last update
+  const int lloyd = scope::km_lloyd_blocks(&p, 1, plan);
+  if (lloyd) plan.blocks = lloyd;
+  if (lloyd == 1) {
+    SCOPE_TRY(scope::km_lloyd(&p, 1, 1, iters, false, p.chunk_hist, plan, w.slab, w.cslab,
+                              dev_status, s));
+    SCOPE_TRY(scope::km_group(p, s));
+    return SCOPE_OK;
+  }
   for (int it = 0; it < iters; ++it) {
     const bool last = it + 1 == iters;
-    SCOPE_TRY(scope::km_assign(p, last, s));
+    int32_t *status = it == 0 ? dev_status : nullptr;
+    if (lloyd) {
+      SCOPE_TRY(scope::km_lloyd(&p, 1, lloyd, 1, false, last ? p.chunk_hist : nullptr, plan, w.slab,
+                                w.cslab, status, s));
+    } else {
+      SCOPE_TRY(scope::km_assign(p, last, s));
+      SCOPE_TRY(scope::km_accum(plan, q, p.bf16, p.x_head_stride, d, n, shape->heads, assign,
+                                p.a_head_stride, 0, w.slab, w.cslab, status, s));
+    }
     if (last) SCOPE_TRY(scope::km_group(p, s));
-    SCOPE_TRY(scope::km_accum(plan, q, p.bf16, p.x_head_stride, d, n, shape->heads,
-                              assign, p.a_head_stride, 0, w.slab, w.cslab,
-                              it == 0 ? dev_status : nullptr, s));
     SCOPE_TRY(scope::km_finish(plan, &p, 1, !last, w.slab, w.cslab, s));
   }
   return SCOPE_OK;
@@ -501,7 +514,7 @@ int32_t cluster_key_subspaces(const scope_shape *shape, const void *k, const int
     set_split(pm, w.split);
     ucol += static_cast<size_t>(c_m[m]) * pm.dx;
   }
-  const scope::AccPlan plan = key_plan(shape, c_m);
+  scope::AccPlan plan = key_plan(shape, c_m);
   // the three assignments in one pass over K when the codebooks fit the LDS
   // together, else one pass per subspace
   const bool fused = scope::km_assign3_ok(p);
@@ -518,14 +531,25 @@ int32_t cluster_key_subspaces(const scope_shape *shape, const void *k, const int
     }
     return hipSuccess;
   };
-  for (int it = 0; it < iters; ++it) {
+  const int lloyd = scope::km_lloyd_blocks(p, 3, plan);
+  if (lloyd) plan.blocks = lloyd;
+  if (lloyd == 1) {
+    SCOPE_TRY(scope::km_lloyd(p, 3, 1, iters, true, nullptr, plan, w.slab, w.cslab, dev_status, s));
+  } else {
+    for (int it = 0; it < iters; ++it) {
+      int32_t *status = it == 0 ? dev_status : nullptr;
+      if (lloyd) {
+        SCOPE_TRY(scope::km_lloyd(p, 3, lloyd, 1, false, nullptr, plan, w.slab, w.cslab, status, s));
+      } else {
+        SCOPE_TRY(assign_all());
+        SCOPE_TRY(scope::km_accum(plan, k, p[0].bf16, p[0].x_head_stride, d, n, shape->heads,
+                                  w.assign3, static_cast<size_t>(3) * n, n, w.slab, w.cslab,
+                                  status, s));
+      }
+      SCOPE_TRY(scope::km_finish(plan, p, 3, true, w.slab, w.cslab, s));
+    }
     SCOPE_TRY(assign_all());
-    SCOPE_TRY(scope::km_accum(plan, k, p[0].bf16, p[0].x_head_stride, d, n, shape->heads,
-                              w.assign3, static_cast<size_t>(3) * n, n, w.slab, w.cslab,
-                              it == 0 ? dev_status : nullptr, s));
-    SCOPE_TRY(scope::km_finish(plan, p, 3, true, w.slab, w.cslab, s));
   }
-  SCOPE_TRY(assign_all());
   SCOPE_TRY(scope::km_pack_codes(w.assign3, static_cast<size_t>(3) * n, n, n,
                                  shape->heads, codes, s));
   return SCOPE_OK;
@@ -677,7 +701,7 @@ int32_t scope_cluster_key_partition(const scope_shape *shape, const void *k,
     for (int m = 0; m < g.M; ++m) mx = g.C[m] > mx ? g.C[m] : mx;
     if (init_stride < mx) return SCOPE_ERR_INVALID_ARGUMENT;
   }
-  const scope::AccPlan plan = part_plan(shape, g);
+  scope::AccPlan plan = part_plan(shape, g);
   if (plan.nwin == 0) return SCOPE_ERR_UNSUPPORTED;
   const size_t need = part_key_ws(shape, part, nullptr, nullptr);
   if ((st = check_ws(workspace, ws_bytes, need))) return st;
@@ -722,14 +746,24 @@ int32_t scope_cluster_key_partition(const scope_shape *shape, const void *k,
   // rows of head h, subspace m at init_idx[(h*M + m)*init_stride]
   SCOPE_TRY(scope::km_init(p, M, false, init_idx, M * init_stride, init_stride, dev_status,
                            nullptr, 0, scope::DeviceArgs{}, s));
-  for (int it = 0; it < iters; ++it) {
+  const int lloyd = scope::km_lloyd_blocks(p, M, plan);
+  if (lloyd) plan.blocks = lloyd;
+  if (lloyd == 1) {
+    SCOPE_TRY(scope::km_lloyd(p, M, 1, iters, true, nullptr, plan, w.slab, w.cslab, dev_status, s));
+  } else {
+    for (int it = 0; it < iters; ++it) {
+      int32_t *status = it == 0 ? dev_status : nullptr;
+      if (lloyd) {
+        SCOPE_TRY(scope::km_lloyd(p, M, lloyd, 1, false, nullptr, plan, w.slab, w.cslab, status, s));
+      } else {
+        for (int m = 0; m < M; ++m) SCOPE_TRY(scope::km_assign(p[m], false, s));
+        SCOPE_TRY(scope::km_accum(plan, x, bf16, p[0].x_head_stride, d, n, shape->heads, w.assign,
+                                  static_cast<size_t>(M) * n, n, w.slab, w.cslab, status, s));
+      }
+      SCOPE_TRY(scope::km_finish(plan, p, M, true, w.slab, w.cslab, s));
+    }
     for (int m = 0; m < M; ++m) SCOPE_TRY(scope::km_assign(p[m], false, s));
-    SCOPE_TRY(scope::km_accum(plan, x, bf16, p[0].x_head_stride, d, n, shape->heads,
-                              w.assign, static_cast<size_t>(M) * n, n, w.slab, w.cslab,
-                              it == 0 ? dev_status : nullptr, s));
-    SCOPE_TRY(scope::km_finish(plan, p, M, true, w.slab, w.cslab, s));
   }
-  for (int m = 0; m < M; ++m) SCOPE_TRY(scope::km_assign(p[m], false, s));
   SCOPE_TRY(scope::km_codes16(w.assign, static_cast<size_t>(shape->heads) * M * n, codes, s));
   return SCOPE_OK;
 }

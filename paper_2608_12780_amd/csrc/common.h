@@ -59,6 +59,28 @@ __device__ __forceinline__ T wave_incl_scan(T v) {
   return v;
 }
 
+// rint(x * 2^24) as a two's complement int64, exact for |x| < 2^27: the
+// fp64 value x * 2^24 + 1.5 * 2^52 is rounded once, to the nearest integer
+// with ties to even (the spacing of doubles in [2^52, 2^53) is 1), and the
+// low 52 bits of its encoding then hold 2^51 + rint(x * 2^24).  The high
+// word minus the fixed exponent and 2^19 is the upper half of the result.
+// Other x (flagged in the status word) give some value, never a trap.
+__device__ __forceinline__ unsigned long long fixed24(float x) {
+  const double d = fma(static_cast<double>(x), 0x1p24, 0x1.8p52);
+  const unsigned long long bits = static_cast<unsigned long long>(__double_as_longlong(d));
+  const uint32_t lo = static_cast<uint32_t>(bits);
+  const uint32_t hi = static_cast<uint32_t>(bits >> 32) - 0x43380000u;
+  return (static_cast<unsigned long long>(hi) << 32) | lo;
+}
+
+// The int64 sums stay exact while n terms of magnitude below 2^(e+24) cannot
+// reach 2^63: |x| < lim = 2^e with e = min(22, 39 - ceil(log2 n)).  Larger or
+// non-finite inputs are flagged.
+__device__ __forceinline__ void check_value(float x, float lim, int &bad) {
+  if (!(fabsf(x) < lim))
+    bad |= isfinite(x) ? kStatusRange : (kStatusRange | kStatusNonFinite);
+}
+
 // ---------------------------------------------------------------------------
 // Proxy-logit arithmetic (Eq. 6): ((P_T + P_H) + P_W) * sigma, then + 0 to
 // fold -0 into +0.  P points at one concatenated table row.

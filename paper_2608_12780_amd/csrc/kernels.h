@@ -137,6 +137,17 @@ hipError_t km_accum(const AccPlan &plan, const void *x, bool bf16, size_t x_hs,
 // matrix-core codebooks too (not needed after a call's last update).
 hipError_t km_finish(const AccPlan &plan, const KmProblem *p, int nsub, bool prepare,
                      const long long *slab, const int32_t *cslab, hipStream_t s);
+// Largest |x| (exclusive) for which n rows' fixed-point sums are exact.
+float km_range_limit(int n);
+// Small problems: assignment and update of an iteration in one launch, or with
+// one block per head and subspace all iterations (and the keys' last
+// assignment).  km_lloyd_blocks: blocks per head and subspace, 0 where the
+// separate launches are used, at most the plan's.  The plan's block count is
+// to be set to it; with more than one block km_finish follows each launch.
+int km_lloyd_blocks(const KmProblem *p, int nsub, const AccPlan &plan);
+hipError_t km_lloyd(const KmProblem *p, int nsub, int blocks, int iters, bool final_assign,
+                    int32_t *chunk_hist, const AccPlan &plan, long long *slab, int32_t *cslab,
+                    int32_t *status, hipStream_t s);
 hipError_t km_pack_codes(const int32_t *a3, size_t a_head_stride,
                          size_t a_sub_stride, int n, int heads,
                          uint32_t *codes, hipStream_t s);

@@ -1,0 +1,348 @@
+// Lloyd iterations of small problems: assignment and update in one launch.
+//
+// With few rows an iteration is not bound by its work but by its chain of
+// launches (3 heads x 2185 rows x 32 centroids x 128 channels: assign 16 us,
+// accumulate 8 us, finish 5 us, each little above an empty launch's 4.5 us).
+// Here a wave that has assigned a 32-row slice (assign_slice, the same exact
+// filter) adds the slice's rows to the block's int64 sums at once, while they
+// are in cache.  Where the rows of a head are few enough for one block, the
+// block also turns the sums into the next centroids and goes round again: all
+// iterations of a (head, subspace) are one launch.
+// Measured, separate launches -> here: a layer of 3 heads x 2185 rows (C = 32;
+// 16, 16, 16) 754 -> 491 us; Tiny (2 x 256 fp32, 8; 8, 8, 8) 276 -> 160 us; 8
+// heads x 6417 fp32 (64; 32, 32, 32) 1155 -> 1030 us.
+//
+// Block (b, h, m): a share of the slices of head h in subspace m.  LDS: the
+// two-term codebook, norms, int64 sums laid out so that the lanes of a row hit
+// consecutive slots (channel c of a row of L pairs at (c mod 2) L + c / 2).
+#include <math.h>
+
+#include "common.h"
+#include "kernels.h"
+#include "kmeans_slice.h"
+
+namespace scope {
+
+namespace {
+
+constexpr int kLloydWaves = 8;
+constexpr int kLloydThreads = 64 * kLloydWaves;
+constexpr int kLloydLds = 150 * 1024;
+
+struct LloydSub {
+  int col0, dx, dxp, C, cpad;
+  int ucol, ccol;         // float offset and first cluster within a head
+  const uint16_t *ubf;    // prepared codebook (km_init, km_finish)
+  const float *nu, *bnd;
+  float *u;
+  int32_t *assign;
+};
+struct LloydArgs {
+  const void *X;
+  size_t x_hs, u_hs, a_hs;
+  int ld, n, nchunks;
+  int iters, final_assign;  // one-block form
+  int32_t *chunk_hist;      // grouping histogram of the last assignment, or null
+  long long *slab;          // several blocks: their sums and counts
+  int32_t *cslab;
+  int S, SC;
+  int32_t *status;
+  float lim;
+  LloydSub sub[kMaxSub];
+};
+
+// Pairs of channels of a row of sums.
+__device__ __host__ __forceinline__ int pairs_of(int dx) { return (dx + 1) / 2; }
+
+struct LloydLds {
+  uint16_t *Us;
+  unsigned long long *sums;
+  float *nus, *nhs, *bnd;
+  int *cnts;
+};
+// Bytes of LDS, and with l the arrays at base.
+__device__ __host__ __forceinline__ size_t lloyd_lds(int C, int cpad, int dx, int dxp, char *base, LloydLds *l) {
+  auto up = [](size_t bytes) { return (bytes + 15) / 16 * 16; };
+  const size_t us = 0, su = us + up(static_cast<size_t>(cpad) * (2 * dxp + 8) * 2);
+  const size_t nu = su + up(static_cast<size_t>(C) * 2 * pairs_of(dx) * 8);
+  const size_t row = up(4 * static_cast<size_t>(cpad));
+  if (l)
+    *l = LloydLds{reinterpret_cast<uint16_t *>(base + us),
+                  reinterpret_cast<unsigned long long *>(base + su),
+                  reinterpret_cast<float *>(base + nu), reinterpret_cast<float *>(base + nu + row),
+                  reinterpret_cast<float *>(base + nu + 2 * row),
+                  reinterpret_cast<int *>(base + nu + 3 * row)};
+  return nu + 3 * row + up(4 * static_cast<size_t>(C));
+}
+
+// Adds the rows of slice sl (whose centroids the wave's lanes hold in arg) to
+// the sums and counts.
+template <typename T, bool CHECK>
+__device__ __forceinline__ void accumulate_slice(const LloydArgs &A, const LloydSub &K, const LloydLds &L,
+                                                 int h, int sl, int arg, int &bad) {
+  const int lane = threadIdx.x & 63, P = pairs_of(K.dx);
+  const int rows = min(32, A.n - 32 * sl);
+  if (lane < rows) atomicAdd(&L.cnts[arg], 1);
+  const int rpw = 64 / P, rr = lane / P, c2 = lane - rr * P;  // rows per step, the lane's row and pair
+  const bool two = 2 * c2 + 1 < K.dx;
+  const T *x0 = static_cast<const T *>(A.X) + h * A.x_hs + static_cast<size_t>(32 * sl) * A.ld + K.col0 + 2 * c2;
+  constexpr int U = 8;
+  for (int r0 = 0; r0 < rows; r0 += U * rpw) {
+    float a[U], b[U];
+    int g[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int row = r0 + k * rpw + rr;
+      const int rc = min(row, rows - 1);
+      g[k] = __shfl(arg, rc);
+      const T *x = x0 + static_cast<size_t>(rc) * A.ld;
+      if constexpr (sizeof(T) == 2) {  // pairs are 4-byte aligned
+        const uint32_t v = *reinterpret_cast<const uint32_t *>(x);
+        a[k] = __uint_as_float(v << 16);
+        b[k] = __uint_as_float(v & 0xFFFF0000u);
+      } else {
+        a[k] = x[0];
+        b[k] = two ? x[1] : 0.0f;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      if (rr < rpw && r0 + k * rpw + rr < rows) {
+        if (CHECK) {
+          check_value(a[k], A.lim, bad);
+          check_value(b[k], A.lim, bad);
+        }
+        unsigned long long *s = L.sums + static_cast<size_t>(g[k]) * 2 * P + c2;
+        atomicAdd(s, fixed24(a[k]));
+        atomicAdd(s + P, fixed24(b[k]));
+      }
+    }
+  }
+}
+
+// The next centroids of the block's sums, in global memory and as two-term
+// codebook, norms and residual bounds in LDS; an empty cluster keeps its own.
+// Leaves the sums and counts cleared.
+template <int DXP>
+__device__ __forceinline__ void finish_block(const LloydSub &K, const LloydLds &L, float *U) {
+  constexpr int US = 2 * DXP + 8;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, P = pairs_of(K.dx);
+  __syncthreads();
+  for (int r = w; r < K.C; r += kLloydWaves) {
+    const int cnt = L.cnts[r];
+    if (cnt <= 0) continue;
+    unsigned long long *s = L.sums + static_cast<size_t>(r) * 2 * P;
+    const double den = static_cast<double>(cnt) * 16777216.0;
+    float xs[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int c = lane + 64 * j;
+      xs[j] = c < K.dx ? static_cast<float>(static_cast<double>(static_cast<long long>(
+                                                s[(c & 1) * P + (c >> 1)])) / den)
+                       : 0.0f;
+    }
+    float e2 = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int c = lane + 64 * j;
+      const float hi = bf16_to_f32(to_bf16(xs[j])), rest = xs[j] - hi;  // exact
+      const float df = rest - bf16_to_f32(to_bf16(rest));               // exact
+      e2 = fmaf(df, df, e2);
+      if (c < K.dx) {
+        U[static_cast<size_t>(r) * K.dx + c] = xs[j];
+        L.Us[r * US + c] = to_bf16(xs[j]);
+        L.Us[r * US + DXP + c] = to_bf16(rest);
+      }
+    }
+    e2 = wave_sum(e2);
+    wave_sync();  // the wave has read the row's sums
+    float *row = reinterpret_cast<float *>(s);
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      if (lane + 64 * j < K.dx) row[lane + 64 * j] = xs[j];
+    if (lane == 0) L.bnd[r] = sqrtf(e2) * 1.001f + 1e-21f;
+  }
+  __syncthreads();
+  // the canonical norms, one thread per row
+  for (int r = t; r < K.C; r += kLloydThreads)
+    if (L.cnts[r] > 0) {
+      const float *row = reinterpret_cast<const float *>(L.sums + static_cast<size_t>(r) * 2 * P);
+      float n = 0.0f;
+#pragma unroll 8
+      for (int c = 0; c < K.dx; ++c) n = fmaf(row[c], row[c], n);
+      L.nus[r] = n;
+      L.nhs[r] = -0.5f * n;
+    }
+  __syncthreads();
+  for (int e = t; e < K.C * 2 * P; e += kLloydThreads) L.sums[e] = 0ull;
+  for (int r = t; r < K.C; r += kLloydThreads) L.cnts[r] = 0;
+  __syncthreads();
+}
+
+template <int DXP, typename T, bool ONE>
+__device__ __forceinline__ void lloyd_block(const LloydArgs &A, const LloydSub &K, char *lds,
+                                            uint32_t *cand, unsigned long long *best, int *ncand,
+                                            int *next, float (*red)[kLloydWaves]) {
+  const int t = threadIdx.x, w = t >> 6, lane = t & 63, b = blockIdx.x, h = blockIdx.y;
+  LloydLds L;
+  lloyd_lds(K.C, K.cpad, K.dx, DXP, lds, &L);
+  const int P = pairs_of(K.dx);
+  for (int e = t; e < K.C * 2 * P; e += kLloydThreads) L.sums[e] = 0ull;
+  for (int r = t; r < K.C; r += kLloydThreads) L.cnts[r] = 0;
+  if (t == 0) *next = 0;
+  FilterBound B = stage_codebook<DXP, kLloydWaves, sizeof(T) == 4>(L.Us, L.nus, L.nhs, red, K.ubf, K.nu,
+                                                                  K.bnd, h, K.C, K.cpad);
+  float *U = K.u + h * A.u_hs;
+  SliceArgs<T> S{static_cast<const T *>(A.X), A.x_hs, A.ld, K.col0, K.dx, A.n, K.C, K.cpad, K.u,
+                 A.u_hs, K.assign, A.a_hs, nullptr, A.nchunks};
+  const int nslices = (A.n + 31) / 32;
+  const int lo = static_cast<int>(static_cast<long long>(nslices) * b / gridDim.x);
+  const int hi = static_cast<int>(static_cast<long long>(nslices) * (b + 1) / gridDim.x);
+  const int rounds = ONE ? A.iters + A.final_assign : 1;
+  int bad = 0;
+  if constexpr (ONE) {
+    for (int r = t; r < K.C; r += kLloydThreads) L.bnd[r] = K.bnd[static_cast<size_t>(h) * K.cpad + r];
+  }
+  for (int it = 0; it < rounds; ++it) {
+    const bool update = !ONE || it < A.iters;
+    if (it + 1 == rounds) S.chunk_hist = A.chunk_hist;
+    // a wave that is done takes the block's next slice
+    for (;;) {
+      int u = 0;
+      if (lane == 0) u = atomicAdd(next, 1);
+      u = lo + __builtin_amdgcn_readfirstlane(u);
+      if (u >= hi) break;
+      const int arg = assign_slice<DXP, T>(S, L.Us, L.nus, L.nhs, B, h, u, cand, best, ncand);
+      if (update) {
+        if (A.status && it == 0) accumulate_slice<T, true>(A, K, L, h, u, arg, bad);
+        else accumulate_slice<T, false>(A, K, L, h, u, arg, bad);
+      }
+    }
+    if constexpr (ONE) {
+      if (!update) break;
+      finish_block<DXP>(K, L, U);
+      if (t == 0) *next = 0;
+      // the bound constants of the new codebook (finish_block ended on a
+      // barrier; every wave works them out for itself)
+      float e_max = 0.0f, nu_max = 0.0f;
+      for (int r = lane; r < K.C; r += 64) {
+        e_max = fmaxf(e_max, L.bnd[r]);
+        nu_max = fmaxf(nu_max, fabsf(L.nus[r]));
+        if (sizeof(T) == 4 && !(fabsf(L.nus[r]) < kNuLimit)) nu_max = INFINITY;
+      }
+      B = filter_bound(wave_max(e_max), wave_max(nu_max));
+      __syncthreads();
+    }
+  }
+  if (A.status && bad) atomicOr(A.status, bad);
+  if constexpr (!ONE) {
+    __syncthreads();
+    const size_t hb = static_cast<size_t>(h) * gridDim.x + b;
+    long long *sl = A.slab + hb * A.S + K.ucol;
+    for (int e = t; e < K.C * K.dx; e += kLloydThreads) {
+      const int r = e / K.dx, c = e - r * K.dx;
+      sl[e] = static_cast<long long>(L.sums[static_cast<size_t>(r) * 2 * P + (c & 1) * P + (c >> 1)]);
+    }
+    for (int r = t; r < K.C; r += kLloydThreads) A.cslab[hb * A.SC + K.ccol + r] = L.cnts[r];
+  }
+}
+
+template <typename T, bool ONE>
+__global__ __launch_bounds__(kLloydThreads) void km_lloyd_kernel(const LloydArgs A) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  __shared__ uint32_t cand[kLloydWaves][kWaveCand];
+  __shared__ unsigned long long best[kLloydWaves][32];
+  __shared__ int ncand[kLloydWaves];
+  __shared__ int next;
+  __shared__ float red[2][kLloydWaves];
+  const int w = threadIdx.x >> 6;
+  const LloydSub &K = A.sub[blockIdx.z];
+  switch (K.dxp) {
+    case 16: lloyd_block<16, T, ONE>(A, K, lds, cand[w], best[w], &ncand[w], &next, red); break;
+    case 32: lloyd_block<32, T, ONE>(A, K, lds, cand[w], best[w], &ncand[w], &next, red); break;
+    case 48: lloyd_block<48, T, ONE>(A, K, lds, cand[w], best[w], &ncand[w], &next, red); break;
+    case 64: lloyd_block<64, T, ONE>(A, K, lds, cand[w], best[w], &ncand[w], &next, red); break;
+    default: lloyd_block<128, T, ONE>(A, K, lds, cand[w], best[w], &ncand[w], &next, red); break;
+  }
+}
+
+}  // namespace
+
+// Up to 48 MiB of rows: their second and third reads come from the L2s and the
+// memory-side cache.  Beyond, the separate launches win, which stream the rows
+// with 16 waves per CU (a whole clustering, here against there: keys 5 heads x
+// 32760 tokens x 64 centroids, 42 MB, 555 / 605 us; layer 24 x 8192, 50 MB, 2041
+// / 2117 us; fp32 layer 8 x 16384, 67 MB, 2112 / 1920 us; keys 3 x 118800 x 128,
+// 91 MB, 1080 / 1002 us; keys 40 x 32760, 335 MB, 3320 / 2528 us).
+// All iterations in one block up to 10 slices (queries 3 heads x 300 rows x 16:
+// 173 us against 181 with several blocks, 700 rows x 32: 269 against 205).
+constexpr size_t kLloydBytes = 48u << 20;
+constexpr int kLloydOneBlock = 10;
+int km_lloyd_blocks(const KmProblem *p, int nsub, const AccPlan &plan) {
+  const int slices = (p[0].n + 31) / 32;
+  for (int m = 0; m < nsub; ++m)
+    if (!p[m].mfma || lloyd_lds(p[m].C, p[m].cpad, p[m].dx, p[m].dxp, nullptr, nullptr) > kLloydLds) return 0;
+  const size_t row_bytes = static_cast<size_t>(p[0].ld) * (p[0].bf16 ? 2 : 4);
+  if (row_bytes * p[0].n * p[0].heads > kLloydBytes) return 0;
+  if (slices <= kLloydOneBlock) return 1;
+  // about one block per CU, each wave with a slice, and no more slabs than the
+  // workspace has
+  int blocks = kAccTargetBlocks / (p[0].heads * nsub);
+  const int most = (slices + kLloydWaves - 1) / kLloydWaves;
+  if (blocks > most) blocks = most;
+  if (blocks > plan.blocks) blocks = plan.blocks;
+  return blocks < 1 ? 1 : blocks;
+}
+
+hipError_t km_lloyd(const KmProblem *p, int nsub, int blocks, int iters, bool final_assign,
+                    int32_t *chunk_hist, const AccPlan &plan, long long *slab, int32_t *cslab,
+                    int32_t *status, hipStream_t s) {
+  LloydArgs A{};
+  A.X = p[0].x;
+  A.x_hs = p[0].x_head_stride;
+  A.u_hs = p[0].u_head_stride;
+  A.a_hs = p[0].a_head_stride;
+  A.ld = p[0].ld;
+  A.n = p[0].n;
+  A.nchunks = km_nchunks(p[0].n);
+  A.iters = iters;
+  A.final_assign = final_assign ? 1 : 0;
+  A.chunk_hist = chunk_hist;
+  A.slab = slab;
+  A.cslab = cslab;
+  A.S = plan.S;
+  A.SC = plan.SC;
+  A.status = status;
+  A.lim = km_range_limit(p[0].n);
+  size_t lds = 0;
+  for (int m = 0; m < nsub; ++m) {
+    LloydSub &K = A.sub[m];
+    K.col0 = p[m].col0;
+    K.dx = p[m].dx;
+    K.dxp = p[m].dxp;
+    K.C = p[m].C;
+    K.cpad = p[m].cpad;
+    K.ucol = plan.ucol[m];
+    K.ccol = plan.ccol[m];
+    K.ubf = p[m].ubf;
+    K.nu = p[m].nu;
+    K.bnd = p[m].bnd;
+    K.u = p[m].u;
+    K.assign = p[m].assign;
+    const size_t need = lloyd_lds(K.C, K.cpad, K.dx, K.dxp, nullptr, nullptr);
+    lds = need > lds ? need : lds;
+  }
+  const dim3 grid(blocks, p[0].heads, nsub), block(kLloydThreads);
+#define SCOPE_LLOYD(T)                                                                  \
+  if (blocks == 1) hipLaunchKernelGGL((km_lloyd_kernel<T, true>), grid, block, lds, s, A); \
+  else hipLaunchKernelGGL((km_lloyd_kernel<T, false>), grid, block, lds, s, A)
+  if (p[0].bf16) {
+    SCOPE_LLOYD(uint16_t);
+  } else {
+    SCOPE_LLOYD(float);
+  }
+#undef SCOPE_LLOYD
+  return hipGetLastError();
+}
+
+}  // namespace scope

@@ -26,28 +26,6 @@ namespace {
 constexpr int kAccThreads = 1024;
 constexpr int kAccWaves = kAccThreads / 64;
 
-// rint(x * 2^24) as a two's complement int64, exact for |x| < 2^27: the
-// fp64 value x * 2^24 + 1.5 * 2^52 is rounded once, to the nearest integer
-// with ties to even (the spacing of doubles in [2^52, 2^53) is 1), and the
-// low 52 bits of its encoding then hold 2^51 + rint(x * 2^24).  The high
-// word minus the fixed exponent and 2^19 is the upper half of the result.
-// Other x (flagged in the status word) give some value, never a trap.
-__device__ __forceinline__ unsigned long long fixed24(float x) {
-  const double d = fma(static_cast<double>(x), 0x1p24, 0x1.8p52);
-  const unsigned long long bits = static_cast<unsigned long long>(__double_as_longlong(d));
-  const uint32_t lo = static_cast<uint32_t>(bits);
-  const uint32_t hi = static_cast<uint32_t>(bits >> 32) - 0x43380000u;
-  return (static_cast<unsigned long long>(hi) << 32) | lo;
-}
-
-// The int64 sums stay exact while n terms of magnitude below 2^(e+24) cannot
-// reach 2^63: |x| < lim = 2^e with e = min(22, 39 - ceil(log2 n)).  Larger or
-// non-finite inputs are flagged.
-__device__ __forceinline__ void check_value(float x, float lim, int &bad) {
-  if (!(fabsf(x) < lim))
-    bad |= isfinite(x) ? kStatusRange : (kStatusRange | kStatusNonFinite);
-}
-
 // CPL (2 or 4) adjacent channels of a row as floats.  VEC: one aligned load
 // of the whole chunk (every chunk complete); else scalar loads, repeating the
 // first element past the `nvalid` channels the chunk has.
@@ -264,15 +242,19 @@ size_t km_accum_cslab_bytes(const AccPlan &p, int heads) {
   return static_cast<size_t>(heads) * p.blocks * p.SC * sizeof(int32_t);
 }
 
+float km_range_limit(int n) {
+  int ce = 0;  // ceil(log2 n)
+  while (ce < 31 && (1LL << ce) < n) ++ce;
+  return ldexpf(1.0f, 39 - ce < 22 ? 39 - ce : 22);
+}
+
 hipError_t km_accum(const AccPlan &plan, const void *x, bool bf16, size_t x_hs,
                     int ld, int n, int heads, const int32_t *assign,
                     size_t a_hs, size_t a_ss, long long *slab, int32_t *cslab,
                     int32_t *status, hipStream_t s) {
   const dim3 grid(plan.blocks, plan.nwin, heads);
   const bool check = status != nullptr;
-  int ce = 0;  // ceil(log2 n)
-  while (ce < 31 && (1LL << ce) < n) ++ce;
-  const float lim = ldexpf(1.0f, 39 - ce < 22 ? 39 - ce : 22);
+  const float lim = km_range_limit(n);
   // vector loads need complete chunks starting on chunk boundaries
   auto aligned = [&](int cpl) {
     const size_t bytes = static_cast<size_t>(cpl) * (bf16 ? 2 : 4);

@@ -1,8 +1,10 @@
 """GPU k-means against the oracle, bit for bit, where the kernels' paths meet:
 element type, channel widths on both sides of each padded width (odd ones for
-fp32), one centroid to more than the LDS holds, few and many row blocks per
-head (the finish kernel shares a row's sums among four waves from 8 blocks
-on), exact ties, and fp32 values outside the range of the matrix-core filter.
+fp32), one centroid to more than the LDS holds, all iterations in one block
+(320 rows), several blocks of fused iterations, and the separate launches
+(sums beyond the LDS, or 48 MiB of rows), few and many row blocks per head
+(the finish kernel shares a row's sums among four waves from 8 blocks on),
+exact ties, and fp32 values outside the range of the matrix-core filter.
 """
 import numpy as np
 import pytest
@@ -72,6 +74,13 @@ def _check(x, dtype, split, c_q, c_m, iters, init_q, init_k):
     ("bf16", 1, 2311, (10, 2, 52), 1, (3, 2, 70)),
     ("bf16", 40, 300, (44, 42, 42), 33, (17, 64, 31)),  # few blocks per head
     ("bf16", 2, 1999, (16, 24, 24), 129, (32, 33, 16)),
+    ("bf16", 3, 320, (16, 56, 56), 31, (9, 33, 32)),    # one block, ten slices
+    ("bf16", 3, 321, (16, 56, 56), 31, (9, 33, 32)),    # eleven
+    ("f32", 1, 29, (43, 42, 43), 7, (5, 29, 1)),        # one slice, odd pairs
+    ("bf16", 300, 330, (8, 4, 4), 5, (3, 2, 7)),        # one block of 11 slices
+    ("bf16", 1, 700, (44, 42, 42), 86, (64, 90, 128)),  # sums about as large as the LDS
+    ("f32", 2, 98304, (16, 24, 24), 9, (8, 8, 8)),      # either side of 48 MiB
+    ("bf16", 2, 98305, (44, 42, 42), 9, (8, 8, 8)),
 ])
 def test_clustering_matches_the_oracle(dtype, heads, n, split, c_q, c_m):
     rng = np.random.default_rng(n + heads)
