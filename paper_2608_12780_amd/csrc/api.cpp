@@ -516,7 +516,7 @@ int32_t cluster_key_subspaces(const scope_shape *shape, const void *k, const int
   }
   scope::AccPlan plan = key_plan(shape, c_m);
   // the three assignments in one pass over K when the codebooks fit the LDS
-  // together, else one pass per subspace
+  // together, else blocks of their own for each subspace
   const bool fused = scope::km_assign3_ok(p);
   scope::DeviceArgs args{};
   if (fused) scope::km_assign3_args(p, w.args3, &args);
@@ -524,12 +524,7 @@ int32_t cluster_key_subspaces(const scope_shape *shape, const void *k, const int
   SCOPE_TRY(scope::km_init(p, 3, warm, init_idx, 3 * init_stride, init_stride, dev_status,
                            nullptr, 0, args, s));
   auto assign_all = [&]() -> hipError_t {
-    if (fused) return scope::km_assign3(p, w.args3, s);
-    for (int m = 0; m < 3; ++m) {
-      const hipError_t e = scope::km_assign(p[m], false, s);
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    return fused ? scope::km_assign3(p, w.args3, s) : scope::km_assign_subspaces(p, 3, s);
   };
   const int lloyd = scope::km_lloyd_blocks(p, 3, plan);
   if (lloyd) plan.blocks = lloyd;
@@ -756,13 +751,13 @@ int32_t scope_cluster_key_partition(const scope_shape *shape, const void *k,
       if (lloyd) {
         SCOPE_TRY(scope::km_lloyd(p, M, lloyd, 1, false, nullptr, plan, w.slab, w.cslab, status, s));
       } else {
-        for (int m = 0; m < M; ++m) SCOPE_TRY(scope::km_assign(p[m], false, s));
+        SCOPE_TRY(scope::km_assign_subspaces(p, M, s));
         SCOPE_TRY(scope::km_accum(plan, x, bf16, p[0].x_head_stride, d, n, shape->heads, w.assign,
                                   static_cast<size_t>(M) * n, n, w.slab, w.cslab, status, s));
       }
       SCOPE_TRY(scope::km_finish(plan, p, M, true, w.slab, w.cslab, s));
     }
-    for (int m = 0; m < M; ++m) SCOPE_TRY(scope::km_assign(p[m], false, s));
+    SCOPE_TRY(scope::km_assign_subspaces(p, M, s));
   }
   SCOPE_TRY(scope::km_codes16(w.assign, static_cast<size_t>(shape->heads) * M * n, codes, s));
   return SCOPE_OK;

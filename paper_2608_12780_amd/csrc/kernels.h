@@ -34,8 +34,8 @@ struct KmProblem {
   uint16_t *ubf;          // [heads][cpad][2 * dxp]: bf16 hi then lo terms
   float *nu;              // [heads][cpad]
   float *bnd;             // [heads][cpad]: bound on the two terms' residual
-  // codebooks beyond the LDS: per chunk and point the four smallest packed
-  // scores ([parts][heads][n][4]) and the point's norm bound ([heads][n])
+  // codebooks beyond the LDS: per chunk and point the three largest packed
+  // values ([parts][heads][n][4], the last unused) and the point's norm bound ([heads][n])
   float *part, *pnx;
 };
 
@@ -70,6 +70,8 @@ hipError_t km_init(const KmProblem *p, int nsub, bool warm, const int32_t *init,
                    int init_ms, int32_t *status, int32_t *zero, size_t zero_count,
                    const DeviceArgs &args, hipStream_t s);
 hipError_t km_assign(const KmProblem &p, bool with_hist, hipStream_t s);
+// The assignments of several subspaces of the same rows.
+hipError_t km_assign_subspaces(const KmProblem *p, int nsub, hipStream_t s);
 hipError_t km_group(const KmProblem &p, hipStream_t s);
 // The three key subspaces' assignments in one pass over the rows (matrix
 // cores; codebooks side by side in LDS): applies when km_assign3_ok.

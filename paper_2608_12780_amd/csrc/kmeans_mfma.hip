@@ -17,6 +17,55 @@ namespace scope {
 
 namespace {
 
+// The LDS of one block's assignment.
+template <int NW>
+struct AssignLds {
+  __attribute__((aligned(16))) uint16_t Us[kUbfLds];
+  __attribute__((aligned(16))) float nus[kMaxCpad];
+  __attribute__((aligned(16))) float nhs[kMaxCpad];
+  uint32_t cand[NW][kWaveCand];
+  unsigned long long best[NW][32];
+  int ncand[NW];
+  float red[2][NW];
+  int next_slice;
+};
+
+// Block b of nb: its contiguous range of (head, slice) pairs.
+template <int DXP, typename T>
+__device__ __forceinline__ void assign_range(const SliceArgs<T> &A, const uint16_t *__restrict__ ubf,
+                                             const float *__restrict__ nu,
+                                             const float *__restrict__ bnd, int heads, int b, int nb,
+                                             AssignLds<kWaves<T>> &L) {
+  constexpr int NW = kWaves<T>;
+  const int w = threadIdx.x >> 6;
+  const int nslices = (A.n + 31) / 32;
+  const long long total = static_cast<long long>(heads) * nslices;
+  const long long per = (total + nb - 1) / nb;
+  long long beg = static_cast<long long>(b) * per;
+  const long long end = beg + per < total ? beg + per : total;
+  while (beg < end) {
+    const int h = static_cast<int>(beg / nslices);
+    const long long seg_end = end < static_cast<long long>(h + 1) * nslices
+                                  ? end : static_cast<long long>(h + 1) * nslices;
+    __syncthreads();
+    if (threadIdx.x == 0) L.next_slice = 0;  // visible after the staging barrier
+    const FilterBound B = stage_codebook<DXP, NW, sizeof(T) == 4>(L.Us, L.nus, L.nhs, L.red, ubf, nu, bnd,
+                                                                 h, A.C, A.cpad);
+    // a wave that is done takes the block's next slice
+    const long long count = seg_end - beg;
+    for (;;) {
+      int u = 0;
+      if ((threadIdx.x & 63) == 0) u = atomicAdd(&L.next_slice, 1);
+      u = __builtin_amdgcn_readfirstlane(__shfl(u, 0));
+      if (u >= count) break;
+      const long long g = beg + u;
+      assign_slice<DXP, T>(A, L.Us, L.nus, L.nhs, B, h, static_cast<int>(g - static_cast<long long>(h) * nslices),
+                           L.cand[w], L.best[w], &L.ncand[w]);
+    }
+    beg = seg_end;
+  }
+}
+
 template <int DXP, typename T>
 __global__ __launch_bounds__(64 * kWaves<T>) void km_assign_mfma_kernel(
     const T *__restrict__ X, size_t x_hs, int ld, int col0, int dx,
@@ -24,43 +73,36 @@ __global__ __launch_bounds__(64 * kWaves<T>) void km_assign_mfma_kernel(
     const uint16_t *__restrict__ ubf, const float *__restrict__ nu,
     const float *__restrict__ bnd, int C, int cpad, int32_t *assign,
     size_t a_hs, int32_t *chunk_hist, int nchunks) {
-  constexpr int NW = kWaves<T>;
-  __shared__ __attribute__((aligned(16))) uint16_t Us[kUbfLds];
-  __shared__ __attribute__((aligned(16))) float nus[kMaxCpad];
-  __shared__ __attribute__((aligned(16))) float nhs[kMaxCpad];
-  __shared__ uint32_t cand[NW][kWaveCand];
-  __shared__ unsigned long long best[NW][32];
-  __shared__ int ncand[NW];
-  __shared__ float red[2][NW];
-  __shared__ int next_slice;
-  const int w = threadIdx.x >> 6;
+  __shared__ AssignLds<kWaves<T>> L;
   const SliceArgs<T> A{X, x_hs, ld, col0, dx, n, C, cpad, U, u_hs, assign, a_hs, chunk_hist, nchunks};
-  const int nslices = (n + 31) / 32;
+  assign_range<DXP, T>(A, ubf, nu, bnd, heads, blockIdx.x, gridDim.x, L);
+}
 
-  // this block's contiguous range of (head, slice) pairs
-  const long long total = static_cast<long long>(heads) * nslices;
-  const long long per = (total + gridDim.x - 1) / gridDim.x;
-  long long beg = static_cast<long long>(blockIdx.x) * per;
-  const long long end = beg + per < total ? beg + per : total;
-  while (beg < end) {
-    const int h = static_cast<int>(beg / nslices);
-    const long long seg_end = end < static_cast<long long>(h + 1) * nslices
-                                  ? end : static_cast<long long>(h + 1) * nslices;
-    __syncthreads();
-    if (threadIdx.x == 0) next_slice = 0;  // visible after the staging barrier
-    const FilterBound B = stage_codebook<DXP, NW, sizeof(T) == 4>(Us, nus, nhs, red, ubf, nu, bnd, h, C, cpad);
-    // a wave that is done takes the block's next slice
-    const long long count = seg_end - beg;
-    for (;;) {
-      int u = 0;
-      if ((threadIdx.x & 63) == 0) u = atomicAdd(&next_slice, 1);
-      u = __builtin_amdgcn_readfirstlane(__shfl(u, 0));
-      if (u >= count) break;
-      const long long g = beg + u;
-      assign_slice<DXP, T>(A, Us, nus, nhs, B, h, static_cast<int>(g - static_cast<long long>(h) * nslices),
-                        cand[w], best[w], &ncand[w]);
-    }
-    beg = seg_end;
+// Several subspaces in one launch, each with blocks of its own (from first[m]
+// on) in proportion to its work.  One launch per subspace leaves the last
+// slices of each to a few waves: 5 heads x 32760 rows are 1.25 slices per wave
+// of the chip, two rounds where one and a quarter would do.
+template <typename T>
+struct ManyArgs {
+  int nsub, heads;
+  int first[kMaxSub + 1], dxp[kMaxSub];
+  SliceArgs<T> a[kMaxSub];
+  const uint16_t *ubf[kMaxSub];
+  const float *nu[kMaxSub], *bnd[kMaxSub];
+};
+template <typename T>
+__global__ __launch_bounds__(64 * kWaves<T>) void km_assign_mfma_many_kernel(const ManyArgs<T> M) {
+  __shared__ AssignLds<kWaves<T>> L;
+  int m = 0;
+  while (m + 1 < M.nsub && static_cast<int>(blockIdx.x) >= M.first[m + 1]) ++m;
+  const int b = blockIdx.x - M.first[m], nb = M.first[m + 1] - M.first[m];
+  const SliceArgs<T> A = M.a[m];
+  switch (M.dxp[m]) {
+    case 16: assign_range<16, T>(A, M.ubf[m], M.nu[m], M.bnd[m], M.heads, b, nb, L); break;
+    case 32: assign_range<32, T>(A, M.ubf[m], M.nu[m], M.bnd[m], M.heads, b, nb, L); break;
+    case 48: assign_range<48, T>(A, M.ubf[m], M.nu[m], M.bnd[m], M.heads, b, nb, L); break;
+    case 64: assign_range<64, T>(A, M.ubf[m], M.nu[m], M.bnd[m], M.heads, b, nb, L); break;
+    default: assign_range<128, T>(A, M.ubf[m], M.nu[m], M.bnd[m], M.heads, b, nb, L); break;
   }
 }
 
@@ -140,10 +182,10 @@ __global__ __launch_bounds__(64 * kWaves<T>) void km_assign_mfma3_kernel(
 // Codebooks larger than the LDS holds (e.g. 300 centroids at d = 128) are
 // cut into chunks of at most CR rows, and every chunk gets its own
 // persistent blocks, which keep the chunk in LDS for their whole range of
-// slices (waves run independently, as above).  Per point, each chunk yields
-// its four smallest packed scores (indices over the whole codebook), and
-// chunk 0 also the point's norm bound.  The decision kernel below merges the
-// lists, one point per thread.
+// slices (waves take slices independently, as above).  Per point, each chunk
+// yields its three largest packed values (indices over the whole codebook),
+// and chunk 0 also the point's norm bound.  The decision kernel below merges
+// the lists, one point per thread.
 template <int DXP, typename T>
 __global__ __launch_bounds__(64 * kWaves<T>) void km_assign_mfma_part_kernel(
     const T *__restrict__ X, size_t x_hs, int ld, int col0, int dx,
@@ -151,10 +193,12 @@ __global__ __launch_bounds__(64 * kWaves<T>) void km_assign_mfma_part_kernel(
     int cpad, int crows, float *part, float *pnx) {
   constexpr int US = 2 * DXP + 8;  // LDS row stride of the two-term codebook
   constexpr int KS = DXP / 16;     // MFMA k-steps per term
+  constexpr int NW = kWaves<T>;
   __shared__ __attribute__((aligned(16))) uint16_t Us[kUbfLds];
-  __shared__ float nus[kMaxCpad];
+  __shared__ __attribute__((aligned(16))) float nhs[kMaxCpad];
+  __shared__ int next_slice;
   const int t = threadIdx.x;
-  const int lane = t & 63, w = t >> 6, l32 = lane & 31, hf = lane >> 5;
+  const int lane = t & 63, l32 = lane & 31, hf = lane >> 5;
   const int chunk = blockIdx.y, r0 = chunk * crows;
   const int rows = cpad - r0 < crows ? cpad - r0 : crows;  // a multiple of 32
   const int ib = 32 - __clz(cpad - 1);
@@ -170,67 +214,35 @@ __global__ __launch_bounds__(64 * kWaves<T>) void km_assign_mfma_part_kernel(
     const int h = static_cast<int>(beg / nslices);
     const long long seg_end = end < static_cast<long long>(h + 1) * nslices
                                   ? end : static_cast<long long>(h + 1) * nslices;
-    // stage this head's chunk (rows r0 .. r0+rows) and its norms
+    // stage this head's chunk (rows r0 .. r0+rows) and its start values
     __syncthreads();
+    if (t == 0) next_slice = 0;
     const uint16_t *ub = ubf + (static_cast<size_t>(h) * cpad + r0) * (2 * DXP);
-    for (int e = t; e < rows * (DXP / 4); e += 64 * kWaves<T>) {
+    for (int e = t; e < rows * (DXP / 4); e += 64 * NW) {
       const int r = e / (DXP / 4), q = e % (DXP / 4);
       *reinterpret_cast<uint4 *>(&Us[r * US + 8 * q]) =
           *reinterpret_cast<const uint4 *>(ub + static_cast<size_t>(r) * (2 * DXP) + 8 * q);
     }
-    for (int r = t; r < rows; r += 64 * kWaves<T>)
-      nus[r] = nu[static_cast<size_t>(h) * cpad + r0 + r];
+    for (int r = t; r < rows; r += 64 * NW)
+      nhs[r] = -0.5f * nu[static_cast<size_t>(h) * cpad + r0 + r];
     __syncthreads();
-    for (long long g = beg + w; g < seg_end; g += kWaves<T>) {
-      const int sl = static_cast<int>(g - static_cast<long long>(h) * nslices);
+    const long long count = seg_end - beg;
+    for (;;) {
+      int u = 0;
+      if (lane == 0) u = atomicAdd(&next_slice, 1);
+      u = __builtin_amdgcn_readfirstlane(u);
+      if (u >= count) break;
+      const int sl = static_cast<int>(beg + u - static_cast<long long>(h) * nslices);
       const int i = sl * 32 + l32;
       const bool valid = i < n;
       const T *xrow = X + h * x_hs + static_cast<size_t>(valid ? i : 0) * ld + col0;
       PointFrag<KS, T> xf;
       float ss = load_point<KS, T>(xrow, hf, dx, valid, vec, xf);
       ss += __shfl_xor(ss, 32);
-
-      auto chain = [&](int rb) {  // rb: row within the chunk
-        f32x16 acc;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
-        score_chain<DXP, T>(&Us[(rb + l32) * US + 8 * hf], xf, acc);
-        return acc;
-      };
-      // the four smallest packed scores, m1 <= m2 <= m3 <= m4
-      float m1 = 0x1.1p127f, m2 = 0x1.1p127f, m3 = 0x1.1p127f, m4 = 0x1.1p127f;
-      auto insert = [&](float sp) {
-        m4 = __builtin_amdgcn_fmed3f(m3, m4, sp);
-        m3 = __builtin_amdgcn_fmed3f(m2, m3, sp);
-        m2 = __builtin_amdgcn_fmed3f(m1, m2, sp);
-        m1 = fminf(m1, sp);
-      };
-      auto fold = [&](const f32x16 &acc, int rb) {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int rl = rb + 8 * (e >> 2) + 4 * hf + (e & 3);
-          const float sc = fmaf(-2.0f, acc[e], nus[rl]);
-          insert(__uint_as_float((__float_as_uint(sc) & ~imask) | static_cast<uint32_t>(r0 + rl)));
-        }
-      };
-      f32x16 prev = chain(0);
-      for (int rb = 32; rb < rows; rb += 32) {
-        const f32x16 cur = chain(rb);
-        fold(prev, rb - 32);
-        prev = cur;
-      }
-      fold(prev, rows - 32);
-      {  // the two half-waves saw disjoint centroids of the same points
-        const float o1 = __shfl_xor(m1, 32), o2 = __shfl_xor(m2, 32);
-        const float o3 = __shfl_xor(m3, 32), o4 = __shfl_xor(m4, 32);
-        insert(o1);
-        insert(o2);
-        insert(o3);
-        insert(o4);
-      }
+      const Top3 top = top_scores<DXP, T>(Us, nhs, xf, rows, imask, r0);
       if (valid && hf == 0) {
         *reinterpret_cast<float4 *>(part + ((static_cast<size_t>(chunk) * heads + h) * n + i) * 4) =
-            make_float4(m1, m2, m3, m4);
+            make_float4(top.m1, top.m2, top.m3, 0.0f);
         if (chunk == 0) pnx[static_cast<size_t>(h) * n + i] = sqrtf(ss) * 1.0001f + 1e-30f;
       }
     }
@@ -238,11 +250,11 @@ __global__ __launch_bounds__(64 * kWaves<T>) void km_assign_mfma_part_kernel(
   }
 }
 
-// The decision for chunked codebooks, one point per thread: the chunks'
-// lists merged into the four smallest packed scores, then the margin of the
-// kernel above; with a runner-up inside it, the fourth score bounds the
-// candidates to at most three, re-scored canonically, and only four or more
-// candidates scan every centroid canonically.
+// The decision for chunked codebooks, one point per thread: the margin of the
+// kernel above around the largest of all chunks' values.  A chunk whose third
+// value lies outside it has at most two candidates, both listed; the listed
+// candidates are re-scored canonically if there are several, and only a point
+// with three candidates in one chunk (or more) scans every centroid.
 template <int DXP, typename T>
 __global__ __launch_bounds__(256) void km_assign_decide_kernel(
     const T *__restrict__ X, size_t x_hs, int ld, int col0, int dx, int n,
@@ -268,62 +280,88 @@ __global__ __launch_bounds__(256) void km_assign_decide_kernel(
   }
   __syncthreads();
   const FilterBound B = reduce_bound<4>(red);
-  const int i = blockIdx.x * 256 + t;
-  if (i >= n) return;
+  // every lane of a wave stays for the joint scans; those past the end repeat
+  // the last point
+  const bool valid = static_cast<int>(blockIdx.x * 256 + t) < n;
+  const int i = min(static_cast<int>(blockIdx.x * 256 + t), n - 1);
   const int ib = 32 - __clz(cpad - 1);
   const uint32_t imask = (1u << ib) - 1u;
   const float dpack = __uint_as_float(static_cast<uint32_t>(127 + ib - 23) << 23);
-  float m1 = 0x1.1p127f, m2 = 0x1.1p127f, m3 = 0x1.1p127f, m4 = 0x1.1p127f;
-  auto insert = [&](float sp) {
-    m4 = __builtin_amdgcn_fmed3f(m3, m4, sp);
-    m3 = __builtin_amdgcn_fmed3f(m2, m3, sp);
-    m2 = __builtin_amdgcn_fmed3f(m1, m2, sp);
-    m1 = fminf(m1, sp);
+  auto listed = [&](int k) {
+    return *reinterpret_cast<const float4 *>(part + ((static_cast<size_t>(k) * heads + h) * n + i) * 4);
   };
-  for (int k = 0; k < nparts; ++k) {
-    const float4 v = *reinterpret_cast<const float4 *>(
-        part + ((static_cast<size_t>(k) * heads + h) * n + i) * 4);
-    insert(v.x);
-    insert(v.y);
-    insert(v.z);
-    insert(v.w);
-  }
+  float m1 = -0x1.1p127f;
+  for (int k = 0; k < nparts; ++k) m1 = fmaxf(m1, listed(k).x);
   const float nx = pnx[static_cast<size_t>(h) * n + i];
-  const float beta = margin<DXP, T, false>(nx, B);
-  const float slack = (2.0f * beta + 2.0f * dpack * fabsf(m1)) * 1.001f;
-  const float lim = m1 + slack;
-  const float thr = lim + fabsf(lim) * 2e-6f + 1e-30f;
+  const float beta = margin<DXP, T>(nx, B);
+  const float slack = (beta + 2.0f * dpack * fabsf(m1)) * 1.001f;
+  const float lim = m1 - slack;
+  const float thr = lim - fabsf(lim) * 2e-6f - 1e-30f;
   int arg = static_cast<int>(__float_as_uint(m1) & imask);
+  int near = 0;         // listed candidates
+  bool scan = false;
+  for (int k = 0; k < nparts; ++k) {
+    const float4 v = listed(k);
+    near += (!(v.x < thr) ? 1 : 0) + (!(v.y < thr) ? 1 : 0);
+    scan = scan || !(v.z < thr);
+  }
   const T *xr = X + h * x_hs + static_cast<size_t>(i) * ld + col0;
   const float *Uh = U + h * u_hs;
-  if (sizeof(T) == 4 && !(nx < kNormLimit && B.numax < kNuLimit * 1.01f)) {
+  const float *nuh = nu + static_cast<size_t>(h) * cpad;
+  auto score_key = [&](const T *x, int r) {
+    const float dot = canon_dot(x, Uh + static_cast<size_t>(r) * dx, dx);
+    const float sc = fmaf(-2.0f, dot, nuh[r]) + 0.0f;
+    return (static_cast<unsigned long long>(asc_key(sc)) << 32) | static_cast<unsigned>(r);
+  };
+  const bool unsafe = sizeof(T) == 4 && !(nx < kNormLimit && B.numax < kNuLimit * 1.01f);
+  if (unsafe) {
     // outside the filter's range: every centroid, canonically
-    arg = canon_scan(xr, Uh, nu + static_cast<size_t>(h) * cpad, C, dx);
-  } else if (!(m2 > thr)) {
+    arg = canon_scan(xr, Uh, nuh, C, dx);
+  } else if (!scan && near > 1) {
     unsigned long long b = ~0ull;
-    auto rescore = [&](int r) {
-      r = min(r, C - 1);
-      const float *u = Uh + static_cast<size_t>(r) * dx;
-      const float dot = canon_dot(xr, u, dx);
-      const float sc = fmaf(-2.0f, dot, nu[static_cast<size_t>(h) * cpad + r]) + 0.0f;
-      const unsigned long long key =
-          (static_cast<unsigned long long>(asc_key(sc)) << 32) | static_cast<unsigned>(r);
-      b = key < b ? key : b;
-    };
-    if (m4 > thr) {
-      // every candidate is among the three smallest
-      rescore(arg);
-      rescore(static_cast<int>(__float_as_uint(m2) & imask));
-      if (m3 <= thr) rescore(static_cast<int>(__float_as_uint(m3) & imask));
-    } else {
-      for (int r = 0; r < C; ++r) rescore(r);
+    for (int k = 0; k < nparts; ++k) {
+      const float4 v = listed(k);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const float c = j ? v.y : v.x;
+        if (!(c < thr)) {
+          const unsigned long long key = score_key(xr, min(static_cast<int>(__float_as_uint(c) & imask), C - 1));
+          b = key < b ? key : b;
+        }
+      }
     }
     arg = static_cast<int>(b & 0xFFFFFFFFu);
   }
+  // a scan takes the whole wave, each lane every 64th centroid (one thread
+  // going through 300 centroids held its block up for 350 us)
+  for (uint64_t todo = __ballot(valid && scan && !unsafe); todo; todo &= todo - 1) {
+    const int src = __ffsll(static_cast<long long>(todo)) - 1;
+    const T *xs = X + h * x_hs + static_cast<size_t>(__shfl(i, src)) * ld + col0;
+    unsigned long long b = ~0ull;
+    for (int r = lane; r < C; r += 64) {
+      const unsigned long long key = score_key(xs, r);
+      b = key < b ? key : b;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const unsigned long long other = __shfl_xor(b, o);
+      b = other < b ? other : b;
+    }
+    if (lane == src) arg = static_cast<int>(b & 0xFFFFFFFFu);
+  }
+  if (!valid) return;
   arg = min(max(arg, 0), C - 1);
   assign[h * a_hs + i] = arg;
   if (chunk_hist)
     atomicAdd(&chunk_hist[(static_cast<size_t>(h) * nchunks + (i / kAssignBlock)) * C + arg], 1);
+}
+
+int cu_count() {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+    cus = 256;
+  return cus;
 }
 
 template <int DXP, typename T>
@@ -333,10 +371,7 @@ hipError_t launch_mfma(const KmProblem &p, bool with_hist, hipStream_t s) {
   // persistent blocks, one per CU (the codebook fills most of the LDS),
   // each over a contiguous range of (head, 32-point slice) pairs
   const long long slices = static_cast<long long>(p.heads) * ((p.n + 31) / 32);
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-    cus = 256;
+  const int cus = cu_count();
   const int blocks = static_cast<int>(slices < static_cast<long long>(cus) * kWaves<T>
                                           ? (slices + kWaves<T> - 1) / kWaves<T> : cus);
   const T *x = static_cast<const T *>(p.x);
@@ -391,10 +426,7 @@ Sub3<T> sub3_args(const KmProblem (&p)[3]) {
 template <int D0, int D1, int D2, typename T>
 hipError_t launch_mfma3(const KmProblem (&p)[3], const void *dev_args, hipStream_t s) {
   const long long slices = static_cast<long long>(p[0].heads) * ((p[0].n + 31) / 32);
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-    cus = 256;
+  const int cus = cu_count();
   const int blocks = static_cast<int>(slices < static_cast<long long>(cus) * kWaves<T>
                                           ? (slices + kWaves<T> - 1) / kWaves<T> : cus);
   hipLaunchKernelGGL((km_assign_mfma3_kernel<D0, D1, D2, T>), dim3(blocks), dim3(64 * kWaves<T>),
@@ -473,6 +505,36 @@ bool km_mfma_ok(bool bf16, int ld, int col0, int dx, int C) {
 
 namespace {
 template <typename T>
+hipError_t assign_many(const KmProblem *p, int nsub, hipStream_t s) {
+  ManyArgs<T> M{};
+  M.heads = p[0].heads;
+  double cost[kMaxSub], sum = 0.0;
+  for (int m = 0; m < nsub; ++m) {
+    // per 32 x 32 values: 4 dxp cycles of MFMA, 256 of the fold
+    cost[m] = static_cast<double>(p[m].cpad) * (4 * p[m].dxp + 256);
+    sum += cost[m];
+  }
+  const int cus = cu_count();
+  const long long slices = static_cast<long long>(p[0].heads) * ((p[0].n + 31) / 32);
+  const long long most = (slices + kWaves<T> - 1) / kWaves<T>;
+  for (int m = 0; m < nsub; ++m) {
+    const KmProblem &q = p[m];
+    long long blocks = static_cast<long long>(cus * cost[m] / sum + 0.5);
+    blocks = blocks < 1 ? 1 : blocks > most ? most : blocks;
+    M.first[m + 1] = M.first[m] + static_cast<int>(blocks);
+    M.dxp[m] = q.dxp;
+    M.a[m] = SliceArgs<T>{static_cast<const T *>(q.x), q.x_head_stride, q.ld, q.col0, q.dx,
+                          q.n, q.C, q.cpad, q.u, q.u_head_stride, q.assign, q.a_head_stride,
+                          nullptr, 0};
+    M.ubf[m] = q.ubf;
+    M.nu[m] = q.nu;
+    M.bnd[m] = q.bnd;
+  }
+  M.nsub = nsub;
+  hipLaunchKernelGGL(km_assign_mfma_many_kernel<T>, dim3(M.first[nsub]), dim3(64 * kWaves<T>), 0, s, M);
+  return hipGetLastError();
+}
+template <typename T>
 hipError_t assign_mfma(const KmProblem &p, bool with_hist, hipStream_t s) {
   switch (p.dxp) {
     case 16: return launch_mfma<16, T>(p, with_hist, s);
@@ -483,6 +545,35 @@ hipError_t assign_mfma(const KmProblem &p, bool with_hist, hipStream_t s) {
   }
 }
 }  // namespace
+
+hipError_t km_assign_subspaces(const KmProblem *p, int nsub, hipStream_t s) {
+  KmProblem fits[kMaxSub];
+  int nfits = 0;
+  for (int m = 0; m < nsub; ++m) {
+    if (p[m].mfma && km_parts(p[m].C, p[m].dx) == 1) {
+      fits[nfits++] = p[m];
+    } else {
+      const hipError_t e = km_assign(p[m], false, s);
+      if (e != hipSuccess) return e;
+    }
+  }
+  if (nfits == 0) return hipSuccess;
+  // one launch where the rounds of slices of a single subspace would end on a
+  // mostly idle one (5 heads x 32760 rows x 333 centroids, 42-44 channels: 1.25
+  // rounds, 86 us apart, 58 us together; 3 x 118800, 16 / 56 / 56 channels: 2.7
+  // rounds, 130 us apart, 136 us together)
+  const long long slices = static_cast<long long>(p[0].heads) * ((p[0].n + 31) / 32);
+  const long long round = static_cast<long long>(cu_count()) * (p[0].bf16 ? kWaves<uint16_t> : kWaves<float>);
+  const bool uneven = 100 * ((slices + round - 1) / round * round) > 115 * slices;
+  if (nfits == 1 || !uneven) {
+    for (int m = 0; m < nfits; ++m) {
+      const hipError_t e = km_assign(fits[m], false, s);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  return p[0].bf16 ? assign_many<uint16_t>(fits, nfits, s) : assign_many<float>(fits, nfits, s);
+}
 
 hipError_t km_assign_mfma(const KmProblem &p, bool with_hist, hipStream_t s) {
   return p.bf16 ? assign_mfma<uint16_t>(p, with_hist, s) : assign_mfma<float>(p, with_hist, s);

@@ -353,15 +353,99 @@ __device__ __forceinline__ FilterBound stage_codebook(uint16_t *Us, float *nus, 
 }
 
 // The margin beta of a point of norm at most nx, in the canonical scale.
-// START: the accumulator started at -nu / 2, which rode through every
-// addition; else nu joins in one final rounding.
-template <int DXP, typename T, bool START>
+template <int DXP, typename T>
 __device__ __forceinline__ float margin(float nx, FilterBound B) {
   const float kappa = 8.0f * DXP * 0x1p-24f;
   float beta = 2.0f * nx * (B.E + kappa * B.Nmax) +
-               0x1p-23f * ((START ? 2.0f * DXP + 1.0f : 1.0f) * B.numax + 2.02f * nx * B.Nmax);
+               0x1p-23f * ((2.0f * DXP + 1.0f) * B.numax + 2.02f * nx * B.Nmax);
   if constexpr (sizeof(T) == 4) beta += 2.0f * 1.02f * 0x1p-15f * nx * B.Nmax + 0x1p-110f * (nx + B.Nmax);
   return beta * 1.01f + 1e-25f;
+}
+
+// a_r of the 32 centroids rb .. rb+31 of the staged codebook for the wave's 32
+// points: the accumulator starts at -nu_r / 2 (lane holds rows rb + 8(e/4) +
+// 4hf + e%4).
+template <int DXP, typename T>
+__device__ __forceinline__ f32x16 score_block(const uint16_t *Us, const float *nhs,
+                                              const PointFrag<DXP / 16, T> &xf, int rb) {
+  constexpr int US = 2 * DXP + 8;  // LDS row stride of the two-term codebook
+  const int lane = threadIdx.x & 63, l32 = lane & 31, hf = lane >> 5;
+  f32x16 acc;
+  const float *nh = nhs + rb + 4 * hf;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float4 v = *reinterpret_cast<const float4 *>(nh + 8 * q);
+    acc[4 * q + 0] = v.x;
+    acc[4 * q + 1] = v.y;
+    acc[4 * q + 2] = v.z;
+    acc[4 * q + 3] = v.w;
+  }
+  score_chain<DXP, T>(&Us[(rb + l32) * US + 8 * hf], xf, acc);
+  return acc;
+}
+
+// The three largest packed values of the codebook's first `rows` rows (a
+// multiple of 32) per point, indices from r0 on (each med3 keeps the larger
+// two of its inputs' lower pair; the start value lies below every value of
+// valid inputs).  The index packed in the pass leaves out the lane's 4 hf,
+// which is the same for all of the lane's values (so their order is that of
+// the full index) and is added once after the pass.  The mask stays in a
+// vector register so that the index, uniform across the wave, can come from a
+// scalar register.
+struct Top3 {
+  float m1, m2, m3;
+};
+template <int DXP, typename T>
+__device__ __forceinline__ Top3 top_scores(const uint16_t *Us, const float *nhs,
+                                           const PointFrag<DXP / 16, T> &xf, int rows,
+                                           uint32_t imask, int r0) {
+  const int hf = (threadIdx.x & 63) >> 5;
+  uint32_t vmask;
+  asm volatile("v_mov_b32 %0, %1" : "=v"(vmask) : "s"(~imask));
+  float m1 = -0x1.1p127f, m2 = -0x1.1p127f, m3 = -0x1.1p127f;
+  auto chain = [&](int rb) { return score_block<DXP, T>(Us, nhs, xf, rb); };
+  auto fold = [&](const f32x16 &acc, int rb) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const uint32_t ru = static_cast<uint32_t>(
+          __builtin_amdgcn_readfirstlane(r0 + rb + 8 * (e >> 2) + (e & 3)));
+      const float sp = __uint_as_float((__float_as_uint(acc[e]) & vmask) | ru);
+      m3 = __builtin_amdgcn_fmed3f(m2, m3, sp);
+      m2 = __builtin_amdgcn_fmed3f(m1, m2, sp);
+      m1 = __builtin_amdgcn_fmed3f(m1, sp, 0x1.1p127f);  // max without NaN quieting
+    }
+  };
+  // software pipeline: the values of one block are folded while the MFMAs
+  // of the next run; two accumulators alternate, so no copies
+  f32x16 acc0 = chain(0), acc1;
+  int rb = 32;
+  for (; rb + 32 < rows; rb += 64) {
+    acc1 = chain(rb);
+    fold(acc0, rb - 32);
+    acc0 = chain(rb + 32);
+    fold(acc1, rb);
+  }
+  if (rb < rows) {
+    acc1 = chain(rb);
+    fold(acc0, rb - 32);
+    fold(acc1, rb);
+  } else {
+    fold(acc0, rb - 32);
+  }
+  const uint32_t add = 4u * static_cast<uint32_t>(hf);
+  m1 = __uint_as_float(__float_as_uint(m1) + add);
+  m2 = __uint_as_float(__float_as_uint(m2) + add);
+  m3 = __uint_as_float(__float_as_uint(m3) + add);
+  // the other half-wave's three into this one's (same multiset, same
+  // result in both halves)
+  const float o[3] = {__shfl_xor(m1, 32), __shfl_xor(m2, 32), __shfl_xor(m3, 32)};
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    m3 = __builtin_amdgcn_fmed3f(m2, m3, o[q]);
+    m2 = __builtin_amdgcn_fmed3f(m1, m2, o[q]);
+    m1 = __builtin_amdgcn_fmed3f(m1, o[q], 0x1.1p127f);
+  }
+  return Top3{m1, m2, m3};
 }
 
 // One codebook's view of the rows: channels col0 .. col0+dx of X[h] (row
@@ -390,7 +474,6 @@ __device__ __forceinline__ int assign_slice(const SliceArgs<T> &A, const uint16_
                                              int h, int sl,
                                              uint32_t *cand_w, unsigned long long *best_w,
                                              int *ncand_w) {
-  constexpr int US = 2 * DXP + 8;  // LDS row stride of the two-term codebook
   constexpr int KS = DXP / 16;     // MFMA k-steps per term
   const int lane = threadIdx.x & 63, l32 = lane & 31, hf = lane >> 5;
   const T *X = A.X;
@@ -413,77 +496,11 @@ __device__ __forceinline__ int assign_slice(const SliceArgs<T> &A, const uint16_
   float ss = load_point<KS, T>(xrow, hf, dx, valid, vec, xf);
   ss += __shfl_xor(ss, 32);
   const float nx = sqrtf(ss) * 1.0001f + 1e-30f;
-  const float beta = margin<DXP, T, true>(nx, B);
+  const float beta = margin<DXP, T>(nx, B);
 
-  // a_r of the 32 centroids rb .. rb+31 for the 32 points: the accumulator
-  // starts at -nu_r / 2 (lane holds rows rb + 8(e/4) + 4hf + e%4)
-  auto chain = [&](int rb) {
-    f32x16 acc;
-    const float *nh = nhs + rb + 4 * hf;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const float4 v = *reinterpret_cast<const float4 *>(nh + 8 * q);
-      acc[4 * q + 0] = v.x;
-      acc[4 * q + 1] = v.y;
-      acc[4 * q + 2] = v.z;
-      acc[4 * q + 3] = v.w;
-    }
-    score_chain<DXP, T>(&Us[(rb + l32) * US + 8 * hf], xf, acc);
-    return acc;
-  };
-  // one pass: the three largest packed values per point (each med3 keeps
-  // the larger two of its inputs' lower pair; the start value lies below
-  // every value of valid inputs).  The index packed here leaves out the
-  // lane's 4 hf, which is the same for all of the lane's values (so their
-  // order is that of the full index) and is added once after the pass.
-  // The mask stays in a vector register so that the index, uniform across
-  // the wave, can come from a scalar register.
-  uint32_t vmask;
-  asm volatile("v_mov_b32 %0, %1" : "=v"(vmask) : "s"(~imask));
-  float m1 = -0x1.1p127f, m2 = -0x1.1p127f, m3 = -0x1.1p127f;
-  auto fold = [&](const f32x16 &acc, int rb) {
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const uint32_t ru = static_cast<uint32_t>(
-          __builtin_amdgcn_readfirstlane(rb + 8 * (e >> 2) + (e & 3)));
-      const float sp = __uint_as_float((__float_as_uint(acc[e]) & vmask) | ru);
-      m3 = __builtin_amdgcn_fmed3f(m2, m3, sp);
-      m2 = __builtin_amdgcn_fmed3f(m1, m2, sp);
-      m1 = __builtin_amdgcn_fmed3f(m1, sp, 0x1.1p127f);  // max without NaN quieting
-    }
-  };
-  // software pipeline: the values of one block are folded while the MFMAs
-  // of the next run; two accumulators alternate, so no copies
-  f32x16 acc0 = chain(0), acc1;
-  int rb = 32;
-  for (; rb + 32 < cpad; rb += 64) {
-    acc1 = chain(rb);
-    fold(acc0, rb - 32);
-    acc0 = chain(rb + 32);
-    fold(acc1, rb);
-  }
-  if (rb < cpad) {
-    acc1 = chain(rb);
-    fold(acc0, rb - 32);
-    fold(acc1, rb);
-  } else {
-    fold(acc0, rb - 32);
-  }
-  {
-    const uint32_t add = 4u * static_cast<uint32_t>(hf);
-    m1 = __uint_as_float(__float_as_uint(m1) + add);
-    m2 = __uint_as_float(__float_as_uint(m2) + add);
-    m3 = __uint_as_float(__float_as_uint(m3) + add);
-    // the other half-wave's three into this one's (same multiset, same
-    // result in both halves)
-    const float o[3] = {__shfl_xor(m1, 32), __shfl_xor(m2, 32), __shfl_xor(m3, 32)};
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      m3 = __builtin_amdgcn_fmed3f(m2, m3, o[q]);
-      m2 = __builtin_amdgcn_fmed3f(m1, m2, o[q]);
-      m1 = __builtin_amdgcn_fmed3f(m1, o[q], 0x1.1p127f);
-    }
-  }
+  auto chain = [&](int rb) { return score_block<DXP, T>(Us, nhs, xf, rb); };
+  const Top3 top = top_scores<DXP, T>(Us, nhs, xf, cpad, imask, 0);
+  const float m1 = top.m1, m2 = top.m2, m3 = top.m3;
   // candidates: a_r >= max a - beta (halved scale: 2 x beta / 2), less the
   // two packing perturbations
   const float slack = (beta + 2.0f * dpack * fabsf(m1)) * 1.001f;
