@@ -130,10 +130,11 @@ struct Crossing {
 };
 
 // Smallest bin b with base + sum_{b' <= b} w[b'] >= target, where w is the
-// mass histogram (BY_MASS) or the count histogram.  Two bins per thread.
-template <bool BY_MASS>
-__device__ Crossing find_crossing(const uint32_t *hc, const uint64_t *hm,
-                                  int nbins, uint64_t base, uint64_t target) {
+// mass histogram (BY_MASS) or the count histogram; target_of gives the target
+// from the sum of all bins.  Two bins per thread.
+template <bool BY_MASS, typename Target>
+__device__ Crossing find_crossing_of(const uint32_t *hc, const uint64_t *hm,
+                                     int nbins, uint64_t base, Target target_of) {
   __shared__ Crossing res;
   const int t = threadIdx.x;
   const int b0 = 2 * t, b1 = 2 * t + 1;
@@ -150,6 +151,7 @@ __device__ Crossing find_crossing(const uint32_t *hc, const uint64_t *hm,
   uint32_t ct;
   const uint64_t wex = block_excl_scan<uint64_t>(w0 + w1, &wt);
   const uint32_t cex = block_excl_scan<uint32_t>(c0 + c1, &ct);
+  const uint64_t target = target_of(wt);
   const uint64_t a0 = base + wex, a1 = a0 + w0, a2 = a1 + w1;
   if (a0 < target && target <= a1) res = Crossing{b0, cex, wex};
   if (a1 < target && target <= a2) res = Crossing{b1, cex + c0, wex + w0};
@@ -157,6 +159,12 @@ __device__ Crossing find_crossing(const uint32_t *hc, const uint64_t *hm,
   const Crossing out = res;
   __syncthreads();
   return out;
+}
+
+template <bool BY_MASS>
+__device__ Crossing find_crossing(const uint32_t *hc, const uint64_t *hm,
+                                  int nbins, uint64_t base, uint64_t target) {
+  return find_crossing_of<BY_MASS>(hc, hm, nbins, base, [&](uint64_t) { return target; });
 }
 
 // Where a cluster row's logits come from: the materialised scores, or the
@@ -268,6 +276,60 @@ __device__ void refine(Visit visit, float M, uint64_t target, uint32_t *hc,
   *key_out = prefix;
 }
 
+// The same for a bin of at most kDirect listed logits, entry(k) giving the k-th
+// logit and its weight: thread k sums the weights of the keys above its own and
+// of those equal to it.  Two barriers instead of the digit rounds' two dozen,
+// which were half of a small row's time (256 codes: base and final kernel 17.2
+// and 15.8 us with digit rounds, 10.9 and 9.4 us so; 40 x 128 rows of 32760
+// keys: 380 and 266 us, 306 and 216 us).
+constexpr int kDirect = 128;
+template <bool BY_MASS, typename Entry>
+__device__ void refine_direct(Entry entry, int cnt, float M, uint64_t target, uint32_t *key_out,
+                              uint32_t *cnt_above, uint64_t *mass_above) {
+  __shared__ uint32_t dk[kDirect], dw[kDirect];
+  __shared__ uint64_t de[BY_MASS ? kDirect : 1];
+  __shared__ uint32_t rkey, rcnt;
+  __shared__ uint64_t rmass;
+  const int t = threadIdx.x;
+  uint32_t key = 0;
+  if (t < cnt) {
+    float s;
+    uint32_t wt;
+    entry(t, &s, &wt);
+    key = desc_key(s);
+    dk[t] = key;
+    dw[t] = wt;
+    if constexpr (BY_MASS) de[t] = fixexp(s - M) * wt;
+  }
+  __syncthreads();
+  if (t < cnt) {
+    uint32_t c_lt = 0, c_eq = 0;
+    uint64_t m_lt = 0, m_eq = 0;
+#pragma unroll 4
+    for (int j = 0; j < cnt; ++j) {
+      const uint32_t k = dk[j], c = dw[j];
+      c_lt += k < key ? c : 0u;
+      c_eq += k == key ? c : 0u;
+      if constexpr (BY_MASS) {
+        const uint64_t e = de[j];
+        m_lt += k < key ? e : 0ull;
+        m_eq += k == key ? e : 0ull;
+      }
+    }
+    const uint64_t lo = BY_MASS ? *mass_above + m_lt : static_cast<uint64_t>(*cnt_above) + c_lt;
+    const uint64_t hi = lo + (BY_MASS ? m_eq : static_cast<uint64_t>(c_eq));
+    if (lo < target && target <= hi) {  // threads of equal keys write the same
+      rkey = key;
+      rcnt = c_lt;
+      rmass = m_lt;
+    }
+  }
+  __syncthreads();
+  *key_out = rkey;
+  *cnt_above += rcnt;
+  if (BY_MASS) *mass_above += rmass;
+}
+
 // Gathers the logits of coarse bin `cbin` into cand (one LDS slot per key,
 // reserved per wave); returns how many there are (more than kCand: the
 // list is incomplete and the caller visits all keys instead).
@@ -323,7 +385,12 @@ __device__ void refine_bin(const LogitSource<KIND> &src, float M, int cbin,
                            uint32_t *candw, int *ncand, uint32_t *key_out,
                            uint32_t *cnt_above, uint64_t *mass_above) {
   const int cnt = gather_bin<KIND, CAP>(src, M, cbin, cand, candw, ncand);
-  if (cnt <= CAP) {
+  if (cnt <= kDirect) {
+    refine_direct<BY_MASS>([&](int k, float *s, uint32_t *wt) {
+      *s = cand[k];
+      *wt = candw[k];
+    }, cnt, M, target, key_out, cnt_above, mass_above);
+  } else if (cnt <= CAP) {
     refine<BY_MASS>([&](auto f) {
       for (int k = threadIdx.x; k < cnt; k += kSelBlock) f(cand[k], candw[k]);
     }, M, target, hc, hm, key_out, cnt_above, mass_above);
@@ -373,7 +440,6 @@ __global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_waves_per_eu(8))) 
     __syncthreads();
     // four consecutive entries per thread: a run of them in one bin costs
     // one pair of LDS atomics (integer sums, so the order does not matter)
-    uint64_t tloc = 0;
     for (int j0 = 4 * threadIdx.x; j0 < ne; j0 += 4 * kSelBlock) {
       int cb = -1;
       uint32_t cc = 0;
@@ -394,7 +460,6 @@ __global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_waves_per_eu(8))) 
           const uint32_t wt = wv[i];
           const int bin = coarse_bin(y);
           const uint64_t e = fixexp(y) * wt;
-          tloc += e;
           if (bin != cb) {
             if (cc) atomicAdd(&hc[cb], cc);
             if (cm) atomicAdd(reinterpret_cast<unsigned long long *>(&hm[cb]),
@@ -411,13 +476,14 @@ __global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_waves_per_eu(8))) 
       if (cm) atomicAdd(reinterpret_cast<unsigned long long *>(&hm[cb]),
                         static_cast<unsigned long long>(cm));
     }
-    const uint64_t tot = block_sum<uint64_t>(tloc);
     __syncthreads();
     // the coarse count histogram, for the rank selection of the final kernel
     for (int b = threadIdx.x; b < kCoarseBins; b += kSelBlock)
       coarse_hist[row * kCoarseBins + b] = hc[b];
-    const uint64_t T = mass_target(rho, tot);
-    const Crossing x = find_crossing<true>(hc, hm, kCoarseBins, 0, T);
+    uint64_t T = 0;  // ceil(rho * total mass)
+    const Crossing x = find_crossing_of<true>(hc, hm, kCoarseBins, 0, [&](uint64_t tot) {
+      return T = mass_target(rho, tot);
+    });
     uint32_t cnt_above = x.cnt_before;
     uint64_t mass_above = x.mass_before;
     refine_bin<KIND, true, kCand>(src, M, x.bin, T, hc, hm, cand, candw, &ncand, &key_star,
@@ -573,7 +639,13 @@ __global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_waves_per_eu(8))) 
     const int cnt = ncand;
     uint64_t unused = 0;
     if (cnt <= kMergedCand) {
-      refine<false>([&](auto f) {
+      if (cnt <= kDirect)
+        refine_direct<false>([&](int k2, float *sv, uint32_t *wt) {
+          const uint32_t u = candu[k2];
+          *sv = ulogit(uc[u]);
+          *wt = um[u];
+        }, cnt, M, static_cast<uint64_t>(r), &key_r, &above, &unused);
+      else refine<false>([&](auto f) {
         for (int k2 = threadIdx.x; k2 < cnt; k2 += kSelBlock) {
           const uint32_t u = candu[k2];
           f(ulogit(uc[u]), um[u]);
