@@ -75,47 +75,67 @@ __device__ __host__ __forceinline__ size_t lloyd_lds(int C, int cpad, int dx, in
   return nu + 3 * row + up(4 * static_cast<size_t>(C));
 }
 
+// The rows of one slice as the update takes them: each step kRowsPerStep rows,
+// the lanes of a row holding a pair of channels each.
+template <int DXP, typename T>
+struct SliceRows {
+  static constexpr int kRowsPerStep = 128 / DXP < 64 / (DXP / 2) ? 128 / DXP : 64 / (DXP / 2);
+  static constexpr int kSteps = 32 / kRowsPerStep;
+  static constexpr int kWords = sizeof(T) == 2 ? 1 : 2;  // registers of a pair
+  uint32_t v[kSteps][kWords];
+};
+
+template <int DXP, typename T>
+__device__ __forceinline__ void load_rows(const LloydArgs &A, const LloydSub &K, int h, int sl,
+                                          SliceRows<DXP, T> &R) {
+  using Rows = SliceRows<DXP, T>;
+  const int lane = threadIdx.x & 63, P = pairs_of(K.dx);
+  const int rows = min(32, A.n - 32 * sl);
+  const int rr = lane / P, c2 = lane - rr * P;  // the lane's row of a step and its pair
+  const bool two = 2 * c2 + 1 < K.dx;
+  const T *x0 = static_cast<const T *>(A.X) + h * A.x_hs + static_cast<size_t>(32 * sl) * A.ld + K.col0 + 2 * c2;
+#pragma unroll
+  for (int k = 0; k < Rows::kSteps; ++k) {
+    const T *x = x0 + static_cast<size_t>(min(k * Rows::kRowsPerStep + rr, rows - 1)) * A.ld;
+    if constexpr (sizeof(T) == 2) {  // pairs are 4-byte aligned
+      R.v[k][0] = *reinterpret_cast<const uint32_t *>(x);
+    } else {
+      R.v[k][0] = __float_as_uint(x[0]);
+      R.v[k][1] = two ? __float_as_uint(x[1]) : 0u;
+    }
+  }
+}
+
 // Adds the rows of slice sl (whose centroids the wave's lanes hold in arg) to
 // the sums and counts.
-template <typename T, bool CHECK>
+template <int DXP, typename T, bool CHECK>
 __device__ __forceinline__ void accumulate_slice(const LloydArgs &A, const LloydSub &K, const LloydLds &L,
-                                                 int h, int sl, int arg, int &bad) {
+                                                 int sl, int arg, const SliceRows<DXP, T> &R, int &bad) {
+  using Rows = SliceRows<DXP, T>;
   const int lane = threadIdx.x & 63, P = pairs_of(K.dx);
   const int rows = min(32, A.n - 32 * sl);
   if (lane < rows) atomicAdd(&L.cnts[arg], 1);
-  const int rpw = 64 / P, rr = lane / P, c2 = lane - rr * P;  // rows per step, the lane's row and pair
-  const bool two = 2 * c2 + 1 < K.dx;
-  const T *x0 = static_cast<const T *>(A.X) + h * A.x_hs + static_cast<size_t>(32 * sl) * A.ld + K.col0 + 2 * c2;
-  constexpr int U = 8;
-  for (int r0 = 0; r0 < rows; r0 += U * rpw) {
-    float a[U], b[U];
-    int g[U];
+  const int rr = lane / P, c2 = lane - rr * P;
 #pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const int row = r0 + k * rpw + rr;
-      const int rc = min(row, rows - 1);
-      g[k] = __shfl(arg, rc);
-      const T *x = x0 + static_cast<size_t>(rc) * A.ld;
-      if constexpr (sizeof(T) == 2) {  // pairs are 4-byte aligned
-        const uint32_t v = *reinterpret_cast<const uint32_t *>(x);
-        a[k] = __uint_as_float(v << 16);
-        b[k] = __uint_as_float(v & 0xFFFF0000u);
+  for (int k = 0; k < Rows::kSteps; ++k) {
+    const int row = k * Rows::kRowsPerStep + rr;
+    const int g = __shfl(arg, min(row, 31));
+    if (rr < Rows::kRowsPerStep && row < rows) {
+      float a, b;
+      if constexpr (sizeof(T) == 2) {
+        a = __uint_as_float(R.v[k][0] << 16);
+        b = __uint_as_float(R.v[k][0] & 0xFFFF0000u);
       } else {
-        a[k] = x[0];
-        b[k] = two ? x[1] : 0.0f;
+        a = __uint_as_float(R.v[k][0]);
+        b = __uint_as_float(R.v[k][1]);
       }
-    }
-#pragma unroll
-    for (int k = 0; k < U; ++k) {
-      if (rr < rpw && r0 + k * rpw + rr < rows) {
-        if (CHECK) {
-          check_value(a[k], A.lim, bad);
-          check_value(b[k], A.lim, bad);
-        }
-        unsigned long long *s = L.sums + static_cast<size_t>(g[k]) * 2 * P + c2;
-        atomicAdd(s, fixed24(a[k]));
-        atomicAdd(s + P, fixed24(b[k]));
+      if (CHECK) {
+        check_value(a, A.lim, bad);
+        check_value(b, A.lim, bad);
       }
+      unsigned long long *s = L.sums + static_cast<size_t>(g) * 2 * P + c2;
+      atomicAdd(s, fixed24(a));
+      atomicAdd(s + P, fixed24(b));
     }
   }
 }
@@ -179,6 +199,14 @@ __device__ __forceinline__ void finish_block(const LloydSub &K, const LloydLds &
   __syncthreads();
 }
 
+// fp32 rows are requested before their slice is scored, so that they have
+// arrived when its centroids are known (8 heads x 6417 x 64 centroids, one slice
+// per wave: 34.7 -> 24.6 us).  bf16 rows are not: their registers would leave
+// room for one block per CU instead of two (keys of 5 heads x 32760: 52 us
+// against 45).
+template <typename T, bool ONE>
+constexpr bool kPrefetch = sizeof(T) == 4 && !ONE;
+
 template <int DXP, typename T, bool ONE>
 __device__ __forceinline__ void lloyd_block(const LloydArgs &A, const LloydSub &K, char *lds,
                                             uint32_t *cand, unsigned long long *best, int *ncand,
@@ -212,10 +240,13 @@ __device__ __forceinline__ void lloyd_block(const LloydArgs &A, const LloydSub &
       if (lane == 0) u = atomicAdd(next, 1);
       u = lo + __builtin_amdgcn_readfirstlane(u);
       if (u >= hi) break;
+      SliceRows<DXP, T> R;
+      if (kPrefetch<T, ONE> && update) load_rows<DXP, T>(A, K, h, u, R);
       const int arg = assign_slice<DXP, T>(S, L.Us, L.nus, L.nhs, B, h, u, cand, best, ncand);
       if (update) {
-        if (A.status && it == 0) accumulate_slice<T, true>(A, K, L, h, u, arg, bad);
-        else accumulate_slice<T, false>(A, K, L, h, u, arg, bad);
+        if (!kPrefetch<T, ONE>) load_rows<DXP, T>(A, K, h, u, R);
+        if (A.status && it == 0) accumulate_slice<DXP, T, true>(A, K, L, u, arg, R, bad);
+        else accumulate_slice<DXP, T, false>(A, K, L, u, arg, R, bad);
       }
     }
     if constexpr (ONE) {
@@ -239,16 +270,21 @@ __device__ __forceinline__ void lloyd_block(const LloydArgs &A, const LloydSub &
     __syncthreads();
     const size_t hb = static_cast<size_t>(h) * gridDim.x + b;
     long long *sl = A.slab + hb * A.S + K.ucol;
-    for (int e = t; e < K.C * K.dx; e += kLloydThreads) {
-      const int r = e / K.dx, c = e - r * K.dx;
-      sl[e] = static_cast<long long>(L.sums[static_cast<size_t>(r) * 2 * P + (c & 1) * P + (c >> 1)]);
-    }
+    for (int r = w; r < K.C; r += kLloydWaves)
+      for (int c = lane; c < K.dx; c += 64)
+        sl[static_cast<size_t>(r) * K.dx + c] =
+            static_cast<long long>(L.sums[static_cast<size_t>(r) * 2 * P + (c & 1) * P + (c >> 1)]);
     for (int r = t; r < K.C; r += kLloydThreads) A.cslab[hb * A.SC + K.ccol + r] = L.cnts[r];
   }
 }
 
+// Blocks of eight waves whose registers fit a CU.
 template <typename T, bool ONE>
-__global__ __launch_bounds__(kLloydThreads) void km_lloyd_kernel(const LloydArgs A) {
+constexpr int kPerCu = sizeof(T) == 2 && !ONE ? 2 : 1;
+
+template <typename T, bool ONE>
+__global__ __launch_bounds__(kLloydThreads)
+__attribute__((amdgpu_waves_per_eu(kPerCu<T, ONE> * 2))) void km_lloyd_kernel(const LloydArgs A) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   __shared__ uint32_t cand[kLloydWaves][kWaveCand];
   __shared__ unsigned long long best[kLloydWaves][32];
@@ -285,9 +321,15 @@ int km_lloyd_blocks(const KmProblem *p, int nsub, const AccPlan &plan) {
   const size_t row_bytes = static_cast<size_t>(p[0].ld) * (p[0].bf16 ? 2 : 4);
   if (row_bytes * p[0].n * p[0].heads > kLloydBytes) return 0;
   if (slices <= kLloydOneBlock) return 1;
-  // about one block per CU, each wave with a slice, and no more slabs than the
-  // workspace has
-  int blocks = kAccTargetBlocks / (p[0].heads * nsub);
+  // as many blocks as the CUs hold, each wave with a slice, and no more slabs
+  // than the workspace has
+  size_t lds = 0;
+  for (int m = 0; m < nsub; ++m) {
+    const size_t need = lloyd_lds(p[m].C, p[m].cpad, p[m].dx, p[m].dxp, nullptr, nullptr);
+    lds = need > lds ? need : lds;
+  }
+  const int per_cu = p[0].bf16 && 2 * lds <= kLloydLds ? kPerCu<uint16_t, false> : 1;
+  int blocks = per_cu * kAccTargetBlocks / (p[0].heads * nsub);
   const int most = (slices + kLloydWaves - 1) / kLloydWaves;
   if (blocks > most) blocks = most;
   if (blocks > plan.blocks) blocks = plan.blocks;
