@@ -990,15 +990,16 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
 // within a bucket, bucket w (largest first) takes partners from bucket
 // min(8 - w, w) down to 1 in key-count order, so paired chunks run similar
 // numbers of key tiles.  Remainders left without a partner (among them every
-// remainder of 8 waves) run alone.  Up to kSortMaxSlots slots per head, the
-// head's slots are then reordered by estimated cost, largest first (ties
+// remainder of 8 waves) run alone.  With `sort` (where attn_plan_kernel does
+// not order them) and up to kSortMaxSlots slots per head, the head's slots are
+// then reordered by estimated cost, largest first (ties
 // keep their order, so a cluster's full chunks stay adjacent): the
 // expensive blocks of each head start early and the cheap ones fill in
 // behind them, which shortens the launch's tail.
 constexpr int kPairMaxClusters = 2048;  // pairing up to this many clusters
 constexpr int kSortMaxSlots = 2048;     // cost-ordered work lists up to this many slots
 __global__ __launch_bounds__(1024) void attn_items_kernel(
-    int n, int c_q, int items_per_head, int pair, const int32_t *__restrict__ offsets,
+    int n, int c_q, int items_per_head, int pair, int sort, const int32_t *__restrict__ offsets,
     const int32_t *__restrict__ sel_counts, int4 *items) {
   __shared__ int wtot[16];
   __shared__ int rem_w[kPairMaxClusters], rem_r[kPairMaxClusters], ord[kPairMaxClusters];
@@ -1012,7 +1013,7 @@ __global__ __launch_bounds__(1024) void attn_items_kernel(
   const int32_t *scnt = sel_counts + static_cast<size_t>(h) * c_q;
   int4 *out = items + static_cast<size_t>(h) * items_per_head * 2;
   const bool do_pair = pair && c_q <= kPairMaxClusters;
-  const bool sorted = items_per_head <= kSortMaxSlots;
+  const bool sorted = sort && items_per_head <= kSortMaxSlots;
   auto count_of = [&](int c) { return min(max(off[c + 1] - off[c], 0), n); };
   auto keys_of = [&](int c) { return min(max(scnt[c], 0), n); };
   auto put = [&](int slot, int4 a, int4 b) {
@@ -1287,7 +1288,7 @@ int attn_items_per_head(int n, int c_q) { return (n + kBM - 1) / kBM + c_q; }
 hipError_t attention_items(int heads, int n, int c_q, bool pair, const int32_t *offsets,
                            const int32_t *sel_counts, int4 *items, hipStream_t s) {
   hipLaunchKernelGGL(attn_items_kernel, dim3(heads), dim3(1024), 0, s, n, c_q,
-                     attn_items_per_head(n, c_q), pair ? 1 : 0, offsets, sel_counts, items);
+                     attn_items_per_head(n, c_q), pair ? 1 : 0, 1, offsets, sel_counts, items);
   return hipGetLastError();
 }
 
@@ -1338,7 +1339,7 @@ hipError_t attention_run(int heads, int n, int d, bool bf16, const void *q,
   // remainder chunks share blocks only in the LDS-DMA kernel
   const int pair = bf16 || w.kv16 ? 1 : 0;
   hipLaunchKernelGGL(attn_items_kernel, dim3(heads), dim3(1024), 0, s, n, c_q,
-                     iph, pair, offsets, sel_counts, w.items);
+                     iph, pair, w.order ? 0 : 1, offsets, sel_counts, w.items);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const float sl2 = scale * 1.4426950408889634f;

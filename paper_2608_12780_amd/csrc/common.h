@@ -75,10 +75,17 @@ __device__ __forceinline__ unsigned long long fixed24(float x) {
 
 // The int64 sums stay exact while n terms of magnitude below 2^(e+24) cannot
 // reach 2^63: |x| < lim = 2^e with e = min(22, 39 - ceil(log2 n)).  Larger or
-// non-finite inputs are flagged.
-__device__ __forceinline__ void check_value(float x, float lim, int &bad) {
-  if (!(fabsf(x) < lim))
-    bad |= isfinite(x) ? kStatusRange : (kStatusRange | kStatusNonFinite);
+// non-finite inputs are flagged: the encodings of |x| order like the values,
+// with inf and NaN above all others, so their maximum decides (two instructions
+// per value; classified one by one they took the checking pass of 40 heads x
+// 75600 rows from 164 to 228 us, so to 200 us).
+__device__ __forceinline__ void check_value(float x, uint32_t &most) {
+  const uint32_t a = __float_as_uint(x) & 0x7FFFFFFFu;
+  most = a > most ? a : most;
+}
+__device__ __forceinline__ int status_of(uint32_t most, float lim) {
+  return most >= 0x7F800000u ? (kStatusRange | kStatusNonFinite)
+                             : most >= __float_as_uint(lim) ? kStatusRange : 0;
 }
 
 // ---------------------------------------------------------------------------

@@ -110,7 +110,7 @@ __device__ __forceinline__ void load_rows(const LloydArgs &A, const LloydSub &K,
 // the sums and counts.
 template <int DXP, typename T, bool CHECK>
 __device__ __forceinline__ void accumulate_slice(const LloydArgs &A, const LloydSub &K, const LloydLds &L,
-                                                 int sl, int arg, const SliceRows<DXP, T> &R, int &bad) {
+                                                 int sl, int arg, const SliceRows<DXP, T> &R, uint32_t &most) {
   using Rows = SliceRows<DXP, T>;
   const int lane = threadIdx.x & 63, P = pairs_of(K.dx);
   const int rows = min(32, A.n - 32 * sl);
@@ -130,8 +130,8 @@ __device__ __forceinline__ void accumulate_slice(const LloydArgs &A, const Lloyd
         b = __uint_as_float(R.v[k][1]);
       }
       if (CHECK) {
-        check_value(a, A.lim, bad);
-        check_value(b, A.lim, bad);
+        check_value(a, most);
+        check_value(b, most);
       }
       unsigned long long *s = L.sums + static_cast<size_t>(g) * 2 * P + c2;
       atomicAdd(s, fixed24(a));
@@ -227,7 +227,7 @@ __device__ __forceinline__ void lloyd_block(const LloydArgs &A, const LloydSub &
   const int lo = static_cast<int>(static_cast<long long>(nslices) * b / gridDim.x);
   const int hi = static_cast<int>(static_cast<long long>(nslices) * (b + 1) / gridDim.x);
   const int rounds = ONE ? A.iters + A.final_assign : 1;
-  int bad = 0;
+  uint32_t most = 0;  // largest |x| seen, as bits
   if constexpr (ONE) {
     for (int r = t; r < K.C; r += kLloydThreads) L.bnd[r] = K.bnd[static_cast<size_t>(h) * K.cpad + r];
   }
@@ -245,8 +245,8 @@ __device__ __forceinline__ void lloyd_block(const LloydArgs &A, const LloydSub &
       const int arg = assign_slice<DXP, T>(S, L.Us, L.nus, L.nhs, B, h, u, cand, best, ncand);
       if (update) {
         if (!kPrefetch<T, ONE>) load_rows<DXP, T>(A, K, h, u, R);
-        if (A.status && it == 0) accumulate_slice<DXP, T, true>(A, K, L, u, arg, R, bad);
-        else accumulate_slice<DXP, T, false>(A, K, L, u, arg, R, bad);
+        if (A.status && it == 0) accumulate_slice<DXP, T, true>(A, K, L, u, arg, R, most);
+        else accumulate_slice<DXP, T, false>(A, K, L, u, arg, R, most);
       }
     }
     if constexpr (ONE) {
@@ -265,7 +265,10 @@ __device__ __forceinline__ void lloyd_block(const LloydArgs &A, const LloydSub &
       __syncthreads();
     }
   }
-  if (A.status && bad) atomicOr(A.status, bad);
+  if (A.status) {
+    const int bad = status_of(most, A.lim);
+    if (bad) atomicOr(A.status, bad);
+  }
   if constexpr (!ONE) {
     __syncthreads();
     const size_t hb = static_cast<size_t>(h) * gridDim.x + b;

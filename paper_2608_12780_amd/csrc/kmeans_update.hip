@@ -102,7 +102,7 @@ __global__ __launch_bounds__(kAccThreads) void km_accum_kernel(
   const int e_stride = VEC ? p_width / CPL : 1;
   const int lds_base = active ? W.piece[p].lds + (VEC ? j / CPL : j) : kAccLds;
   const int lds_stride = active ? p_width : 0;
-  int bad = 0;
+  uint32_t most = 0;  // largest |x| seen, as bits
 
   const int lo = static_cast<int>((static_cast<long long>(n) * b) / gridDim.x);
   const int hi = static_cast<int>((static_cast<long long>(n) * (b + 1)) / gridDim.x);
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(kAccThreads) void km_accum_kernel(
 #pragma unroll
       for (int e = 0; e < CPL; ++e) {
         const float x = ok ? xv[u][e] : 0.0f;
-        if (CHECK && e < nvalid) check_value(x, lim, bad);
+        if (CHECK && e < nvalid) check_value(x, most);
         if (VEC || e < nvalid) atomicAdd(&sums[idx + (active ? e * e_stride : e)], fixed24(x));
       }
       if (counter) atomicAdd(&cnts[p_cnt + a], ok ? 1 : 0);
@@ -137,7 +137,10 @@ __global__ __launch_bounds__(kAccThreads) void km_accum_kernel(
   int g = lo + wv * rpw + rr;
   for (; (g - rr) + (U - 1) * step + rpw - 1 < hi; g += U * step) group(g, true);
   if (g - rr < hi) group(g, false);
-  if (CHECK && status && bad) atomicOr(status, bad);
+  if (CHECK && status) {
+    const int bad = status_of(most, lim);
+    if (bad) atomicOr(status, bad);
+  }
   __syncthreads();
 
   // this block's sums into its slab, in the centroids' layout

@@ -60,3 +60,22 @@ def test_selection_from_codes_equals_selection_from_scores(heads, n, distinct):
     torch.cuda.synchronize()
     for key in got[0]:
         assert torch.equal(got[0][key], got[1][key]), key
+
+
+@pytest.mark.parametrize("cnt", [1, 2, 127, 128, 129, 130])
+@pytest.mark.parametrize("ties", [False, True])
+def test_crossing_lists_around_the_direct_limit(cnt, ties):
+    """All logits within one coarse bin (1/64): the crossing list holds `cnt`
+    distinct codes, resolved directly up to 128 of them; with `ties` several
+    codes share a logit.  Both crossings (Top-p and rank) against the oracle."""
+    G.say(f"[codes] crossing list of {cnt}, ties={ties}")
+    rng = np.random.default_rng(cnt + 1000 * ties)
+    c_q, d, n = 3, 64, 3 * cnt + 5
+    step = np.arange(cnt) // 3 if ties else np.arange(cnt)
+    tables = np.zeros((1, c_q, cnt + 2), np.float32)
+    for c in range(c_q):
+        tables[0, c, :cnt] = rng.permutation(step).astype(np.float32) * 2.0 ** -11
+    codes = np.concatenate([np.arange(cnt), rng.integers(0, cnt, n - cnt)])[rng.permutation(n)]
+    counts = rng.integers(1, 50, (1, c_q)).astype(np.int32)
+    for rho, k_fix in ((0.5, 1), (0.05, max(1, n // 3)), (0.9, n - 1)):
+        G.select_from_codes(tables, codes[None].astype(np.uint32), counts, d, (cnt, 1, 1), rho, k_fix)
