@@ -213,7 +213,7 @@ def trace_summary(trace_csv, cmd, bench_line=None, config_name="hy720"):
         return agg
 
     def model(name, grid):
-        m = re.match(r"km_assign_mfma_kernel<(\d+)>", name)
+        m = re.match(r"km_assign_mfma_kernel<(\d+)[,>]", name)
         if m:
             dx = dx_of.get(int(m.group(1)))
             return None if dx is None else ("B", H * N * (dx * e + 4))

@@ -745,7 +745,7 @@ __global__ __launch_bounds__(kBM *kMergeGroups) void attn_merge_kernel(
   float m = -INFINITY, l = 0.0f;
   for (int i = 0; i < split; ++i) {
     const float2 ml = *reinterpret_cast<const float2 *>(p0 + i * step + D * kBM + 2 * slot);
-    if (ml.y > 0.0f) {
+    if (ml.y != 0.0f) {  // not an empty piece (NaN stays NaN)
       const float mn = fmaxf(m, ml.x);
       l = l * __builtin_amdgcn_exp2f(m - mn) + ml.y * __builtin_amdgcn_exp2f(ml.x - mn);
       m = mn;
@@ -757,7 +757,7 @@ __global__ __launch_bounds__(kBM *kMergeGroups) void attn_merge_kernel(
   for (int k = 0; k < D / 4 / kMergeGroups; ++k) o[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   for (int i = 0; i < split; ++i) {
     const float2 ml = *reinterpret_cast<const float2 *>(p0 + i * step + D * kBM + 2 * slot);
-    const float w = ml.y > 0.0f ? __builtin_amdgcn_exp2f(ml.x - m) : 0.0f;
+    const float w = ml.y != 0.0f ? __builtin_amdgcn_exp2f(ml.x - m) : 0.0f;
     const float4 *po = reinterpret_cast<const float4 *>(p0 + i * step) + slot;
 #pragma unroll
     for (int k = 0; k < D / 4 / kMergeGroups; ++k) {
