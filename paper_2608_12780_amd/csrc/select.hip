@@ -6,7 +6,8 @@
 //   of 2^-32; total and the exact target T = ceil(rho * total);
 //   radix selection of the logit where the descending cumulative mass first
 //   reaches T: one coarse pass over a monotone binning of M - s, one pass
-//   that gathers the logits of the crossing bin into LDS, then three digit
+//   that gathers the logits of the crossing bin into LDS, then either each
+//   listed logit's weights above it (up to 128 of them) or three digit
 //   rounds (11/11/10 bits) of the order-preserving key bits over that list
 //   (over all keys again if the bin overflows the list); keys that tie at
 //   the crossing logit all carry the same mass E*, so the Top-p count is
