@@ -277,7 +277,10 @@ int32_t scope_proxy_scores_partition(const scope_shape *shape,
 
 /* Selection (call 4b) with the logits of `part`: from `scores` if not
  * NULL, else from (tables, codes) exactly as scope_proxy_scores_partition
- * computes them.  Arguments, outputs and errors otherwise as call 4b.      */
+ * computes them.  Arguments, outputs and errors otherwise as call 4b.  With
+ * heads * n words more workspace than that call needs, which
+ * scope_partition_workspace_size covers, codes of up to three subspaces are
+ * packed first (the same results, faster).                                 */
 int32_t scope_select_partition(const scope_shape *shape, int32_t c_q,
                                const scope_partition *part,
                                const float *scores, const float *tables,

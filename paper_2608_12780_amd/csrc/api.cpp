@@ -192,6 +192,17 @@ size_t select_ws(const scope_shape *s, int c_q, void *base, SelectWs *w) {
   return cv.used;
 }
 
+// The selection from code planes also packs the codes where they fit a word
+// and the workspace has the room (scope_partition_workspace_size covers it).
+size_t part_select_ws(const scope_shape *s, int c_q, int M, void *base, uint32_t **pack) {
+  Carver cv(base);
+  cv.take<char>(select_ws(s, c_q, nullptr, nullptr));
+  uint32_t *p = nullptr;
+  if (scope::planes_as_packed(s->n, M)) p = cv.take<uint32_t>(static_cast<size_t>(s->heads) * s->n);
+  if (pack) *pack = p;
+  return cv.used;
+}
+
 // The work list is all that the call cannot do without; a workspace that also
 // holds the rest (scope_workspace_size covers it) lets it copy fp32 K and V to
 // bf16 and split slots.  *list: the bytes of the list alone.
@@ -639,8 +650,8 @@ int32_t scope_select_policy(const scope_shape *shape, int32_t c_q,
                               shape->d, scores, tables, codes, nullptr, counts,
                               rho, k_fix,
                               base_counts, topp_counts, k_head, sel_counts,
-                              sel_idx, w.row_max, w.row_state, w.coarse_hist, w.dedup, policy,
-                              static_cast<hipStream_t>(stream)));
+                              sel_idx, w.row_max, w.row_state, w.coarse_hist, w.dedup, nullptr,
+                              policy, static_cast<hipStream_t>(stream)));
   return SCOPE_OK;
 }
 
@@ -670,7 +681,7 @@ int32_t scope_partition_workspace_size(const scope_shape *shape, int32_t c_q,
   size_t need = query_ws(shape, c_q, nullptr, nullptr);
   for (size_t x : {part_key_ws(shape, part, nullptr, nullptr),
                    part_table_ws(shape, c_q, nullptr, nullptr),
-                   select_ws(shape, c_q, nullptr, nullptr),
+                   part_select_ws(shape, c_q, part->m, nullptr, nullptr),
                    attn_ws(shape, c_q, nullptr, 0, nullptr, nullptr)})
     if (x > need) need = x;
   *bytes = need;
@@ -824,10 +835,13 @@ int32_t scope_select_partition(const scope_shape *shape, int32_t c_q,
   if ((st = check_ws(workspace, ws_bytes, need))) return st;
   SelectWs w;
   select_ws(shape, c_q, workspace, &w);
+  uint32_t *pack = nullptr;
+  if (ws_bytes >= part_select_ws(shape, c_q, part->m, nullptr, nullptr))
+    part_select_ws(shape, c_q, part->m, workspace, &pack);
   SCOPE_TRY(scope::select_run(shape->heads, shape->n, c_q, part_subspaces(part_geom(part)),
                               shape->d, scores, tables, nullptr, codes, counts, rho,
                               k_fix, base_counts, topp_counts, k_head, sel_counts,
-                              sel_idx, w.row_max, w.row_state, w.coarse_hist, w.dedup, policy,
+                              sel_idx, w.row_max, w.row_state, w.coarse_hist, w.dedup, pack, policy,
                               static_cast<hipStream_t>(stream)));
   return SCOPE_OK;
 }

@@ -189,7 +189,9 @@ hipError_t select_run(int heads, int n, int c_q, const Subspaces &sub, int d,
                       int k_fix, int32_t *base, int32_t *topp, int32_t *k_head,
                       int32_t *sel_counts, int32_t *sel_idx, float *row_max,
                       uint32_t *row_state, uint32_t *coarse_hist, uint32_t *dedup,
-                      int policy, hipStream_t s);
+                      uint32_t *pack, int policy, hipStream_t s);
+// whether select_run packs code planes given room for [heads][n] words in `pack`
+bool planes_as_packed(int n, int M);
 // 32-bit words of the distinct-code scratch of select_run
 size_t select_dedup_words(int heads, int n);
 constexpr int kSelCoarseBins = 2048;  // coarse histogram bins per cluster row

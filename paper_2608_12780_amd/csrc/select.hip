@@ -182,6 +182,7 @@ struct CodeBooks {
   const uint32_t *uidx;    // [heads][upitch]: each key's distinct code, or null
   int upitch;              // n rounded up to a multiple of 4
   CodePlanes cp;           // M and the table columns of each subspace
+  int row;                 // floats of a table row; columns beyond it hold -0
 };
 
 // Entry j of a row: its logit and how many keys it stands for (1 except
@@ -227,8 +228,8 @@ __device__ LogitSource<KIND> make_source(float *lut, int h, int c, int n, int c_
   src.planes = cb.planes ? cb.planes + static_cast<size_t>(h) * cb.cp.M * n : nullptr;
   if (KIND != kFromScores) {
     const int cs = cb.cp.col[cb.cp.M];
-    const float *row = tables + (static_cast<size_t>(h) * c_q + c) * cs;
-    for (int e = threadIdx.x; e < cs; e += kSelBlock) lut[e] = row[e];
+    const float *row = tables + (static_cast<size_t>(h) * c_q + c) * cb.row;
+    for (int e = threadIdx.x; e < cs; e += kSelBlock) lut[e] = e < cb.row ? row[e] : -0.0f;
     __syncthreads();
     src.P = lut;
   } else {
@@ -1024,6 +1025,23 @@ __global__ __launch_bounds__(kSelBlock) void code_parts_gather_kernel(
   if (g == 0 && threadIdx.x == 0) ucount[h] = pbase[parts] < n ? pbase[parts] : n;
 }
 
+// Code planes of up to three subspaces as packed codes, each field clamped to
+// its codebook as the plane's code would be.
+__global__ void pack_planes_kernel(const uint16_t *__restrict__ planes, int n, CodePlanes cp,
+                                   uint32_t *__restrict__ packed) {
+  const int j = blockIdx.x * blockDim.x + threadIdx.x, h = blockIdx.y;
+  if (j >= n) return;
+  const uint16_t *p = planes + static_cast<size_t>(h) * cp.M * n + j;
+  uint32_t code = 0;
+#pragma unroll
+  for (int m = 0; m < 3; ++m)
+    if (m < cp.M) {
+      const int z = min(static_cast<int>(p[static_cast<size_t>(m) * n]), cp.col[m + 1] - cp.col[m] - 1);
+      code |= static_cast<uint32_t>(z) << (10 * m);
+    }
+  packed[static_cast<size_t>(h) * n + j] = code;
+}
+
 __global__ void fixexp_kernel(const float *y, uint64_t *out, int64_t count) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i < count) out[i] = fixexp(y[i]);
@@ -1067,22 +1085,47 @@ size_t select_dedup_words(int heads, int n) {
          (key_pitch(n) + 3 * parts * cp.slots + parts + 2 * static_cast<size_t>(n) + 2);
 }
 
+// Whether code planes are packed first, so that the distinct codes take the
+// place of the keys.  Up to three subspaces fit a word (codebooks have at most
+// 1024 centroids); where the build of the distinct codes applies, packing is
+// the better side at every size measured: 5 heads x 32760 keys x 300 clusters
+// of 3 x 333 centroids 511 -> 168 us, one subspace 336 -> 117 us, 1 x 118800 x 4
+// clusters 387 -> 125 us, 24 x 1024 x 8 46.8 -> 38.5 us, 1 x 512 x 8 40.8 ->
+// 34.7 us (key by key, every entry reads a plane per subspace and is weighed by
+// itself); with every key's code its own 5 x 32760 x 300 still 502 -> 353 us and
+// 1 x 200000 x 300 962 -> 796 us.
+bool planes_as_packed(int n, int M) { return M <= 3 && use_distinct_codes(n); }
+
 hipError_t select_run(int heads, int n, int c_q, const Subspaces &sub, int d,
                       const float *scores, const float *tables,
                       const uint32_t *codes32, const uint16_t *codes16,
                       const int32_t *counts, float rho, int k_fix, int32_t *base,
                       int32_t *topp, int32_t *k_head, int32_t *sel_counts,
                       int32_t *sel_idx, float *row_max, uint32_t *row_state,
-                      uint32_t *coarse_hist, uint32_t *dedup, int policy, hipStream_t s) {
+                      uint32_t *coarse_hist, uint32_t *dedup, uint32_t *pack, int policy,
+                      hipStream_t s) {
   CodeBooks cb{};
   cb.packed = codes32;
   cb.planes = codes16;
   cb.cp.M = sub.M;
   for (int m = 0; m < sub.M; ++m) cb.cp.col[m + 1] = cb.cp.col[m] + sub.c[m];
-  const int kind = scores ? kFromScores : codes16 ? kFromPlanes : kFromPacked;
+  cb.row = cb.cp.col[sub.M];
+  int kind = scores ? kFromScores : codes16 ? kFromPlanes : kFromPacked;
   const float sigma = static_cast<float>(1.0 / sqrt(static_cast<double>(d)));
   const dim3 grid(c_q, heads), block(kSelBlock);
   hipError_t e = hipSuccess;
+  if (kind == kFromPlanes && pack && planes_as_packed(n, sub.M)) {
+    hipLaunchKernelGGL(pack_planes_kernel, dim3((n + 255) / 256, heads), dim3(256), 0, s,
+                       codes16, n, cb.cp, pack);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    kind = kFromPacked;
+    codes32 = cb.packed = pack;
+    cb.planes = nullptr;
+    // a missing subspace reads one column of -0, which changes no sum
+    for (int m = sub.M; m < 3; ++m) cb.cp.col[m + 1] = cb.cp.col[m] + 1;
+    cb.cp.M = 3;
+  }
   const bool distinct = kind == kFromPacked && use_distinct_codes(n);
   if (distinct) {
     // the head's distinct codes, their multiplicities and each key's index
