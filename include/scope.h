@@ -302,15 +302,13 @@ int32_t scope_select_partition(const scope_shape *shape, int32_t c_q,
  * queries (c_q = 1, offsets = {0, n}, perm = identity) and all keys.
  * Bad indices cannot fault: index arrays are clamped to their valid
  * ranges on the device, or read through range-checked loads that return
- * 0 (the selected-key gather of bf16 inputs).  Requires d in {64, 128},
- * 16-byte aligned q, k, v, o, and for bf16 inputs n * d * 2 < 2^32
- * (n < 2^24 at d = 128), else SCOPE_ERR_UNSUPPORTED.
+ * 0 (the selected-key gather from bf16 K and V, copies among them).
+ * Requires d in {64, 128}, 16-byte aligned q, k, v, o, and for bf16 inputs
+ * n * d * 2 < 2^32 (n < 2^24 at d = 128), else SCOPE_ERR_UNSUPPORTED.
  * The call needs workspace for its work list only: heads * (ceil(n / 256) +
  * c_q) slots of 32 bytes, rounded up to 256.  With scope_workspace_size bytes
- * it also keeps bf16 copies of fp32 K and V and, where the work slots are few
- * and their key lists long, splits key lists over several blocks and joins
- * the parts: the same sums in another order, so results with and without that
- * room may differ in rounding.                                            */
+ * it also keeps bf16 copies of fp32 K and V and a block order, and is faster;
+ * the results are the same bit for bit.                                    */
 int32_t scope_sparse_attention(const scope_shape *shape, const void *q,
                                const void *k, const void *v, int32_t c_q,
                                const int32_t *offsets, const int32_t *perm,
@@ -321,8 +319,7 @@ int32_t scope_sparse_attention(const scope_shape *shape, const void *q,
 /* 5n. Sparse attention without allocation or workspace, for callers that
  * cannot allocate device memory (code under HIP graph capture, serving loops
  * and harnesses that forbid it).  Arguments, outputs, layout and errors as
- * call 5 without `workspace`/`ws_bytes` (and with the results of a call 5
- * that has room for its work list only): the call's work list (heads *
+ * call 5 without `workspace`/`ws_bytes`: the call's work list (heads *
  * (ceil(n / 256) + c_q) slots of two 16-byte entries) lives in a fixed
  * device array of SCOPE_NOALLOC_MAX_WORK_ITEMS entries (1 MiB), one per GPU, held until
  * the process ends; larger problems return SCOPE_ERR_SCRATCH_LIMIT before
@@ -367,8 +364,10 @@ int32_t scope_debug_fixexp(const float *y, uint64_t *out, int64_t count,
  * rows, selected keys) run by one block, the second with rows = 0 when the
  * block runs one chunk, and slots with both entries empty after the used
  * ones.  pair != 0 lets two remainder chunks share a slot, as every kernel
- * but the one for fp32 inputs without room for bf16 copies does.  Returns SCOPE_ERR_INVALID_ARGUMENT on bad sizes or
- * pointers, before any launch.                                              */
+ * but the one for fp32 inputs without room for bf16 copies does.  The list
+ * is in cost order, as for a call without a block order of its own.
+ * Returns SCOPE_ERR_INVALID_ARGUMENT on bad sizes or pointers, before any
+ * launch.                                                                   */
 int32_t scope_debug_attention_items(int32_t heads, int32_t n, int32_t c_q,
                                     int32_t pair, const int32_t *offsets,
                                     const int32_t *sel_counts, int32_t *items,

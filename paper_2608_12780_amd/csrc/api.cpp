@@ -204,8 +204,8 @@ size_t part_select_ws(const scope_shape *s, int c_q, int M, void *base, uint32_t
 }
 
 // The work list is all that the call cannot do without; a workspace that also
-// holds the rest (scope_workspace_size covers it) lets it copy fp32 K and V to
-// bf16 and split slots.  *list: the bytes of the list alone.
+// holds bf16 copies of fp32 K and V, and the block order (scope_workspace_size
+// covers both), makes it faster.  *list: the bytes of the list alone.
 size_t attn_ws(const scope_shape *s, int c_q, void *base, size_t bytes, size_t *list,
                scope::AttnScratch *w) {
   Carver cv(base);
@@ -214,18 +214,15 @@ size_t attn_ws(const scope_shape *s, int c_q, void *base, size_t bytes, size_t *
   a.items = cv.take<int4>(2 * H * scope::attn_items_per_head(s->n, c_q));
   if (list) *list = cv.used;
   const bool bf16 = s->dtype == SCOPE_BF16;
-  const bool copies = scope::attention_copies_kv(s->n, s->d, bf16);
-  if (copies) a.kv16 = cv.take<uint16_t>(2 * H * s->n * s->d);
-  // the register-staged fp32 kernel has neither order nor pieces
-  if ((bf16 || copies) && scope::attention_ordered(s->heads, s->n, s->d, c_q)) {
-    a.pieces = scope::attention_pieces(s->heads, s->n, s->d, c_q);
-    a.order = cv.take<int4>(scope::attention_order_entries(s->heads, s->n, c_q, a.pieces));
-    a.part = cv.take<float>(a.pieces * scope::attention_piece_floats(s->d));
+  bool dma = bf16;  // the register-staged fp32 kernel has no order
+  if (scope::attention_copies_kv(s->n, s->d, bf16)) {
+    uint16_t *kv16 = cv.take<uint16_t>(2 * H * s->n * s->d);
+    dma = cv.used <= bytes;
+    if (dma) a.kv16 = kv16;
   }
-  if (bytes < cv.used) {
-    a.kv16 = nullptr;
-    a.order = nullptr;
-    a.pieces = 0;
+  if (dma && scope::attention_ordered(s->heads, s->n, s->d, c_q)) {
+    int2 *order = cv.take<int2>(scope::attention_order_entries(s->heads, s->n, s->d, c_q));
+    if (cv.used <= bytes) a.order = order;
   }
   if (w) *w = a;
   return cv.used;
@@ -382,7 +379,7 @@ int32_t scope_workspace_size(const scope_shape *shape, int32_t c_q,
   size_t need = query_ws(shape, c_q, nullptr, nullptr);
   size_t k = key_ws(shape, c_m, nullptr, nullptr);
   size_t s = select_ws(shape, c_q, nullptr, nullptr);
-  size_t a = attn_ws(shape, c_q, nullptr, 0, nullptr, nullptr);
+  size_t a = attn_ws(shape, c_q, nullptr, SIZE_MAX, nullptr, nullptr);
   if (k > need) need = k;
   if (s > need) need = s;
   if (a > need) need = a;
@@ -682,7 +679,7 @@ int32_t scope_partition_workspace_size(const scope_shape *shape, int32_t c_q,
   for (size_t x : {part_key_ws(shape, part, nullptr, nullptr),
                    part_table_ws(shape, c_q, nullptr, nullptr),
                    part_select_ws(shape, c_q, part->m, nullptr, nullptr),
-                   attn_ws(shape, c_q, nullptr, 0, nullptr, nullptr)})
+                   attn_ws(shape, c_q, nullptr, SIZE_MAX, nullptr, nullptr)})
     if (x > need) need = x;
   *bytes = need;
   return SCOPE_OK;
@@ -894,7 +891,7 @@ int32_t scope_sparse_attention_noalloc(const scope_shape *shape, const void *q,
   const size_t entries = 2 * static_cast<size_t>(shape->heads) *
                          scope::attn_items_per_head(shape->n, c_q);
   if (entries > scope::kAttnScratchItems) return SCOPE_ERR_SCRATCH_LIMIT;
-  scope::AttnScratch w{};  // the list alone: no split slots, no copies
+  scope::AttnScratch w{};  // the list alone
   SCOPE_TRY(scope::attention_scratch(&w.items));
   SCOPE_TRY(scope::attention_run(shape->heads, shape->n, shape->d,
                                  shape->dtype == SCOPE_BF16, q, k, v, o, c_q,

@@ -352,25 +352,27 @@ __global__ __launch_bounds__(kNW * 64) void attn_kernel(
   }
 }
 
-// Split slots: a slot's keys cut into `split` pieces, each run by a block of its
-// own, joined by attn_merge_kernel.  A slot of fewer than kSplitTiles tiles
-// stays whole (small calls keep bit for bit the result of the call without
-// workspace), and a piece has at least kPieceTiles.
-constexpr int kSplitTiles = 64, kPieceTiles = 8;
-template <int D>
-constexpr int kPieceFloats = kBM * (D + 2);
 __device__ __forceinline__ int key_tiles(const int4 &e) { return e.z > 0 ? (e.w + kBN - 1) / kBN : 0; }
-__device__ __forceinline__ int slot_split(const int4 &ia, const int4 &ib, int want) {
-  const int nt = max(key_tiles(ia), key_tiles(ib));
-  return nt < kSplitTiles ? 1 : min(want, nt / kPieceTiles);
-}
-// Cuts the entry to piece i of `split`; returns its first key.
-__device__ __forceinline__ int key_range(int4 *e, int i, int split) {
-  const int nt = key_tiles(*e);
-  const int t0 = nt * i / split, t1 = nt * (i + 1) / split;
-  const int k0 = t0 * kBN;
-  e->w = max(min(e->w - k0, (t1 - t0) * kBN), 0);
-  return k0;
+
+// Half a slot: the queries of its waves 0 .. kNW/2 - 1 (half 1) or of the others
+// (half 2).  A query's result depends neither on its wave nor on its block, so
+// halves give the slot's results bit for bit.
+__device__ __forceinline__ void take_half(int4 *a, int4 *b, int half) {
+  const int first = half == 2 ? kNW / 2 : 0;
+  // the rows of an entry, whose first wave is w0, that the half's waves hold
+  auto cut = [&](int4 *e, int w0) {
+    const int from = min(max(32 * (first - w0), 0), e->z);
+    const int to = min(max(32 * (first + kNW / 2 - w0), 0), e->z);
+    e->y += from;
+    e->z = to - from;
+  };
+  const int wa = (a->z + 31) >> 5;
+  cut(a, 0);
+  cut(b, wa);
+  if (a->z <= 0) {
+    *a = *b;
+    b->z = 0;
+  }
 }
 
 // The same computation with bf16 K/V rows gathered straight into LDS by the
@@ -390,14 +392,9 @@ __device__ __forceinline__ int key_range(int4 *e, int i, int split) {
 template <int D>
 using DmaTile = uint16_t[2][kBN * D];
 
-//
-// ia, ib: the slot's entries with r the keys of this block, which start at
-// key ka, kb of the clusters' lists.  part: null, or the piece's place for its
-// unnormalised results: O as [D / 4][kBM] float4 over the block's query slots
-// (32 w + lane), then [kBM] (running max, row sum).
 template <int D, bool BF16IO, bool PAIRED>
 __device__ __forceinline__ void attn_dma_body(
-    int n, int c_q, int h, int4 ia, int4 ib, int ka, int kb, float *part,
+    int n, int c_q, int h, const int4 &ia, const int4 &ib,
     const void *__restrict__ qv,
     const void *__restrict__ kv, const void *__restrict__ vv, void *ov,
     const int32_t *__restrict__ offsets, const int32_t *__restrict__ perm,
@@ -445,13 +442,13 @@ __device__ __forceinline__ void attn_dma_body(
   const int ntA = (ia.w + kBN - 1) / kBN, ntB = PAIRED ? (ib.w + kBN - 1) / kBN : 0;
   const int ntiles = ntA > ntB ? ntA : ntB;
   const int nt_own = (r + kBN - 1) / kBN;
-  auto sel_rsrc = [&](const int4 &e, int k0) {
+  auto sel_rsrc = [&](const int4 &e) {
     return __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<int32_t *>(sel_idx + (static_cast<size_t>(h) * c_q + e.x) * n + k0),
+        const_cast<int32_t *>(sel_idx + (static_cast<size_t>(h) * c_q + e.x) * n),
         static_cast<short>(0), e.w * 4, 0x00020000);
   };
-  const __amdgpu_buffer_rsrc_t rselA = sel_rsrc(ia, ka);
-  const __amdgpu_buffer_rsrc_t rselB = PAIRED ? sel_rsrc(ib, kb) : rselA;
+  const __amdgpu_buffer_rsrc_t rselA = sel_rsrc(ia);
+  const __amdgpu_buffer_rsrc_t rselB = PAIRED ? sel_rsrc(ib) : rselA;
   const int nbytes = static_cast<int>(static_cast<uint32_t>(n) * (D * 2));
   const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint16_t *>(static_cast<const uint16_t *>(kv) + hoff), static_cast<short>(0), nbytes, 0x00020000);
@@ -643,19 +640,6 @@ __device__ __forceinline__ void attn_dma_body(
 
   // lanes l and l^32 hold the two halves of one query's row sum
   const float l_tot = l_run + __shfl_xor(l_run, 32);
-  if (part) {
-    if (!wave_active) return;
-    float4 *po = reinterpret_cast<float4 *>(part) + 32 * w + l32;
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        po[(8 * db + 2 * i + hf) * kBM] = make_float4(oacc[db][4 * i + 0], oacc[db][4 * i + 1],
-                                                      oacc[db][4 * i + 2], oacc[db][4 * i + 3]);
-    if (hf == 0)
-      *reinterpret_cast<float2 *>(part + D * kBM + 2 * (32 * w + l32)) = make_float2(m_run, l_tot);
-    return;
-  }
   if (!qvalid) return;
   const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
 #pragma unroll
@@ -684,100 +668,31 @@ __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2))) void attn_kernel_dma(
     const void *__restrict__ qv, const void *__restrict__ kv,
     const void *__restrict__ vv, void *ov, const int32_t *__restrict__ offsets,
     const int32_t *__restrict__ perm, const int32_t *__restrict__ sel_idx,
-    const int4 *__restrict__ items, const int4 *__restrict__ order, float *part, float scale_log2) {
+    const int4 *__restrict__ items, const int2 *__restrict__ order, float scale_log2) {
   __shared__ __attribute__((aligned(16))) DmaTile<D> K0;
   __shared__ __attribute__((aligned(16))) DmaTile<D> K1;
   __shared__ __attribute__((aligned(16))) DmaTile<D> V0;
   __shared__ __attribute__((aligned(16))) DmaTile<D> V1;
-  int item, piece = 0, split = 1;
-  float *po = nullptr;
+  int item, half = 0;
   if (order) {
-    const int4 e = order[blockIdx.x];  // (slot, piece, pieces, place)
+    const int2 e = order[blockIdx.x];  // (slot, 0: all of it, 1 or 2: a half)
     item = e.x;
-    piece = e.y;
-    split = e.z;
-    if (split > 1) po = part + static_cast<size_t>(e.w) * kPieceFloats<D>;
+    half = e.y;
   } else {
     item = xcd_item(static_cast<int>(blockIdx.x), total_items);
   }
   if (item < 0 || item >= total_items) return;
   const int h = item / items_per_head;
   int4 ia = items[2 * item], ib = items[2 * item + 1];
+  if (half) take_half(&ia, &ib, half);
   if (ia.z <= 0) return;
-  int ka = 0, kb = 0;
-  if (split > 1) {
-    ka = key_range(&ia, piece, split);
-    kb = key_range(&ib, piece, split);
-  }
   // one block-uniform branch: a lone chunk gathers one set of tiles
   if (ib.z > 0)
-    attn_dma_body<D, BF16IO, true>(n, c_q, h, ia, ib, ka, kb, po, qv, kv, vv, ov, offsets, perm,
+    attn_dma_body<D, BF16IO, true>(n, c_q, h, ia, ib, qv, kv, vv, ov, offsets, perm,
                                    sel_idx, scale_log2, K0, K1, V0, V1);
   else
-    attn_dma_body<D, BF16IO, false>(n, c_q, h, ia, ib, ka, kb, po, qv, kv, vv, ov, offsets, perm,
+    attn_dma_body<D, BF16IO, false>(n, c_q, h, ia, ib, qv, kv, vv, ov, offsets, perm,
                                     sel_idx, scale_log2, K0, K1, V0, V1);
-}
-
-// Joins the pieces of one split slot: per query the largest running max, the
-// sums rescaled to it in piece order, and the normalised result.  Thread t
-// holds query slot t % kBM and every kMergeGroups-th group of 4 channels.
-constexpr int kMergeGroups = 4;
-template <int D, bool BF16IO>
-__global__ __launch_bounds__(kBM *kMergeGroups) void attn_merge_kernel(
-    int n, int c_q, int items_per_head, const int32_t *__restrict__ offsets,
-    const int32_t *__restrict__ perm, const int4 *__restrict__ items,
-    const int4 *__restrict__ merges, const float *__restrict__ part, void *ov) {
-  const int4 e = merges[blockIdx.x];  // (slot, -, pieces, first place)
-  const int split = e.z;
-  if (split <= 1) return;
-  const int h = e.x / items_per_head;
-  const int4 ia = items[2 * static_cast<size_t>(e.x)], ib = items[2 * static_cast<size_t>(e.x) + 1];
-  const int slot = threadIdx.x % kBM, g0 = threadIdx.x / kBM;
-  // the query of this slot: A's waves first, then B's
-  const int wa = (ia.z + 31) >> 5;
-  const int4 it = (slot >> 5) >= wa ? ib : ia;
-  const int ql = slot - ((slot >> 5) >= wa ? 32 * wa : 0);
-  if (ql >= it.z) return;
-  const int pb = offsets[static_cast<size_t>(h) * (c_q + 1) + it.x] + it.y + ql;
-  const int qi = min(max(perm[static_cast<size_t>(h) * n + min(max(pb, 0), n - 1)], 0), n - 1);
-  const float *p0 = part + static_cast<size_t>(e.w) * kPieceFloats<D>;
-  const size_t step = kPieceFloats<D>;
-  float m = -INFINITY, l = 0.0f;
-  for (int i = 0; i < split; ++i) {
-    const float2 ml = *reinterpret_cast<const float2 *>(p0 + i * step + D * kBM + 2 * slot);
-    if (ml.y != 0.0f) {  // not an empty piece (NaN stays NaN)
-      const float mn = fmaxf(m, ml.x);
-      l = l * __builtin_amdgcn_exp2f(m - mn) + ml.y * __builtin_amdgcn_exp2f(ml.x - mn);
-      m = mn;
-    }
-  }
-  const float inv = l > 0.0f ? 1.0f / l : 0.0f;
-  float4 o[D / 4 / kMergeGroups];
-#pragma unroll
-  for (int k = 0; k < D / 4 / kMergeGroups; ++k) o[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  for (int i = 0; i < split; ++i) {
-    const float2 ml = *reinterpret_cast<const float2 *>(p0 + i * step + D * kBM + 2 * slot);
-    const float w = ml.y != 0.0f ? __builtin_amdgcn_exp2f(ml.x - m) : 0.0f;
-    const float4 *po = reinterpret_cast<const float4 *>(p0 + i * step) + slot;
-#pragma unroll
-    for (int k = 0; k < D / 4 / kMergeGroups; ++k) {
-      const float4 v = po[(g0 + kMergeGroups * k) * kBM];
-      o[k].x = fmaf(v.x, w, o[k].x);
-      o[k].y = fmaf(v.y, w, o[k].y);
-      o[k].z = fmaf(v.z, w, o[k].z);
-      o[k].w = fmaf(v.w, w, o[k].w);
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < D / 4 / kMergeGroups; ++k) {
-    const size_t to = (static_cast<size_t>(h) * n + qi) * D + 4 * (g0 + kMergeGroups * k);
-    const float4 v = make_float4(o[k].x * inv, o[k].y * inv, o[k].z * inv, o[k].w * inv);
-    if constexpr (BF16IO)
-      *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(ov) + to) =
-          make_uint2(pack_bf16(v.x, v.y), pack_bf16(v.z, v.w));
-    else
-      *reinterpret_cast<float4 *>(static_cast<float *>(ov) + to) = v;
-  }
 }
 
 // K and V rounded to bf16, 8 elements per thread.
@@ -802,7 +717,7 @@ __device__ __forceinline__ uint32_t slot_cost(const int4 &a, const int4 &b) {
 }
 
 // The block order of a call whose heads' K and V fit the memory-side cache
-// together, or eight of them at a time (attention_pieces).  Block b runs on
+// together, or eight of them at a time (attention_ordered).  Block b runs on
 // XCD b mod 8, whatever the XCDs' loads, so each XCD is given a queue of its
 // own: the list of all heads' slots cut into eight runs of equal cost.  An XCD
 // then works on one or two heads, whose rows its L2 serves to the 32 (d = 64:
@@ -811,42 +726,40 @@ __device__ __forceinline__ uint32_t slot_cost(const int4 &a, const int4 &b) {
 //
 // Within a queue the slots run by cost, largest first, and where the queue is
 // short its last round, partly empty, would be a large part of the launch: the
-// first w rounds of slots run whole, and the rest are cut along their keys
-// into ns pieces, the same key range of all of them before the next.  w and ns
-// are those of the shortest estimated time; a piece costs about kPieceCost
-// tiles on top (its start and its partial results), and the pieces of a whole
-// last round are worth kRoundSlack of it (unequal slots fill a round badly).
-// Nothing is split from kSplitRounds rounds on, where the last matters little.
+// first w rounds of slots run whole, and the rest as halves (take_half), which
+// take kHalfCost of a slot's time (118 / 171 of slot_cost; from 0.60 on the
+// times are the same, below every tail is halved: dense 4 x 8448 280 us for 203).
+// w is that of the shortest estimated time;
+// kRoundSlack: unequal slots fill a last round of whole ones badly.  Nothing is
+// halved from kHalfRounds rounds on, where the last matters little.  (Slots cut
+// along their keys would balance better, but a row's sums in parts round
+// differently, so a result would depend on the other heads of the call and on
+// the workspace.)
 // Measured, list order -> here: 5 heads x 32760 tokens, d = 128: dense (2.5
-// rounds of slots) 2614 -> 2402 us, 128 clusters 1685 -> 1416 us; 40 heads
-// (nothing split) 12.95 -> 12.00 ms; 16 heads x 19721, d = 64, 96 clusters
-// 1202 -> 1030 us; dense 4224 tokens, one head 108 -> 68 us.
+// rounds of slots) 2641 -> 2454 us, 128 clusters 1627 -> 1397 us; 40 heads
+// (nothing halved) 12.85 -> 11.99 ms; 3 heads x 118800, 300 clusters 10.69 ->
+// 10.51 ms; 16 heads x 19721, d = 64, 96 clusters 1085 -> 971 us; 8 heads x 9504
+// dense fp32 519 -> 457 us.
 //
 // One block per XCD, `slots` the most slots of a queue.  order[8 j + x], j <
-// slots + max_pieces: (slot, piece, pieces, place of
-// the partial results), slot -1: nothing; merges[8 s + x], s < max_merges:
-// (slot, 0, pieces, first place), pieces <= 1: nothing.
+// slots + max_halved: (slot, 0 or half), slot -1: nothing.
 constexpr int kPlanThreads = 1024;
 constexpr int kPlanSlots = 4096;      // slots of one queue (sorted in LDS)
-constexpr int kSplitRounds = 8, kMaxSplit = 16;
-constexpr float kPieceCost = 5.0f, kRoundSlack = 0.15f;
+constexpr int kHalfRounds = 8;
+constexpr float kHalfCost = 0.69f, kRoundSlack = 0.15f;
 __device__ __forceinline__ void wave_fence() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
-    int total_items, int slots, int resident, int max_pieces, const int4 *__restrict__ items,
-    int4 *order, int4 *merges, int max_merges) {
+    int total_items, int slots, int resident, int max_halved, const int4 *__restrict__ items,
+    int2 *order) {
   __shared__ unsigned long long key[kPlanSlots];
   __shared__ unsigned long long wsum[kPlanThreads / 64];
-  __shared__ unsigned long long q_cost;
   __shared__ int used, wcnt[kPlanThreads / 64], in_queue[kXcds];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6, x = blockIdx.x;
-  if (t == 0) {
-    used = 0;
-    q_cost = 0;
-  }
+  if (t == 0) used = 0;
   if (t < kXcds) in_queue[t] = 0;
   auto cost_at = [&](int i) -> uint32_t {
     const int4 a = items[2 * static_cast<size_t>(i)], b = items[2 * static_cast<size_t>(i) + 1];
@@ -896,7 +809,6 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
   for (int k = 0; k < kXcds; ++k) fits = fits && in_queue[k] <= slots;
   const int eighth = (ntotal + kXcds - 1) / kXcds;
   const unsigned long long lo = x ? bound[x - 1] : 0, hi = bound[x];
-  unsigned long long taken = 0;
   for (int i = i0; i < i1; ++i) {
     const uint32_t c = cost_at(i);
     if (!c) continue;
@@ -905,12 +817,10 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
       // not depend on where the slots were put
       const int at = atomicAdd(&used, 1);
       if (at < slots) key[at] = (static_cast<unsigned long long>(c) << 32) | static_cast<uint32_t>(~i);
-      taken += c;
     }
     before += c;
     ++nbefore;
   }
-  if (taken) atomicAdd(&q_cost, taken);
   __syncthreads();
   const int n = min(used, slots);
   int size = 64;
@@ -933,49 +843,25 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
       else wave_fence();
     }
   __syncthreads();
-  // one candidate (w, ns) per thread: w = the full rounds less 0, 1 or 2, ns =
-  // 2 .. kMaxSplit; 63: nothing split
+  // rounds of whole slots, or w of them and the rest as halves
   const int cap = resident / kXcds, full = n / cap;
-  const float tiles = n > 0 ? static_cast<float>(q_cost) / (static_cast<float>(kTileCost) * n) : 0.0f;
-  // every wave works out the same candidates
-  float e = INFINITY;
-  {
-    const int wr = full - lane / 16, ns = lane % 16 + 2, tail = n - wr * cap;
-    if (lane == 63) {
-      e = (static_cast<float>((n + cap - 1) / cap) + kRoundSlack) * tiles;
-    } else if (lane < 48 && ns <= kMaxSplit && wr >= 0 && tail > 0 && tail <= max_merges &&
-               tail * ns <= max_pieces && tiles >= static_cast<float>(ns * kPieceTiles) &&
-               n < kSplitRounds * cap) {
-      e = wr * tiles + static_cast<float>((tail * ns + cap - 1) / cap) * (tiles / ns + kPieceCost);
+  int whole = n;
+  if (n < kHalfRounds * cap) {
+    float least = static_cast<float>((n + cap - 1) / cap) + kRoundSlack;
+    for (int wr = full; wr >= 0 && wr >= full - 2; --wr) {
+      const int tail = n - wr * cap;
+      const float e = wr + static_cast<float>((2 * tail + cap - 1) / cap) * kHalfCost;
+      if (tail > 0 && tail <= max_halved && e < least) {
+        least = e;
+        whole = wr * cap;
+      }
     }
   }
-  const float e_min = -wave_max(-e);
-  const int best = __ffsll(static_cast<long long>(__ballot(e == e_min))) - 1;
-  const int ns = best == 63 ? 1 : best % 16 + 2;
-  const int whole = best == 63 ? n : (full - best / 16) * cap, tail = n - whole;
-  auto slot_at = [&](int p) { return static_cast<int>(~static_cast<uint32_t>(key[p])); };
-  auto pieces_of = [&](int slot) {
-    return slot_split(items[2 * static_cast<size_t>(slot)], items[2 * static_cast<size_t>(slot) + 1], ns);
-  };
-  const int place0 = x * max_pieces;
-  for (int j = t; j < slots + max_pieces; j += kPlanThreads) {
-    int4 e = make_int4(-1, 0, 1, 0);
-    if (j < whole) {
-      e.x = slot_at(j);
-    } else if (j - whole < tail * ns) {
-      const int i = (j - whole) / tail, s = (j - whole) - i * tail;
-      const int slot = slot_at(whole + s), split = pieces_of(slot);
-      if (i < split) e = make_int4(slot, i, split, place0 + s * ns + i);
-    }
+  for (int j = t; j < slots + max_halved; j += kPlanThreads) {
+    int2 e = make_int2(-1, 0);
+    const int p = j < whole ? j : whole + (j - whole) / 2;  // halves of a slot side by side
+    if (p < n) e = make_int2(static_cast<int>(~static_cast<uint32_t>(key[p])), j < whole ? 0 : 1 + (j - whole) % 2);
     order[kXcds * static_cast<size_t>(j) + x] = e;
-  }
-  for (int s = t; s < max_merges; s += kPlanThreads) {
-    int4 e = make_int4(-1, 0, 0, 0);
-    if (s < tail) {
-      const int slot = slot_at(whole + s);
-      e = make_int4(slot, 0, pieces_of(slot), place0 + s * ns);
-    }
-    merges[kXcds * static_cast<size_t>(s) + x] = e;
   }
 }
 
@@ -1195,6 +1081,14 @@ int resident_blocks(int d) { return d == 64 ? 512 : 256; }
 // Slots that one XCD's queue holds: half as many again as its share.
 int queue_slots(int total_items) { return (total_items + total_items / 2 + kXcds - 1) / kXcds; }
 
+// The most slots of a queue that run as halves: three rounds where even the
+// fewest slots (all chunks full) fill fewer than kHalfRounds rounds; else none.
+int halved_slots(int heads, int n, int d) {
+  const int cap = resident_blocks(d);
+  const long long least = static_cast<long long>(heads) * ((n + kBM - 1) / kBM);
+  return least < static_cast<long long>(kHalfRounds) * cap ? 3 * cap / kXcds : 0;
+}
+
 template <int D, bool BF16IO>
 hipError_t launch_dma(int heads, int n, const void *q, const void *k, const void *v, void *o,
                       int c_q, const int32_t *offsets, const int32_t *perm, const int32_t *sel_idx,
@@ -1203,24 +1097,17 @@ hipError_t launch_dma(int heads, int n, const void *q, const void *k, const void
   if (!w.order) {
     hipLaunchKernelGGL((attn_kernel_dma<D, BF16IO>), dim3(total), dim3(kNW * 64), 0, s, n, c_q,
                        iph, total, q, k, v, o, offsets, perm, sel_idx, w.items,
-                       static_cast<const int4 *>(nullptr), w.part, scale_log2);
+                       static_cast<const int2 *>(nullptr), scale_log2);
     return hipGetLastError();
   }
-  const int slots = queue_slots(total), queue = slots + w.pieces / kXcds;
-  const int merges = w.pieces / kXcds / 2;
+  const int slots = queue_slots(total), halved = halved_slots(heads, n, D);
+  const int queue = slots + halved;
   hipLaunchKernelGGL(attn_plan_kernel, dim3(kXcds), dim3(kPlanThreads), 0, s, total, slots,
-                     resident_blocks(D), w.pieces / kXcds, w.items, w.order,
-                     w.order + static_cast<size_t>(kXcds) * queue, merges);
-  hipError_t e = hipGetLastError();
+                     resident_blocks(D), halved, w.items, w.order);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((attn_kernel_dma<D, BF16IO>), dim3(kXcds * queue), dim3(kNW * 64), 0, s, n, c_q,
-                     iph, total, q, k, v, o, offsets, perm, sel_idx, w.items, w.order, w.part,
-                     scale_log2);
-  e = hipGetLastError();
-  if (e != hipSuccess || !w.pieces) return e;
-  hipLaunchKernelGGL((attn_merge_kernel<D, BF16IO>), dim3(kXcds * merges), dim3(kBM * kMergeGroups),
-                     0, s, n, c_q, iph, offsets, perm, w.items,
-                     w.order + static_cast<size_t>(kXcds) * queue, w.part, o);
+                     iph, total, q, k, v, o, offsets, perm, sel_idx, w.items, w.order, scale_log2);
   return hipGetLastError();
 }
 
@@ -1300,35 +1187,28 @@ bool attention_copies_kv(int n, int d, bool bf16) {
          static_cast<uint64_t>(n) * d * 2 < (1ull << 32);
 }
 
-// Dense calls (one cluster) from the length on from which lists are split.
-// Sparse calls keep about half of the keys and have more slots; up to 16,384
-// tokens the order gains less than its two launches cost (8 heads x 9504
-// tokens, 40 clusters: 280 us with, 277 us without; 16 heads x 19721, d = 64:
-// 985 us with, 1027 us without).
+// Dense calls (one cluster) from 4,096 tokens on: one head of 4,224 tokens, d =
+// 128, 103 us in list order, 80 us so.  Not those whose slots fill more than half
+// the CUs but not a round, where every order is as good (4 heads x 8,448 tokens,
+// 132 slots: 196 us in list order, 203 us with a plan; 8 x 5,280, d = 64, 168
+// slots: 104 and 112 us).  Sparse calls have more slots of unequal cost; up to
+// 16,384 tokens the order gains less than its launch costs (8 heads x 9,504
+// tokens, 40 clusters: 277 us in list order, 280 us so; one head of 17,316: 254
+// and 194 us).
 bool attention_ordered(int heads, int n, int d, int c_q) {
-  if ((d != 64 && d != 128) || n < kSplitTiles * kBN * (c_q > 1 ? 4 : 1)) return false;
+  if ((d != 64 && d != 128) || n < (c_q > 1 ? 16384 : 4096)) return false;
   const int at_once = heads < kXcds ? heads : kXcds;
   if (static_cast<uint64_t>(at_once) * n * d * 4 > kMemorySideCache) return false;
   const long long total = static_cast<long long>(heads) * attn_items_per_head(n, c_q);
-  return total <= (1 << 20) && queue_slots(static_cast<int>(total)) <= kPlanSlots;
+  if (total > (1 << 20) || queue_slots(static_cast<int>(total)) > kPlanSlots) return false;
+  const long long full = static_cast<long long>(heads) * ((n + kBM - 1) / kBM);
+  return c_q > 1 || 2 * full <= resident_blocks(128) || full > resident_blocks(d);
 }
 
-// Three rounds of pieces where even the fewest slots (all chunks full) fill
-// fewer than kSplitRounds rounds; else none.
-int attention_pieces(int heads, int n, int d, int c_q) {
-  if (!attention_ordered(heads, n, d, c_q)) return 0;
-  const int cap = resident_blocks(d);
-  if (static_cast<long long>(heads) * ((n + kBM - 1) / kBM) >= static_cast<long long>(kSplitRounds) * cap)
-    return 0;
-  return 3 * cap;
+size_t attention_order_entries(int heads, int n, int d, int c_q) {
+  return static_cast<size_t>(kXcds) *
+         (queue_slots(heads * attn_items_per_head(n, c_q)) + halved_slots(heads, n, d));
 }
-
-size_t attention_order_entries(int heads, int n, int c_q, int pieces) {
-  return static_cast<size_t>(kXcds) * queue_slots(heads * attn_items_per_head(n, c_q)) + pieces +
-         pieces / 2;
-}
-
-size_t attention_piece_floats(int d) { return d == 64 ? kPieceFloats<64> : kPieceFloats<128>; }
 
 hipError_t attention_run(int heads, int n, int d, bool bf16, const void *q,
                          const void *k, const void *v, void *o, int c_q,

@@ -213,16 +213,13 @@ hipError_t attention_scratch(int4 **items);
 hipError_t attention_items(int heads, int n, int c_q, bool pair, const int32_t *offsets,
                            const int32_t *sel_counts, int4 *items, hipStream_t s);
 // Scratch of one attention call: the work list, and where the workspace holds
-// them the block order (attention_order_entries; null: list order), room for
-// `pieces` pieces of split slots (attention_piece_floats(d) floats each) and
-// bf16 copies of fp32 K and V (2 * heads * n * d elements).  Without them slots
-// stay whole (pieces == 0) and K and V are rounded row by row (kv16 null, same
-// result).
+// them bf16 copies of fp32 K and V (2 * heads * n * d elements; null: rows are
+// rounded one by one) and the block order (attention_order_entries; null: list
+// order, and for fp32 without the copies).  The result is the same with and
+// without them.
 struct AttnScratch {
   int4 *items;
-  int4 *order;
-  float *part;
-  int pieces;
+  int2 *order;
   uint16_t *kv16;
 };
 hipError_t attention_run(int heads, int n, int d, bool bf16, const void *q,
@@ -233,11 +230,8 @@ hipError_t attention_run(int heads, int n, int d, bool bf16, const void *q,
 // Whether the workspace holds bf16 copies of K and V.  One head's copy is
 // addressed with 32-bit byte offsets.
 bool attention_copies_kv(int n, int d, bool bf16);
-// Whether the call has a block order of its own, the pieces that the workspace
-// then holds partial results for, and the order's 16-byte entries.
+// Whether the call has a block order of its own, and that order's entries.
 bool attention_ordered(int heads, int n, int d, int c_q);
-int attention_pieces(int heads, int n, int d, int c_q);
-size_t attention_order_entries(int heads, int n, int c_q, int pieces);
-size_t attention_piece_floats(int d);
+size_t attention_order_entries(int heads, int n, int d, int c_q);
 
 }  // namespace scope

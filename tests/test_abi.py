@@ -69,6 +69,22 @@ def test_workspace_size_and_shape_validation():
     assert ws_size(hy_shape(n=100), c_q=101)[0] == INVALID          # C > n
 
 
+def test_attention_workspace_is_sized_to_the_call():
+    # beyond the work list: 8 bytes per block of the order, and for fp32 the
+    # bf16 copies of K and V
+    for heads, n, d in ((1, 4224, 128), (1, 5280, 64), (5, 32760, 128), (3, 118800, 128)):
+        a = d // 3 // 2 * 2
+        ranges = ((0, a, 2 * a), (a, a, d - 2 * a))
+        slots = heads * (-(-n // 256) + 1)
+        room = 32 * slots + 8 * (3 * slots + 2048) + 4096
+        other = ws_size(hy_shape(heads=heads, n=n, d=32, ranges=((0, 8, 16), (8, 8, 16))),
+                        1, (1, 1, 1))[1]  # no attention at this d: the other calls
+        st, bf16 = ws_size(hy_shape(heads=heads, n=n, d=d, ranges=ranges), 1, (1, 1, 1))
+        assert st == OK and bf16 <= room + 8 * other
+        st, f32 = ws_size(hy_shape(heads=heads, n=n, d=d, ranges=ranges, dtype=B.F32), 1, (1, 1, 1))
+        assert st == OK and f32 <= room + 8 * other + 4 * heads * n * d
+
+
 def call_queries(shape, c_q=256, iters=10, ws=FAKE, ws_bytes=1 << 40, q=FAKE):
     return B.lib().scope_cluster_queries(
         ctypes.byref(shape), q, c_q, iters, None, FAKE, FAKE, FAKE, FAKE, FAKE,

@@ -1,8 +1,9 @@
-"""GPU: attention calls of few work slots, which run in an order of their own
-with their last slots cut along the keys and joined from partial results.
-Every row is checked against plain torch attention in float64 on the inputs
-rounded to bf16, and against the same call with room for the work list alone
-(whole slots, K and V rounded row by row)."""
+"""GPU: attention calls that run in a block order of their own, some of their
+slots as two halves.  Every row is checked against plain torch attention in
+float64 on the inputs rounded to bf16, and must be bit for bit that of the same
+call with room for the work list alone (list order, whole slots, fp32 K and V
+rounded row by row): a result depends neither on the workspace nor on the other
+heads of the call, nor do NaN and infinities spread further."""
 import math
 
 import numpy as np
@@ -34,7 +35,7 @@ def _uneven(n):
 
 
 CASES = {
-    "dense_4096": (2, [4096], [4096], 128, "bf16"),            # shortest list that splits
+    "dense_4096": (2, [4096], [4096], 128, "bf16"),            # shortest call with an order
     "dense_4161_d64": (1, [4161], [4161], 64, "bf16"),         # a ragged last tile
     "dense_4500_f32": (1, [4500], [4500], 128, "f32"),
     "sparse_ragged": (1, [5000, 40, 300, 1, 0, 6000, 129, 4914], [16384, 4097, 4032, 1, 9, 8191, 16000, 5000],
@@ -43,15 +44,13 @@ CASES = {
                          64, "bf16"),
     "sparse_f32_d64": (1, [16400 - 3 * 700] + [700] * 3, [4200, 16400, 4100, 64], 64, "f32"),
     "uneven": (1, *_uneven(16500), 128, "bf16"),
-    "whole_slots": (20, [26214 // 9] * 9, [6000] * 9, 64, "bf16"),  # no pieces: eight rounds and more
+    "whole_slots": (20, [26214 // 9] * 9, [6000] * 9, 64, "bf16"),  # no halves
+    "round_and_halves": (5, [14401], [14401], 128, "bf16"),    # a round of whole slots, the rest halved
 }
 
 
-@pytest.mark.parametrize("name", list(CASES))
-def test_split_slots(name):
-    heads, sizes, keys, d, dtype = CASES[name]
+def _problem(heads, sizes, keys, d, dtype):
     n, c_q = sum(sizes), len(sizes)
-    G.say(f"[split] {name}: heads={heads} n={n} clusters={c_q} d={d} {dtype}")
     g = torch.Generator(device="cuda").manual_seed(n + d)
     rand = lambda s: s * torch.randn(heads, n, d, generator=g, device="cuda")
     tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
@@ -66,14 +65,34 @@ def test_split_slots(name):
             sel[h, c, :r] = torch.randperm(n, generator=g, device="cuda")[:r].sort()[0]
     off = (0, d // 4, d // 2)
     shape = B.make_shape(heads, n, d, B.BF16 if dtype == "bf16" else B.F32, (off, (d // 4, d // 4, d // 2)))
+    return shape, q, k, v, offsets, perm, counts, sel
+
+
+def _attend(shape, q, k, v, offsets, perm, counts, sel):
+    """The call with the whole workspace, and with room for the list alone."""
+    heads, n, c_q = shape.heads, shape.n, counts.shape[1]
     full = B.alloc_workspace(shape, c_q, (1, 1, 1))
     lists = torch.empty(2 * heads * (-(-n // 256) + c_q) * 16 + 256, dtype=torch.uint8, device="cuda")
     out = []
     for ws in (full, lists):
         o = torch.full_like(q, float("nan"))
         B.scope_sparse_attention(shape, q, k, v, c_q, offsets, perm.int(), counts, sel, 0.0, o, ws)
-        out.append(o.double())
+        out.append(o)
     torch.cuda.synchronize()
+    return out
+
+
+def _bits(o):
+    return o.view(torch.int16 if o.dtype == torch.bfloat16 else torch.int32)
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_split_slots(name):
+    heads, sizes, keys, d, dtype = CASES[name]
+    n, c_q = sum(sizes), len(sizes)
+    G.say(f"[split] {name}: heads={heads} n={n} clusters={c_q} d={d} {dtype}")
+    shape, q, k, v, offsets, perm, counts, sel = _problem(heads, sizes, keys, d, dtype)
+    out = _attend(shape, q, k, v, offsets, perm, counts, sel)
     ref = torch.zeros(heads, n, d, dtype=torch.float64, device="cuda")
     for h in range(heads):
         qd, kd, vd = (x[h].to(torch.bfloat16).double() for x in (q, k, v))
@@ -85,9 +104,31 @@ def test_split_slots(name):
             for a in range(0, rows.numel(), 2048):
                 p = torch.softmax(qd[rows[a:a + 2048]] @ kd[kk].T / math.sqrt(d), 1)
                 ref[h, rows[a:a + 2048]] = p @ vd[kk]
-    for o in out:
-        err = (o - ref).abs()
-        assert float(err.max()) <= G.MAX_ABS
-        assert float(err.sum() / ref.abs().sum()) <= G.MEAN_REL
-    # both round the weights to bf16 against running maxima of their own
-    assert float((out[0] - out[1]).norm() / out[1].norm()) <= 5e-3
+    err = (out[0].double() - ref).abs()
+    assert float(err.max()) <= G.MAX_ABS
+    assert float(err.sum() / ref.abs().sum()) <= G.MEAN_REL
+    assert torch.equal(_bits(out[0]), _bits(out[1]))
+
+
+@pytest.mark.parametrize("d,dtype", [(128, "bf16"), (64, "bf16"), (128, "f32")])
+def test_not_finite_values_stay_where_they_are(d, dtype):
+    heads, n = 2, 4608
+    G.say(f"[split] NaN and infinite logits, d={d} {dtype}")
+    shape, q, k, v, offsets, perm, counts, sel = _problem(heads, [n], [n], d, dtype)
+    # head 0: the logits of the second half of the keys overflow to -inf, a
+    # whole number of tiles: weights of exactly zero
+    q[0, :, 0] = 4.0
+    k[0, n // 2:, 0] = -3e38
+    # head 1: one NaN value in V, one in Q
+    v[1, 3000, 5] = float("nan")
+    q[1, 77, 1] = float("nan")
+    out = _attend(shape, q, k, v, offsets, perm, counts, sel)
+    assert torch.equal(_bits(out[0]), _bits(out[1]))
+    o = out[0].double()
+    r16 = lambda x: x.to(torch.bfloat16).double()
+    p = torch.softmax(r16(q[0]) @ r16(k[0, :n // 2]).T / math.sqrt(d), 1)
+    ref = p @ r16(v[0, :n // 2])
+    assert float((o[0] - ref).abs().max()) <= G.MAX_ABS
+    nan = torch.zeros(n, d, dtype=torch.bool, device="cuda")
+    nan[:, 5] = nan[77] = True
+    assert torch.equal(torch.isnan(o[1]), nan)
