@@ -72,6 +72,9 @@ hipError_t km_init(const KmProblem *p, int nsub, bool warm, const int32_t *init,
 hipError_t km_assign(const KmProblem &p, bool with_hist, hipStream_t s);
 // The assignments of several subspaces of the same rows.
 hipError_t km_assign_subspaces(const KmProblem *p, int nsub, hipStream_t s);
+// Blocks for each of nsub subspaces of the given costs, out of `cus`: in
+// proportion, at least one and at most `most` each.
+void km_block_shares(const double *cost, int nsub, int cus, long long most, int *blocks);
 hipError_t km_group(const KmProblem &p, hipStream_t s);
 // The three key subspaces' assignments in one pass over the rows (matrix
 // cores; codebooks side by side in LDS): applies when km_assign3_ok.

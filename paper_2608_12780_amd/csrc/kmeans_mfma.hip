@@ -81,7 +81,10 @@ __global__ __launch_bounds__(64 * kWaves<T>) void km_assign_mfma_kernel(
 // Several subspaces in one launch, each with blocks of its own (from first[m]
 // on) in proportion to its work.  One launch per subspace leaves the last
 // slices of each to a few waves: 5 heads x 32760 rows are 1.25 slices per wave
-// of the chip, two rounds where one and a quarter would do.
+// of the chip, two rounds where one and a quarter would do.  A whole clustering
+// of keys into 333 centroids per subspace, apart -> together: that one, 16 / 56 /
+// 56 channels, 1320 -> 1048 us; 3 x 118800 2107 -> 1754 us; 40 x 32760 6149 ->
+// 5819 us; 24 x 118800 12.82 -> 12.53 ms; fp32 3 x 118800 2479 -> 2134 us.
 template <typename T>
 struct ManyArgs {
   int nsub, heads;
@@ -503,25 +506,49 @@ bool km_mfma_ok(bool bf16, int ld, int col0, int dx, int C) {
   return !bf16 || !((ld | col0 | dx) & 1);
 }
 
+// Together never more than `cus` blocks (as long as that gives each one): the
+// codebooks' LDS holds one block per CU, so a block too many would run alone
+// after the others.
+void km_block_shares(const double *cost, int nsub, int cus, long long most, int *blocks) {
+  double sum = 0.0;
+  for (int m = 0; m < nsub; ++m) sum += cost[m];
+  int used = 0;
+  for (int m = 0; m < nsub; ++m) {
+    const int share = static_cast<int>(cus * cost[m] / sum);
+    used += blocks[m] = share < 1 ? 1 : share;
+  }
+  // the blocks left over go where a block has the most to do; those that the
+  // smallest subspaces got beyond their share come from where one is missed least
+  for (; used < cus; ++used) {
+    int at = 0;
+    for (int m = 1; m < nsub; ++m)
+      if (cost[m] * blocks[at] > cost[at] * blocks[m]) at = m;
+    ++blocks[at];
+  }
+  for (; used > cus && used > nsub; --used) {
+    int at = -1;
+    for (int m = 0; m < nsub; ++m)
+      if (blocks[m] > 1 && (at < 0 || cost[m] * (blocks[at] - 1) < cost[at] * (blocks[m] - 1))) at = m;
+    --blocks[at];
+  }
+  for (int m = 0; m < nsub; ++m)
+    if (blocks[m] > most) blocks[m] = static_cast<int>(most);
+}
+
 namespace {
 template <typename T>
 hipError_t assign_many(const KmProblem *p, int nsub, hipStream_t s) {
   ManyArgs<T> M{};
   M.heads = p[0].heads;
-  double cost[kMaxSub], sum = 0.0;
-  for (int m = 0; m < nsub; ++m) {
-    // per 32 x 32 values: 4 dxp cycles of MFMA, 256 of the fold
-    cost[m] = static_cast<double>(p[m].cpad) * (4 * p[m].dxp + 256);
-    sum += cost[m];
-  }
-  const int cus = cu_count();
+  // per 32 x 32 values: 4 dxp cycles of MFMA, 256 of the fold
+  double cost[kMaxSub];
+  for (int m = 0; m < nsub; ++m) cost[m] = static_cast<double>(p[m].cpad) * (4 * p[m].dxp + 256);
   const long long slices = static_cast<long long>(p[0].heads) * ((p[0].n + 31) / 32);
-  const long long most = (slices + kWaves<T> - 1) / kWaves<T>;
+  int blocks[kMaxSub];
+  km_block_shares(cost, nsub, cu_count(), (slices + kWaves<T> - 1) / kWaves<T>, blocks);
   for (int m = 0; m < nsub; ++m) {
     const KmProblem &q = p[m];
-    long long blocks = static_cast<long long>(cus * cost[m] / sum + 0.5);
-    blocks = blocks < 1 ? 1 : blocks > most ? most : blocks;
-    M.first[m + 1] = M.first[m] + static_cast<int>(blocks);
+    M.first[m + 1] = M.first[m] + blocks[m];
     M.dxp[m] = q.dxp;
     M.a[m] = SliceArgs<T>{static_cast<const T *>(q.x), q.x_head_stride, q.ld, q.col0, q.dx,
                           q.n, q.C, q.cpad, q.u, q.u_head_stride, q.assign, q.a_head_stride,
@@ -558,20 +585,7 @@ hipError_t km_assign_subspaces(const KmProblem *p, int nsub, hipStream_t s) {
     }
   }
   if (nfits == 0) return hipSuccess;
-  // one launch where the rounds of slices of a single subspace would end on a
-  // mostly idle one (5 heads x 32760 rows x 333 centroids, 42-44 channels: 1.25
-  // rounds, 86 us apart, 58 us together; 3 x 118800, 16 / 56 / 56 channels: 2.7
-  // rounds, 130 us apart, 136 us together)
-  const long long slices = static_cast<long long>(p[0].heads) * ((p[0].n + 31) / 32);
-  const long long round = static_cast<long long>(cu_count()) * (p[0].bf16 ? kWaves<uint16_t> : kWaves<float>);
-  const bool uneven = 100 * ((slices + round - 1) / round * round) > 115 * slices;
-  if (nfits == 1 || !uneven) {
-    for (int m = 0; m < nfits; ++m) {
-      const hipError_t e = km_assign(fits[m], false, s);
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-  }
+  if (nfits == 1) return km_assign(fits[0], false, s);
   return p[0].bf16 ? assign_many<uint16_t>(fits, nfits, s) : assign_many<float>(fits, nfits, s);
 }
 
