@@ -444,10 +444,11 @@ int32_t cluster_queries(const scope_shape *shape, const void *q, int32_t c_q, in
                            scope::DeviceArgs{}, s));
   // the returned grouping is that of the last assignment, taken before the
   // last update
-  const int lloyd = scope::km_lloyd_blocks(&p, 1, plan);
-  if (lloyd) plan.blocks = lloyd;
-  if (lloyd == 1) {
-    SCOPE_TRY(scope::km_lloyd(&p, 1, 1, iters, false, p.chunk_hist, plan, w.slab, w.cslab,
+  const scope::LloydForm lloyd = scope::km_lloyd_form(&p, 1, plan);
+  const bool fused = lloyd.form != scope::Lloyd::kSeparate;
+  if (fused) plan.blocks = lloyd.blocks;
+  if (lloyd.form == scope::Lloyd::kAll) {
+    SCOPE_TRY(scope::km_lloyd(&p, 1, lloyd, iters, false, p.chunk_hist, plan, w.slab, w.cslab,
                               dev_status, s));
     SCOPE_TRY(scope::km_group(p, s));
     return SCOPE_OK;
@@ -455,7 +456,7 @@ int32_t cluster_queries(const scope_shape *shape, const void *q, int32_t c_q, in
   for (int it = 0; it < iters; ++it) {
     const bool last = it + 1 == iters;
     int32_t *status = it == 0 ? dev_status : nullptr;
-    if (lloyd) {
+    if (fused) {
       SCOPE_TRY(scope::km_lloyd(&p, 1, lloyd, 1, false, last ? p.chunk_hist : nullptr, plan, w.slab,
                                 w.cslab, status, s));
     } else {
@@ -525,23 +526,24 @@ int32_t cluster_key_subspaces(const scope_shape *shape, const void *k, const int
   scope::AccPlan plan = key_plan(shape, c_m);
   // the three assignments in one pass over K when the codebooks fit the LDS
   // together, else blocks of their own for each subspace
-  const bool fused = scope::km_assign3_ok(p);
+  const bool one_pass = scope::km_assign3_ok(p);
   scope::DeviceArgs args{};
-  if (fused) scope::km_assign3_args(p, w.args3, &args);
+  if (one_pass) scope::km_assign3_args(p, w.args3, &args);
   // init rows of head h, subspace m live at init_idx[(h*3 + m)*init_stride]
   SCOPE_TRY(scope::km_init(p, 3, warm, init_idx, 3 * init_stride, init_stride, dev_status,
                            nullptr, 0, args, s));
   auto assign_all = [&]() -> hipError_t {
-    return fused ? scope::km_assign3(p, w.args3, s) : scope::km_assign_subspaces(p, 3, s);
+    return one_pass ? scope::km_assign3(p, w.args3, s) : scope::km_assign_subspaces(p, 3, s);
   };
-  const int lloyd = scope::km_lloyd_blocks(p, 3, plan);
-  if (lloyd) plan.blocks = lloyd;
-  if (lloyd == 1) {
-    SCOPE_TRY(scope::km_lloyd(p, 3, 1, iters, true, nullptr, plan, w.slab, w.cslab, dev_status, s));
+  const scope::LloydForm lloyd = scope::km_lloyd_form(p, 3, plan);
+  const bool fused = lloyd.form != scope::Lloyd::kSeparate;
+  if (fused) plan.blocks = lloyd.blocks;
+  if (lloyd.form == scope::Lloyd::kAll) {
+    SCOPE_TRY(scope::km_lloyd(p, 3, lloyd, iters, true, nullptr, plan, w.slab, w.cslab, dev_status, s));
   } else {
     for (int it = 0; it < iters; ++it) {
       int32_t *status = it == 0 ? dev_status : nullptr;
-      if (lloyd) {
+      if (fused) {
         SCOPE_TRY(scope::km_lloyd(p, 3, lloyd, 1, false, nullptr, plan, w.slab, w.cslab, status, s));
       } else {
         SCOPE_TRY(assign_all());
@@ -749,14 +751,15 @@ int32_t scope_cluster_key_partition(const scope_shape *shape, const void *k,
   // rows of head h, subspace m at init_idx[(h*M + m)*init_stride]
   SCOPE_TRY(scope::km_init(p, M, false, init_idx, M * init_stride, init_stride, dev_status,
                            nullptr, 0, scope::DeviceArgs{}, s));
-  const int lloyd = scope::km_lloyd_blocks(p, M, plan);
-  if (lloyd) plan.blocks = lloyd;
-  if (lloyd == 1) {
-    SCOPE_TRY(scope::km_lloyd(p, M, 1, iters, true, nullptr, plan, w.slab, w.cslab, dev_status, s));
+  const scope::LloydForm lloyd = scope::km_lloyd_form(p, M, plan);
+  const bool fused = lloyd.form != scope::Lloyd::kSeparate;
+  if (fused) plan.blocks = lloyd.blocks;
+  if (lloyd.form == scope::Lloyd::kAll) {
+    SCOPE_TRY(scope::km_lloyd(p, M, lloyd, iters, true, nullptr, plan, w.slab, w.cslab, dev_status, s));
   } else {
     for (int it = 0; it < iters; ++it) {
       int32_t *status = it == 0 ? dev_status : nullptr;
-      if (lloyd) {
+      if (fused) {
         SCOPE_TRY(scope::km_lloyd(p, M, lloyd, 1, false, nullptr, plan, w.slab, w.cslab, status, s));
       } else {
         SCOPE_TRY(scope::km_assign_subspaces(p, M, s));

@@ -144,13 +144,18 @@ hipError_t km_finish(const AccPlan &plan, const KmProblem *p, int nsub, bool pre
                      const long long *slab, const int32_t *cslab, hipStream_t s);
 // Largest |x| (exclusive) for which n rows' fixed-point sums are exact.
 float km_range_limit(int n);
-// Small problems: assignment and update of an iteration in one launch, or with
-// one block per head and subspace all iterations (and the keys' last
-// assignment).  km_lloyd_blocks: blocks per head and subspace, 0 where the
-// separate launches are used, at most the plan's.  The plan's block count is
-// to be set to it; with more than one block km_finish follows each launch.
-int km_lloyd_blocks(const KmProblem *p, int nsub, const AccPlan &plan);
-hipError_t km_lloyd(const KmProblem *p, int nsub, int blocks, int iters, bool final_assign,
+// Small problems: assignment and update of an iteration in one launch, or all
+// iterations (and the keys' last assignment) in one block per head and subspace.
+// km_lloyd_form: which of them, and the blocks per head and subspace, at most
+// the plan's, whose block count is to be set to it.  km_finish follows each
+// launch of a single iteration.
+enum class Lloyd { kSeparate, kIteration, kAll };
+struct LloydForm {
+  Lloyd form;
+  int blocks;
+};
+LloydForm km_lloyd_form(const KmProblem *p, int nsub, const AccPlan &plan);
+hipError_t km_lloyd(const KmProblem *p, int nsub, LloydForm form, int iters, bool final_assign,
                     int32_t *chunk_hist, const AccPlan &plan, long long *slab, int32_t *cslab,
                     int32_t *status, hipStream_t s);
 hipError_t km_pack_codes(const int32_t *a3, size_t a_head_stride,

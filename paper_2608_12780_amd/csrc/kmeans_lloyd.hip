@@ -315,15 +315,31 @@ __attribute__((amdgpu_waves_per_eu(kPerCu<T, ONE> * 2))) void km_lloyd_kernel(co
 // 91 MB, 1080 / 1002 us; keys 40 x 32760, 335 MB, 3320 / 2528 us).
 // All iterations in one block up to 10 slices (queries 3 heads x 300 rows x 16:
 // 173 us against 181 with several blocks, 700 rows x 32: 269 against 205).
+//
+// With so many (head, subspace) pairs that each gets only one block, it runs
+// - up to 32 slices all iterations, unless its rows are bf16 and wider than 64
+//   channels, where two blocks of the iteration form share a CU (bf16 keys of 300
+//   heads x 330 rows: all 379, iteration 445, separate 664 us; 300 x 640 520, 560,
+//   694; queries, 128 channels, 300 x 330 511, 346, 474; 140 x 1000 562, 446, 428;
+//   fp32 queries 150 x 600 363, 453, 416; fp32 keys 86 x 1000 420, 556, 478);
+// - beyond, bf16 rows one iteration where every CU has a block (keys 100 x 1900
+//   534, 516, 583 us; 8 subspaces 33 x 2000 376, 319, 361; queries, 64 channels,
+//   130 x 2900 517, 586, 455);
+// - beyond, fp32 rows all iterations where the rounds of blocks keep three fifths
+//   of the CUs busy (8 subspaces 24 x 4096, 192 blocks, 392, 503, 480 us; keys 60 x
+//   1600, 180 blocks, 431, 581, 485; 8 subspaces 33 x 2500, 264 blocks, 508, 647,
+//   485; keys 50 x 1900, 150 blocks, 501, 649, 421; on the wrong side: 4 subspaces
+//   33 x 2500, 132 blocks, 373, 456, 409).
 constexpr size_t kLloydBytes = 48u << 20;
-constexpr int kLloydOneBlock = 10;
-int km_lloyd_blocks(const KmProblem *p, int nsub, const AccPlan &plan) {
+constexpr int kLloydOneBlock = 10, kLloydOneBlockMany = 32;
+LloydForm km_lloyd_form(const KmProblem *p, int nsub, const AccPlan &plan) {
+  const LloydForm separate{Lloyd::kSeparate, 0};
   const int slices = (p[0].n + 31) / 32;
   for (int m = 0; m < nsub; ++m)
-    if (!p[m].mfma || lloyd_lds(p[m].C, p[m].cpad, p[m].dx, p[m].dxp, nullptr, nullptr) > kLloydLds) return 0;
+    if (!p[m].mfma || lloyd_lds(p[m].C, p[m].cpad, p[m].dx, p[m].dxp, nullptr, nullptr) > kLloydLds) return separate;
   const size_t row_bytes = static_cast<size_t>(p[0].ld) * (p[0].bf16 ? 2 : 4);
-  if (row_bytes * p[0].n * p[0].heads > kLloydBytes) return 0;
-  if (slices <= kLloydOneBlock) return 1;
+  if (row_bytes * p[0].n * p[0].heads > kLloydBytes) return separate;
+  if (slices <= kLloydOneBlock) return LloydForm{Lloyd::kAll, 1};
   // as many blocks as the CUs hold, each wave with a slice, and no more slabs
   // than the workspace has
   size_t lds = 0;
@@ -336,10 +352,16 @@ int km_lloyd_blocks(const KmProblem *p, int nsub, const AccPlan &plan) {
   const int most = (slices + kLloydWaves - 1) / kLloydWaves;
   if (blocks > most) blocks = most;
   if (blocks > plan.blocks) blocks = plan.blocks;
-  return blocks < 1 ? 1 : blocks;
+  if (blocks >= 2) return LloydForm{Lloyd::kIteration, blocks};
+  bool wide = false;
+  for (int m = 0; m < nsub; ++m) wide = wide || (p[m].bf16 && p[m].dxp > 64);
+  if (slices <= kLloydOneBlockMany) return LloydForm{wide ? Lloyd::kIteration : Lloyd::kAll, 1};
+  const int pairs = p[0].heads * nsub, rounds = (pairs + kAccTargetBlocks - 1) / kAccTargetBlocks;
+  if (p[0].bf16) return pairs >= kAccTargetBlocks ? LloydForm{Lloyd::kIteration, 1} : separate;
+  return 5 * pairs >= 3 * rounds * kAccTargetBlocks ? LloydForm{Lloyd::kAll, 1} : separate;
 }
 
-hipError_t km_lloyd(const KmProblem *p, int nsub, int blocks, int iters, bool final_assign,
+hipError_t km_lloyd(const KmProblem *p, int nsub, LloydForm form, int iters, bool final_assign,
                     int32_t *chunk_hist, const AccPlan &plan, long long *slab, int32_t *cslab,
                     int32_t *status, hipStream_t s) {
   LloydArgs A{};
@@ -377,9 +399,9 @@ hipError_t km_lloyd(const KmProblem *p, int nsub, int blocks, int iters, bool fi
     const size_t need = lloyd_lds(K.C, K.cpad, K.dx, K.dxp, nullptr, nullptr);
     lds = need > lds ? need : lds;
   }
-  const dim3 grid(blocks, p[0].heads, nsub), block(kLloydThreads);
+  const dim3 grid(form.blocks, p[0].heads, nsub), block(kLloydThreads);
 #define SCOPE_LLOYD(T)                                                                  \
-  if (blocks == 1) hipLaunchKernelGGL((km_lloyd_kernel<T, true>), grid, block, lds, s, A); \
+  if (form.form == Lloyd::kAll) hipLaunchKernelGGL((km_lloyd_kernel<T, true>), grid, block, lds, s, A); \
   else hipLaunchKernelGGL((km_lloyd_kernel<T, false>), grid, block, lds, s, A)
   if (p[0].bf16) {
     SCOPE_LLOYD(uint16_t);

@@ -21,6 +21,32 @@ int main(int argc, char **argv) {
     for (int m = 0; m < nsub; ++m) cost[m] = atof(argv[4 + m]);
     scope::km_block_shares(cost, nsub, atoi(argv[2]), atoll(argv[3]), blocks);
     for (int m = 0; m < nsub; ++m) printf("%d ", blocks[m]);
+  } else if (!strcmp(argv[1], "lloyd")) {  // bf16 heads n (C dx)...: form, blocks, the plan's blocks
+    const int nsub = (argc - 5) / 2;
+    scope::KmProblem p[8] = {};
+    int col0[8], dx[8], C[8], d = 0;
+    for (int m = 0; m < nsub; ++m) {
+      C[m] = atoi(argv[5 + 2 * m]);
+      dx[m] = atoi(argv[6 + 2 * m]);
+      col0[m] = d;
+      d += dx[m];
+    }
+    for (int m = 0; m < nsub; ++m) {
+      p[m].bf16 = atoi(argv[2]);
+      p[m].heads = atoi(argv[3]);
+      p[m].n = atoi(argv[4]);
+      p[m].ld = d;
+      p[m].col0 = col0[m];
+      p[m].dx = dx[m];
+      p[m].C = C[m];
+      p[m].cpad = scope::km_cpad(C[m]);
+      p[m].dxp = scope::km_dxp(dx[m]);
+      p[m].mfma = scope::km_mfma_ok(p[m].bf16, d, col0[m], dx[m], C[m]);
+    }
+    scope::AccPlan plan;
+    scope::km_accum_plan(nsub, col0, dx, C, p[0].heads, p[0].n, &plan);
+    const scope::LloydForm f = scope::km_lloyd_form(p, nsub, plan);
+    printf("%d %d %d", static_cast<int>(f.form), f.blocks, plan.blocks);
   }
 }
 """
@@ -74,3 +100,49 @@ def test_subspaces_share_the_cus(probe, cols, cus):
                 moved[j] += 1
                 assert max(c / b for c, b in zip(cost, moved)) >= longest * (1 - 1e-12)
     assert probe("shares", cus, 3, *cost) == [min(b, 3) for b in blocks]
+
+
+SEPARATE, ITERATION, ALL = 0, 1, 2
+
+
+def _split(d, m):
+    return [d // m // 2 * 2] * (m - 1) + [d - (m - 1) * (d // m // 2 * 2)]
+
+
+@pytest.mark.parametrize("bf16,heads,n,c,widths,want", [
+    (1, 3, 320, 32, [128], ALL),                  # ten slices
+    (1, 3, 321, 32, [128], ITERATION),
+    (1, 300, 330, 16, [128], ITERATION),          # one block each: queries ...
+    (1, 300, 640, 16, [16, 56, 56], ALL),         # ... and narrower rows
+    (1, 140, 1000, 16, [128], ITERATION),
+    (1, 100, 1024, 16, [16, 56, 56], ALL),        # 32 slices
+    (1, 100, 1025, 16, [16, 56, 56], ITERATION),
+    (1, 130, 2900, 16, [64], SEPARATE),           # half the CUs
+    (0, 60, 1600, 32, [16, 56, 56], ALL),
+    (0, 50, 1900, 32, [16, 56, 56], SEPARATE),
+    (0, 33, 2500, 32, [16] * 8, SEPARATE),        # 264 blocks: a nearly empty round
+    (0, 24, 4096, 32, [16] * 8, ALL),
+    (0, 24, 4097, 32, [16] * 8, SEPARATE),        # beyond 48 MiB
+    (1, 3, 2185, 160, [128], SEPARATE),           # sums beyond the LDS
+])
+def test_lloyd_forms(probe, bf16, heads, n, c, widths, want):
+    form, blocks, plan = probe("lloyd", bf16, heads, n, *[x for w in widths for x in (c, w)])
+    assert form == want
+    assert blocks == 1 if form == ALL else 0 <= blocks <= plan
+
+
+def test_one_block_never_runs_alone_over_many_slices(probe):
+    """One block per head and subspace takes more than 32 slices only where
+    such blocks keep most CUs busy, and blocks never outnumber the slabs."""
+    for bf16 in (0, 1):
+        for m in (1, 3, 8):
+            for heads in (1, 2, 7, 24, 33, 40, 86, 129, 140, 257, 300):
+                for n in (200, 321, 700, 1024, 1025, 2000, 5000):
+                    widths = _split(128, m)
+                    form, blocks, plan = probe("lloyd", bf16, heads, n, *[x for w in widths for x in (16, w)])
+                    assert 0 <= blocks <= plan
+                    assert (blocks == 0) == (form == SEPARATE)
+                    if blocks == 1 and n > 1024:
+                        pairs = heads * m
+                        rounds = -(-pairs // 256)
+                        assert pairs >= 256 if bf16 else pairs >= 0.6 * 256 * rounds

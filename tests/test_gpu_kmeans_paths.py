@@ -78,6 +78,10 @@ def _check(x, dtype, split, c_q, c_m, iters, init_q, init_k):
     ("bf16", 3, 321, (16, 56, 56), 31, (9, 33, 32)),    # eleven
     ("f32", 1, 29, (43, 42, 43), 7, (5, 29, 1)),        # one slice, odd pairs
     ("bf16", 300, 330, (8, 4, 4), 5, (3, 2, 7)),        # one block of 11 slices
+    ("bf16", 260, 700, (44, 42, 42), 5, (3, 2, 7)),     # one block each: an iteration, and all
+    ("bf16", 100, 1100, (8, 4, 4), 5, (3, 2, 7)),       # an iteration, 35 slices
+    ("f32", 60, 1100, (8, 4, 4), 5, (3, 2, 7)),         # all, 35 slices
+    ("f32", 45, 1100, (8, 4, 4), 5, (3, 2, 7)),         # separate
     ("bf16", 1, 700, (44, 42, 42), 86, (64, 90, 128)),  # sums about as large as the LDS
     ("f32", 2, 98304, (16, 24, 24), 9, (8, 8, 8)),      # either side of 48 MiB
     ("bf16", 2, 98305, (44, 42, 42), 9, (8, 8, 8)),
