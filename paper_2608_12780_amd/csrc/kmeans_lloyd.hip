@@ -97,8 +97,8 @@ __device__ __forceinline__ void load_rows(const LloydArgs &A, const LloydSub &K,
 #pragma unroll
   for (int k = 0; k < Rows::kSteps; ++k) {
     const T *x = x0 + static_cast<size_t>(min(k * Rows::kRowsPerStep + rr, rows - 1)) * A.ld;
-    if constexpr (sizeof(T) == 2) {  // pairs are 4-byte aligned
-      R.v[k][0] = *reinterpret_cast<const uint32_t *>(x);
+    if constexpr (sizeof(T) == 2) {
+      R.v[k][0] = *reinterpret_cast<const bf16_pair *>(x);
     } else {
       R.v[k][0] = __float_as_uint(x[0]);
       R.v[k][1] = two ? __float_as_uint(x[1]) : 0u;

@@ -69,10 +69,15 @@ __device__ __forceinline__ uint16_t to_bf16(float f) {
   return static_cast<uint16_t>(__builtin_bit_cast(uint32_t, r) & 0xFFFFu);
 }
 
+// A pair of bf16 channels, at any element: the caller's pointer may be at an odd
+// one (the hardware takes such loads whole; without the attribute the compiler
+// could take them for aligned).
+typedef uint32_t bf16_pair __attribute__((aligned(2)));
+
 // Channels c0 .. c0+7 of one bf16 row as four packed pairs, zero from dx on
 // and for invalid rows.  A whole group is one 16-byte load when the rows are
-// 16-byte aligned (vec), else four 4-byte loads (rows, ld, col0 and dx are
-// even, so no pair straddles dx).
+// 16-byte aligned (vec), else four loads of a pair (ld, col0 and dx are even, so
+// no pair straddles dx).
 __device__ __forceinline__ uint4 load_group8(const uint16_t *xrow, int c0, int dx, bool valid, bool vec) {
   uint4 v = make_uint4(0, 0, 0, 0);
   if (vec && c0 + 8 <= dx) {
@@ -82,7 +87,7 @@ __device__ __forceinline__ uint4 load_group8(const uint16_t *xrow, int c0, int d
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int c = c0 + 2 * q;
-      w[q] = valid && c < dx ? *reinterpret_cast<const uint32_t *>(xrow + c) : 0u;
+      w[q] = valid && c < dx ? *reinterpret_cast<const bf16_pair *>(xrow + c) : 0u;
     }
     v = make_uint4(w[0], w[1], w[2], w[3]);
   }

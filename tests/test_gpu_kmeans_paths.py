@@ -4,7 +4,8 @@ fp32), one centroid to more than the LDS holds, all iterations in one block
 (320 rows), several blocks of fused iterations, and the separate launches
 (sums beyond the LDS, or 48 MiB of rows), few and many row blocks per head
 (the finish kernel shares a row's sums among four waves from 8 blocks on),
-exact ties, and fp32 values outside the range of the matrix-core filter.
+exact ties, fp32 values outside the range of the matrix-core filter, and rows
+that start at any element of a buffer.
 """
 import numpy as np
 import pytest
@@ -127,3 +128,32 @@ def test_fp32_values_outside_the_filter(c_q):
         want = oracle.cluster_queries(x, c_q, 1, init)["assign"]
         got = layer.assign.cpu().numpy()
         assert np.array_equal(got, want), np.flatnonzero(got != want)[:20]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n,c_q,c_m", [
+    (300, 9, (8, 8, 8)),           # all iterations in one block
+    (1500, 33, (33, 32, 31)),      # fused iterations
+    (1500, 160, (200, 224, 224)),  # separate launches
+])
+def test_rows_from_any_element_on(dtype, n, c_q, c_m):
+    """Rows that start one element into their buffer give the same bits."""
+    heads, split, iters = 2, (16, 56, 56), 3
+    rng = np.random.default_rng(n)
+    x = _device(_rows(rng, heads, n, 128, dtype), dtype)
+    buf = torch.empty(x.numel() + 1, dtype=x.dtype, device="cuda")
+    y = buf[1:].view(x.shape)
+    y.copy_(x)
+    assert y.data_ptr() % 16 == x.element_size()
+    init_q = torch.from_numpy(_init(rng, n, c_q, heads)).cuda()
+    init_k = torch.from_numpy(_init(rng, n, max(c_m), heads, 3)).cuda()
+    G.say(f"[kmeans] rows at an odd element, {dtype} n={n} c_q={c_q}")
+    got = []
+    for t in (x, y):
+        layer = ScopeLayer(heads, n, 128, ((0, 16, 72), split), c_q, c_m, iters, 0.9, 1, dtype=dtype)
+        layer.cluster_queries(t, init_q)
+        layer.cluster_keys(t, init_k)
+        torch.cuda.synchronize()
+        got.append((layer.q_centroids, layer.assign, layer.perm, layer.k_centroids, layer.codes))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
