@@ -16,6 +16,7 @@ import oracle  # noqa: E402
 from paper_2608_12780_amd import inputs  # noqa: E402
 from paper_2608_12780_amd.layer import ScopeLayer  # noqa: E402
 
+import canonical  # noqa: E402
 import gpu_harness as G  # noqa: E402
 
 
@@ -160,13 +161,46 @@ def test_full_size_random_partition():
     G.say(f"[fullsize] random partition: head {head} bit-exact, k_head {int(gsel['k_head'][0])}")
 
 
+def _check_canonical(cfg, layer, q, k, iq, ik):
+    """The layer's clusterings of q and k, every head, against canonical.py."""
+    H, cut = cfg.heads, [0]
+    for m in range(3):
+        cut.append(cut[-1] + cfg.c_m * cfg.ranges[1][m])
+    books = lambda U, h, m: U[h, cut[m]:cut[m + 1]].view(cfg.c_m, -1)
+    codes = lambda h, m: (layer.codes[h].long() >> (10 * m)) & 1023
+    channels = [slice(o, o + n) for o, n in zip(*cfg.ranges)]
+    g, u = layer.assign.clone(), layer.q_centroids.clone()
+    U = layer.k_centroids.clone()
+    chains = 0
+    for h in range(H):
+        for m in range(3):
+            z, near = canonical.assign(k[h, :, channels[m]].float(), books(U, h, m))
+            assert torch.equal(z, codes(h, m)), ("codes", h, m)
+            chains += near
+    layer.cluster_queries(q, iq, iters=cfg.iters - 1)
+    layer.cluster_keys(k, ik, iters=cfg.iters - 1)
+    for h in range(H):
+        x = q[h].float()
+        want, near = canonical.assign(x, layer.q_centroids[h])
+        chains += near
+        assert torch.equal(want, g[h].long()), ("assign", h)
+        assert torch.equal(canonical.update(x, want, layer.q_centroids[h]), u[h]), ("centroids", h)
+        for m in range(3):
+            mean = canonical.update(k[h, :, channels[m]].float(), codes(h, m),
+                                    books(layer.k_centroids, h, m))
+            assert torch.equal(mean, books(U, h, m)), ("codebook", h, m)
+    G.say(f"[fullsize] canonical on {H} heads; {chains} of {4 * H * cfg.n} decided by the chains")
+
+
 @pytest.mark.parametrize("name", ["hy720", "wan720"])
 def test_full_size_every_head_matrix_core_assignment_is_canonical(name):
-    """Every head at full size: the bf16 clustering (matrix-core assignment,
-    exact by its filter and canonical re-score) against the same clustering
-    of the bf16 values widened to fp32, which takes the plain canonical
-    fp32 assignment kernel.  Query assignments, centroids, permutation and
-    key codes and centroids must be identical on all heads."""
+    """Every head at full size: the matrix-core clustering (exact by its
+    filter and canonical re-score) against the canonical assignment and update
+    in plain torch.  Queries: the last iteration, from the centroids of a run
+    one iteration shorter.  Keys: the codes against the returned codebooks,
+    and the codebooks as the means of the codes one iteration before.  And the
+    same clustering of the bf16 values widened to fp32 (three products
+    instead of two), whose outputs must be identical."""
     cfg = inputs.CONFIGS[name]
     G.say(f"[fullsize] {name}: every head, matrix-core vs canonical assignment")
     x = inputs.generate(cfg)
@@ -186,6 +220,8 @@ def test_full_size_every_head_matrix_core_assignment_is_canonical(name):
         assert int(layer.status.item()) == 0
         res[dtype] = {key: getattr(layer, key).cpu().numpy() for key in
                       ("assign", "counts", "perm", "q_centroids", "codes", "k_centroids")}
+        if dtype == "bf16":
+            _check_canonical(cfg, layer, q, k, iq, ik)
         del layer, q, k
         torch.cuda.empty_cache()
         G.say(f"[fullsize] {name}: {dtype} clustering done")
