@@ -70,7 +70,7 @@ def _check(x, dtype, split, c_q, c_m, iters, init_q, init_k):
     ("f32", 2, 256, (16, 24, 24), 8, (8, 8, 8)),        # one row block
     ("f32", 1, 2311, (17, 31, 33), 31, (33, 1, 32)),    # odd widths, many blocks
     ("f32", 5, 777, (15, 47, 49), 96, (40, 7, 64)),
-    ("f32", 3, 1500, (16, 56, 56), 65, (33, 32, 31)),   # the three in one pass
+    ("f32", 3, 1500, (16, 56, 56), 65, (33, 32, 31)),   # fused iterations
     ("f32", 2, 1200, (44, 42, 42), 300, (333, 20, 5)),  # beyond one block's LDS
     ("bf16", 1, 2311, (10, 2, 52), 1, (3, 2, 70)),
     ("bf16", 40, 300, (44, 42, 42), 33, (17, 64, 31)),  # few blocks per head
@@ -84,6 +84,14 @@ def _check(x, dtype, split, c_q, c_m, iters, init_q, init_k):
     ("f32", 60, 1100, (8, 4, 4), 5, (3, 2, 7)),         # all, 35 slices
     ("f32", 45, 1100, (8, 4, 4), 5, (3, 2, 7)),         # separate
     ("bf16", 1, 700, (44, 42, 42), 86, (64, 90, 128)),  # sums about as large as the LDS
+    # separate launches, sums beyond the LDS: queries and a lone fitting subspace
+    # by themselves, the three in one pass, several in one launch
+    ("f32", 2, 1100, (44, 42, 42), 160, (700, 20, 720)),
+    ("f32", 2, 1100, (16, 24, 24), 224, (32, 480, 448)),
+    ("f32", 2, 1100, (16, 56, 56), 129, (192, 220, 220)),
+    ("f32", 2, 1100, (44, 42, 42), 255, (320, 160, 150)),
+    ("f32", 2, 1100, (44, 42, 42), 130, (333, 300, 260)),
+    ("bf16", 2, 1100, (16, 56, 56), 161, (333, 260, 300)),
     ("f32", 2, 98304, (16, 24, 24), 9, (8, 8, 8)),      # either side of 48 MiB
     ("bf16", 2, 98305, (44, 42, 42), 9, (8, 8, 8)),
 ])
