@@ -344,20 +344,33 @@ def test_selection_with_heavily_shared_codes():
 
 
 def test_selection_when_one_dedup_part_overflows():
-    """Head 0's 40000 distinct codes all hash to the same part of the
-    distinct-code build (more than its table holds): that head falls back to
-    one entry per key; head 1 (ordinary codes) keeps the distinct list.  Both
-    must give the oracle's sets."""
+    """One part of head 0's distinct-code build gets more distinct codes than
+    its table has slots, the others a few each: that head falls back to one
+    entry per key; head 1 (ordinary codes) keeps the distinct list.  Both must
+    give the oracle's sets."""
     rng = np.random.default_rng(22)
     H, C, n, d, c_m = 2, 4, 40000, 64, (1024, 1024, 1024)
-    parts = (5 * n + 4 * 16384 - 1) // (4 * 16384)  # the build's part count
+    # the build's tables (80% full if every key has its own code), halved while
+    # a head's parts stay within 32 and all heads' within 256
+    parts_of = lambda slots: -(-5 * n // (4 * slots))
+    slots = 16384
+    while slots > 512 and parts_of(slots // 2) <= 32 and parts_of(slots // 2) * H <= 256:
+        slots //= 2
+    parts = parts_of(slots)
     cand = np.arange(0, 1 << 22, dtype=np.uint64)
-    hv = (cand * np.uint64(0x9E3779B1)) & np.uint64(0xFFFFFFFF)
-    same_part = cand[((hv * np.uint64(parts)) >> np.uint64(32)) == 0][:n].astype(np.uint32)
-    assert same_part.size == n
+    part_of = lambda c: ((c.astype(np.uint64) * np.uint64(0x9E3779B1) & np.uint64(0xFFFFFFFF))
+                         * np.uint64(parts)) >> np.uint64(32)
+    many = cand[part_of(cand) == parts // 2][:slots + 1].astype(np.uint32)
+    few = np.concatenate([cand[part_of(cand) == p][:50] for p in range(parts)
+                          if p != parts // 2]).astype(np.uint32)
     codes = np.empty((H, n), np.uint32)
-    codes[0] = rng.permutation(same_part)
+    rest = rng.choice(few, n - many.size - few.size)
+    codes[0] = rng.permutation(np.concatenate([many, few, rest]))
     codes[1] = rng.integers(0, 1 << 30, n, dtype=np.uint32) & np.uint32(0x000FFFFF)
+    # distinct codes per part: one beyond its slots in head 0, none in head 1
+    for h, full in ((0, 1), (1, 0)):
+        load = np.bincount(part_of(np.unique(codes[h])).astype(np.int64), minlength=parts)
+        assert (load > slots).sum() == full and (load > 0).all()
     tables = rng.standard_normal((H, C, sum(c_m))).astype(np.float32) * 3
     counts = rng.multinomial(n, np.ones(C) / C, size=H).astype(np.int32)
     _select_from_codes(tables, codes, counts, d, c_m, 0.7, (n + 9) // 10)
