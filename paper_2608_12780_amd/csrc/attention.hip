@@ -708,11 +708,10 @@ __global__ __launch_bounds__(256) void to_bf16_kernel(const float *__restrict__ 
 // A slot's estimated cost: its key tiles times the per-tile time of its wave
 // count (about 1.45x for 5-8 waves against 1-4) and of a second chunk's gathers
 // (about 1.15x).
-constexpr uint32_t kTileCost = 171u;
 __device__ __forceinline__ uint32_t slot_cost(const int4 &a, const int4 &b) {
   const int ta = key_tiles(a), tb = key_tiles(b);
   const int waves = (a.z + 31) / 32 + (b.z > 0 ? (b.z + 31) / 32 : 0);
-  const uint32_t per = waves > 4 ? (b.z > 0 ? 196u : kTileCost) : (b.z > 0 ? 135u : 118u);
+  const uint32_t per = waves > 4 ? (b.z > 0 ? 196u : 171u) : (b.z > 0 ? 135u : 118u);
   return static_cast<uint32_t>(ta > tb ? ta : tb) * per;
 }
 
@@ -883,12 +882,15 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
 // expensive blocks of each head start early and the cheap ones fill in
 // behind them, which shortens the launch's tail.
 constexpr int kPairMaxClusters = 2048;  // pairing up to this many clusters
+constexpr int kRemKeyBits = 25;         // n <= 2^24
 constexpr int kSortMaxSlots = 2048;     // cost-ordered work lists up to this many slots
 __global__ __launch_bounds__(1024) void attn_items_kernel(
     int n, int c_q, int items_per_head, int pair, int sort, const int32_t *__restrict__ offsets,
     const int32_t *__restrict__ sel_counts, int4 *items) {
   __shared__ int wtot[16];
-  __shared__ int rem_w[kPairMaxClusters], rem_r[kPairMaxClusters], ord[kPairMaxClusters];
+  // a remainder's waves and key count, (waves << 25) + keys, 0: no remainder
+  __shared__ uint32_t rem[kPairMaxClusters];
+  __shared__ int ord[kPairMaxClusters];
   __shared__ int bucket_n[kNW + 1], bucket_at[kNW + 1];
   __shared__ int4 seg[64];   // (A's first ordinal, B's first ordinal or -1, count, same bucket)
   __shared__ int seg_at[65], nseg, full_tot;
@@ -947,7 +949,7 @@ __global__ __launch_bounds__(1024) void attn_items_kernel(
       cnt = count_of(c);
       rsel = keys_of(c);
     }
-    const int k = cnt / kBM, rem = cnt - k * kBM;
+    const int k = cnt / kBM, rows = cnt - k * kBM;
     const int incl = wave_incl_scan(k);
     if (lane == 63) wtot[w] = incl;
     __syncthreads();
@@ -962,9 +964,9 @@ __global__ __launch_bounds__(1024) void attn_items_kernel(
     run += tot;
     // remainders, bucketed by wave count for pairing
     if (do_pair && c < c_q) {
-      rem_w[c] = rem > 0 ? (rem + 31) / 32 : 0;
-      rem_r[c] = rsel;
-      if (rem > 0) atomicAdd(&bucket_n[rem_w[c]], 1);
+      const int waves = (rows + 31) / 32;
+      rem[c] = rows > 0 ? (static_cast<uint32_t>(waves) << kRemKeyBits) + rsel : 0u;
+      if (rows > 0) atomicAdd(&bucket_n[waves], 1);
     }
   }
   if (t == 0) full_tot = run;
@@ -979,7 +981,7 @@ __global__ __launch_bounds__(1024) void attn_items_kernel(
         cnt = count_of(c);
         rsel = keys_of(c);
       }
-      const int rem = cnt % kBM, has = rem > 0 ? 1 : 0;
+      const int rows = cnt % kBM, has = rows > 0 ? 1 : 0;
       const int incl = wave_incl_scan(has);
       if (lane == 63) wtot[w] = incl;
       __syncthreads();
@@ -989,7 +991,7 @@ __global__ __launch_bounds__(1024) void attn_items_kernel(
         tot += wtot[i];
       }
       __syncthreads();
-      if (has) put(full_tot + at + base + incl - 1, make_int4(c, cnt - rem, rem, rsel), none);
+      if (has) put(full_tot + at + base + incl - 1, make_int4(c, cnt - rows, rows, rsel), none);
       at += tot;
     }
     for (int slot = full_tot + at + t; slot < items_per_head; slot += 1024) put(slot, none, none);
@@ -1006,14 +1008,24 @@ __global__ __launch_bounds__(1024) void attn_items_kernel(
     }
   }
   __syncthreads();
-  for (int c = t; c < c_q; c += 1024) {
-    const int wc = rem_w[c];
-    if (wc == 0) continue;
-    const int rc = rem_r[c];
-    int pos = bucket_at[wc];
-    for (int o = 0; o < c_q; ++o)
-      if (rem_w[o] == wc && (rem_r[o] < rc || (rem_r[o] == rc && o < c))) ++pos;
-    ord[pos] = c;
+  // (as many lanes share a cluster as the block has for each; with one thread per
+  // cluster and its waves and keys read and compared apart, this was most of the
+  // kernel: one head of 64 clusters 11.1 -> 4.6 us, 256 31.9 -> 10.2, 1000 138 -> 106)
+  int share = 1;
+  while (share < 64 && 2 * share * c_q <= 1024) share *= 2;
+  for (int c0 = 0; c0 < c_q; c0 += 1024 / share) {
+    const int c = c0 + t / share;
+    const uint32_t mine = c < c_q ? rem[c] : 0u;
+    int pos = 0;
+    if (mine) {
+#pragma unroll 4
+      for (int o = t % share; o < c_q; o += share) {
+        const uint32_t other = rem[o];
+        pos += other != 0u && (other < mine || (other == mine && o < c)) ? 1 : 0;
+      }
+    }
+    for (int k = share / 2; k > 0; k /= 2) pos += __shfl_xor(pos, k);
+    if (mine && t % share == 0) ord[pos] = c;
   }
   // the pairing plan (at most kNW * kNW segments), one thread
   if (t == 0) {
@@ -1055,8 +1067,8 @@ __global__ __launch_bounds__(1024) void attn_items_kernel(
   __syncthreads();
   const int total = seg_at[nseg];
   auto entry = [&](int c) {
-    const int cnt = count_of(c), rem = cnt % kBM;
-    return make_int4(c, cnt - rem, rem, rem_r[c]);
+    const int cnt = count_of(c), rows = cnt % kBM;
+    return make_int4(c, cnt - rows, rows, static_cast<int>(rem[c] & ((1u << kRemKeyBits) - 1u)));
   };
   for (int i = t; i < total; i += 1024) {
     int s = 0;
