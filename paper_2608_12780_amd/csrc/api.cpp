@@ -215,7 +215,7 @@ size_t attn_ws(const scope_shape *s, int c_q, void *base, size_t bytes, size_t *
   if (list) *list = cv.used;
   const bool bf16 = s->dtype == SCOPE_BF16;
   bool dma = bf16;  // the register-staged fp32 kernel has no order
-  if (scope::attention_copies_kv(s->n, s->d, bf16)) {
+  if (scope::attention_copies_kv(s->n, s->d, c_q, bf16)) {
     uint16_t *kv16 = cv.take<uint16_t>(2 * H * s->n * s->d);
     dma = cv.used <= bytes;
     if (dma) a.kv16 = kv16;

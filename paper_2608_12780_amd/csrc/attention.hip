@@ -1191,11 +1191,16 @@ hipError_t attention_items(int heads, int n, int c_q, bool pair, const int32_t *
   return hipGetLastError();
 }
 
-// Below 1024 tokens the copy's launch costs more than it saves (Tiny layer,
-// 256 tokens: 282 us with the copy, 279 us without; 8 heads x 6417 tokens,
-// d = 128: 1154 us with, 1219 us without).
-bool attention_copies_kv(int n, int d, bool bf16) {
-  return !bf16 && (d == 64 || d == 128) && n >= 1024 &&
+// The copies cost a pass over all of K and V and a launch, and save by the key:
+// in dense calls from 1,024 tokens on (one head of 1100, d = 128: 42 us with the
+// copies, 49 us without; d = 64: 33 and 34 us), in sparse ones, which keep from a
+// tenth to half of the keys, from where half of them pay at the latest (a tenth, a
+// quarter, half of the keys; d = 128, 2 x 3000: 29, 40, 58 us with, 26, 40, 62
+// without; 8 x 2200: 32, 40, 52 with, 27, 36, 52 without; d = 64, 8 x 6400: 45, 71,
+// 115 with, 40, 68, 117 without; 2 x 4000: 25, 35, 52 with, 21, 32, 51 without).
+bool attention_copies_kv(int n, int d, int c_q, bool bf16) {
+  const int from = c_q == 1 ? 1024 : d == 128 ? 3072 : 6144;
+  return !bf16 && (d == 64 || d == 128) && n >= from &&
          static_cast<uint64_t>(n) * d * 2 < (1ull << 32);
 }
 

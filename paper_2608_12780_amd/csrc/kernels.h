@@ -237,7 +237,7 @@ hipError_t attention_run(int heads, int n, int d, bool bf16, const void *q,
                          float scale, const AttnScratch &w, hipStream_t s);
 // Whether the workspace holds bf16 copies of K and V.  One head's copy is
 // addressed with 32-bit byte offsets.
-bool attention_copies_kv(int n, int d, bool bf16);
+bool attention_copies_kv(int n, int d, int c_q, bool bf16);
 // Whether the call has a block order of its own, and that order's entries.
 bool attention_ordered(int heads, int n, int d, int c_q);
 size_t attention_order_entries(int heads, int n, int d, int c_q);

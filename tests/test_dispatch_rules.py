@@ -47,6 +47,9 @@ int main(int argc, char **argv) {
     scope::km_accum_plan(nsub, col0, dx, C, p[0].heads, p[0].n, &plan);
     const scope::LloydForm f = scope::km_lloyd_form(p, nsub, plan);
     printf("%d %d %d", static_cast<int>(f.form), f.blocks, plan.blocks);
+  } else if (!strcmp(argv[1], "attention")) {  // heads n d c_q: copies of fp32 K and V, block order
+    const int heads = atoi(argv[2]), n = atoi(argv[3]), d = atoi(argv[4]), c_q = atoi(argv[5]);
+    printf("%d %d", scope::attention_copies_kv(n, d, c_q, false), scope::attention_ordered(heads, n, d, c_q));
   }
 }
 """
@@ -146,3 +149,18 @@ def test_one_block_never_runs_alone_over_many_slices(probe):
                         pairs = heads * m
                         rounds = -(-pairs // 256)
                         assert pairs >= 256 if bf16 else pairs >= 0.6 * 256 * rounds
+
+
+@pytest.mark.parametrize("heads,n,d,c_q,want", [
+    (1, 1023, 128, 1, (0, 0)), (1, 1024, 128, 1, (1, 0)), (1, 1024, 64, 1, (1, 0)),   # dense
+    (8, 3071, 128, 17, (0, 0)), (8, 3072, 128, 17, (1, 0)),                           # sparse
+    (8, 6143, 64, 37, (0, 0)), (8, 6144, 64, 37, (1, 0)),
+    (1, 4095, 128, 1, (1, 0)), (1, 4096, 128, 1, (1, 1)),
+    (4, 8192, 128, 1, (1, 1)), (4, 8193, 128, 1, (1, 0)),      # 128 slots, 132 ...
+    (8, 8192, 128, 1, (1, 0)), (8, 8193, 128, 1, (1, 1)),      # ... 256, 264
+    (8, 16383, 64, 37, (1, 0)), (8, 16384, 64, 37, (1, 1)),
+    (24, 118800, 128, 256, (1, 0)), (8, 65536, 128, 256, (1, 1)), (8, 65537, 128, 256, (1, 0)),
+    (1, 1 << 24, 128, 256, (0, 0)),
+])
+def test_attention_forms(probe, heads, n, d, c_q, want):
+    assert tuple(probe("attention", heads, n, d, c_q)) == want
