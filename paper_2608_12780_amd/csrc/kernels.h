@@ -142,6 +142,8 @@ hipError_t km_accum(const AccPlan &plan, const void *x, bool bf16, size_t x_hs,
 // matrix-core codebooks too (not needed after a call's last update).
 hipError_t km_finish(const AccPlan &plan, const KmProblem *p, int nsub, bool prepare,
                      const long long *slab, const int32_t *cslab, hipStream_t s);
+// Whether km_finish has four waves share a row's slabs instead of one take them all.
+bool km_finish_shared(const AccPlan &plan, int heads);
 // Largest |x| (exclusive) for which n rows' fixed-point sums are exact.
 float km_range_limit(int n);
 // Small problems: assignment and update of an iteration in one launch, or all

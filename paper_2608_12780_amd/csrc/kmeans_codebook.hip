@@ -273,12 +273,21 @@ hipError_t km_init(const KmProblem *p, int nsub, bool warm, const int32_t *init,
   return hipGetLastError();
 }
 
+// From 8 slabs per head on, four waves share a row's slabs, as long as the chip
+// holds the waves of all rows at once (256 CUs of 32): beyond, a wave per row
+// keeps it as full with a quarter of the blocks.  Whole key clusterings, 209
+// centroids per subspace of 64 channels, a wave per row against four: 31 heads x
+// 19721 745 and 834 us, 16 x 2600 200 and 248 us; on the other side queries, 32
+// centroids, one head x 42000 175 and 135 us.
+bool km_finish_shared(const AccPlan &plan, int heads) {
+  return plan.blocks >= 8 && static_cast<long long>(plan.SC) * heads <= 2048;
+}
+
 hipError_t km_finish(const AccPlan &plan, const KmProblem *p, int nsub, bool prepare,
                      const long long *slab, const int32_t *cslab, hipStream_t s) {
   int rows = 0;
   const Codebooks B = codebooks(p, nsub, prepare, &rows);
-  // from 8 slabs per head on, four waves share a row's slabs
-  if (plan.blocks >= 8)
+  if (km_finish_shared(plan, p[0].heads))
     hipLaunchKernelGGL(km_finish_kernel<true>, dim3(rows, p[0].heads, nsub), dim3(kRowThreads), 0,
                        s, B, plan.S, plan.SC, plan.blocks, slab, cslab);
   else

@@ -50,6 +50,17 @@ int main(int argc, char **argv) {
   } else if (!strcmp(argv[1], "attention")) {  // heads n d c_q: copies of fp32 K and V, block order
     const int heads = atoi(argv[2]), n = atoi(argv[3]), d = atoi(argv[4]), c_q = atoi(argv[5]);
     printf("%d %d", scope::attention_copies_kv(n, d, c_q, false), scope::attention_ordered(heads, n, d, c_q));
+  } else if (!strcmp(argv[1], "finish")) {  // heads n C nsub dx
+    const int heads = atoi(argv[2]), n = atoi(argv[3]), nsub = atoi(argv[5]), w = atoi(argv[6]);
+    int col0[8], dx[8], C[8];
+    for (int m = 0; m < nsub; ++m) {
+      col0[m] = m * w;
+      dx[m] = w;
+      C[m] = atoi(argv[4]);
+    }
+    scope::AccPlan plan;
+    scope::km_accum_plan(nsub, col0, dx, C, heads, n, &plan);
+    printf("%d %d", plan.blocks, scope::km_finish_shared(plan, heads));
   }
 }
 """
@@ -164,3 +175,14 @@ def test_one_block_never_runs_alone_over_many_slices(probe):
 ])
 def test_attention_forms(probe, heads, n, d, c_q, want):
     assert tuple(probe("attention", heads, n, d, c_q)) == want
+
+
+@pytest.mark.parametrize("heads,n,c,nsub,dx,want", [
+    (1, 42000, 32, 1, 128, 1),
+    (16, 19721, 128, 1, 128, 1), (16, 19721, 129, 1, 128, 0),   # 2,048 rows, 2,064
+    (31, 19721, 209, 3, 20, 0), (16, 2600, 209, 3, 20, 0),
+    (40, 42000, 32, 1, 128, 0),                                 # fewer than 8 slabs
+])
+def test_slabs_of_a_row_are_shared_while_the_chip_has_room(probe, heads, n, c, nsub, dx, want):
+    blocks, shared = probe("finish", heads, n, c, nsub, dx)
+    assert shared == want and shared == (blocks >= 8 and heads * c * nsub <= 2048)
