@@ -875,7 +875,8 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(
 // within a bucket, bucket w (largest first) takes partners from bucket
 // min(8 - w, w) down to 1 in key-count order, so paired chunks run similar
 // numbers of key tiles.  Remainders left without a partner (among them every
-// remainder of 8 waves) run alone.  With `sort` (where attn_plan_kernel does
+// remainder of 8 waves) run alone, and with d all of them where
+// attention_runs_alone says so of as many heads like this one.  With `sort` (where attn_plan_kernel does
 // not order them) and up to kSortMaxSlots slots per head, the head's slots are
 // then reordered by estimated cost, largest first (ties
 // keep their order, so a cluster's full chunks stay adjacent): the
@@ -885,22 +886,22 @@ constexpr int kPairMaxClusters = 2048;  // pairing up to this many clusters
 constexpr int kRemKeyBits = 25;         // n <= 2^24
 constexpr int kSortMaxSlots = 2048;     // cost-ordered work lists up to this many slots
 __global__ __launch_bounds__(1024) void attn_items_kernel(
-    int n, int c_q, int items_per_head, int pair, int sort, const int32_t *__restrict__ offsets,
-    const int32_t *__restrict__ sel_counts, int4 *items) {
-  __shared__ int wtot[16];
+    int n, int c_q, int items_per_head, int pair, int d, int sort,
+    const int32_t *__restrict__ offsets, const int32_t *__restrict__ sel_counts, int4 *items) {
+  __shared__ int2 wtot[16];
   // a remainder's waves and key count, (waves << 25) + keys, 0: no remainder
   __shared__ uint32_t rem[kPairMaxClusters];
   __shared__ int ord[kPairMaxClusters];
-  __shared__ int bucket_n[kNW + 1], bucket_at[kNW + 1];
+  __shared__ int bucket_n[kNW + 1];
   __shared__ int4 seg[64];   // (A's first ordinal, B's first ordinal or -1, count, same bucket)
-  __shared__ int seg_at[65], nseg, full_tot;
+  __shared__ int seg_at[65], nseg;
   __shared__ int4 staged[2 * kSortMaxSlots];
   __shared__ unsigned long long cost[kSortMaxSlots];
   const int h = blockIdx.x, t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int32_t *off = offsets + static_cast<size_t>(h) * (c_q + 1);
   const int32_t *scnt = sel_counts + static_cast<size_t>(h) * c_q;
   int4 *out = items + static_cast<size_t>(h) * items_per_head * 2;
-  const bool do_pair = pair && c_q <= kPairMaxClusters;
+  const bool may_pair = pair && c_q <= kPairMaxClusters;
   const bool sorted = sort && items_per_head <= kSortMaxSlots;
   auto count_of = [&](int c) { return min(max(off[c + 1] - off[c], 0), n); };
   auto keys_of = [&](int c) { return min(max(scnt[c], 0), n); };
@@ -940,8 +941,30 @@ __global__ __launch_bounds__(1024) void attn_items_kernel(
   const int4 none = make_int4(0, 0, 0, 0);
   if (t <= kNW) bucket_n[t] = 0;
   __syncthreads();
-  // full chunks, in cluster order
+  // full chunks, in cluster order: of 1,024 clusters, the full chunks (x) and the
+  // remainders (y) before each and of all
+  auto prefix = [&](int k, bool has, int2 *tot) {
+    const unsigned long long some = __ballot(has);
+    const int incl = wave_incl_scan(k);
+    if (lane == 63) wtot[w] = make_int2(incl, __popcll(some));
+    __syncthreads();
+    int2 base = make_int2(incl - k, __popcll(some & ((1ull << lane) - 1ull)));
+    *tot = make_int2(0, 0);
+    for (int i = 0; i < 16; ++i) {
+      const int2 v = wtot[i];
+      if (i < w) {
+        base.x += v.x;
+        base.y += v.y;
+      }
+      tot->x += v.x;
+      tot->y += v.y;
+    }
+    __syncthreads();
+    return base;
+  };
   int run = 0;
+  int own_at = 0, remainders = 0;  // of the last 1,024 clusters: this thread's remainder, and how many
+  int4 own = none;
   for (int c0 = 0; c0 < c_q; c0 += 1024) {
     const int c = c0 + t;
     int cnt = 0, rsel = 0;
@@ -950,69 +973,62 @@ __global__ __launch_bounds__(1024) void attn_items_kernel(
       rsel = keys_of(c);
     }
     const int k = cnt / kBM, rows = cnt - k * kBM;
-    const int incl = wave_incl_scan(k);
-    if (lane == 63) wtot[w] = incl;
-    __syncthreads();
-    int base = 0, tot = 0;
-    for (int i = 0; i < 16; ++i) {
-      if (i < w) base += wtot[i];
-      tot += wtot[i];
-    }
-    __syncthreads();
-    const int first = run + base + incl - k;
+    int2 tot;
+    const int2 before = prefix(k, rows > 0, &tot);
+    const int first = run + before.x;
     for (int q = 0; q < k; ++q) put(first + q, make_int4(c, q * kBM, kBM, rsel), none);
-    run += tot;
+    run += tot.x;
+    own = make_int4(c, cnt - rows, rows, rsel);
+    own_at = before.y;
+    remainders = tot.y;
     // remainders, bucketed by wave count for pairing
-    if (do_pair && c < c_q) {
+    if (may_pair && c < c_q) {
       const int waves = (rows + 31) / 32;
       rem[c] = rows > 0 ? (static_cast<uint32_t>(waves) << kRemKeyBits) + rsel : 0u;
       if (rows > 0) atomicAdd(&bucket_n[waves], 1);
     }
   }
-  if (t == 0) full_tot = run;
   __syncthreads();
-  if (!do_pair) {
+  int rem_tot = 0, rem_waves = 0;
+#pragma unroll
+  for (int b = 1; b <= kNW; ++b) {
+    const int some = bucket_n[b];
+    rem_tot += some;
+    rem_waves += b * some;
+  }
+  const bool alone = d && attention_runs_alone(d, static_cast<long long>(run + rem_tot) * gridDim.x,
+                                               static_cast<long long>(kNW * run + rem_waves) * gridDim.x);
+  if (!may_pair || alone) {
     // remainders alone, in cluster order, after the full chunks
     int at = 0;
-    for (int c0 = 0; c0 < c_q; c0 += 1024) {
+    if (c_q <= 1024) {
+      if (own.z > 0) put(run + own_at, own, none);
+      at = remainders;
+    }
+    for (int c0 = c_q <= 1024 ? c_q : 0; c0 < c_q; c0 += 1024) {
       const int c = c0 + t;
       int cnt = 0, rsel = 0;
       if (c < c_q) {
         cnt = count_of(c);
         rsel = keys_of(c);
       }
-      const int rows = cnt % kBM, has = rows > 0 ? 1 : 0;
-      const int incl = wave_incl_scan(has);
-      if (lane == 63) wtot[w] = incl;
-      __syncthreads();
-      int base = 0, tot = 0;
-      for (int i = 0; i < 16; ++i) {
-        if (i < w) base += wtot[i];
-        tot += wtot[i];
-      }
-      __syncthreads();
-      if (has) put(full_tot + at + base + incl - 1, make_int4(c, cnt - rows, rows, rsel), none);
-      at += tot;
+      const int rows = cnt % kBM;
+      int2 tot;
+      const int2 before = prefix(0, rows > 0, &tot);
+      if (rows > 0) put(run + at + before.y, make_int4(c, cnt - rows, rows, rsel), none);
+      at += tot.y;
     }
-    for (int slot = full_tot + at + t; slot < items_per_head; slot += 1024) put(slot, none, none);
-    emit_sorted(min(full_tot + at, items_per_head));
+    for (int slot = run + at + t; slot < items_per_head; slot += 1024) put(slot, none, none);
+    emit_sorted(min(run + at, items_per_head));
     return;
   }
   // ordinal of each remainder within (bucket ascending, keys ascending,
   // cluster ascending)
-  if (t == 0) {
-    int a = 0;
-    for (int b = 0; b <= kNW; ++b) {
-      bucket_at[b] = a;
-      a += b == 0 ? 0 : bucket_n[b];
-    }
-  }
-  __syncthreads();
   // (as many lanes share a cluster as the block has for each; with one thread per
   // cluster and its waves and keys read and compared apart, this was most of the
   // kernel: one head of 64 clusters 11.1 -> 4.6 us, 256 31.9 -> 10.2, 1000 138 -> 106)
   int share = 1;
-  while (share < 64 && 2 * share * c_q <= 1024) share *= 2;
+  while (share < 64 && share < c_q && 2 * share * c_q <= 1024) share *= 2;
   for (int c0 = 0; c0 < c_q; c0 += 1024 / share) {
     const int c = c0 + t / share;
     const uint32_t mine = c < c_q ? rem[c] : 0u;
@@ -1030,9 +1046,10 @@ __global__ __launch_bounds__(1024) void attn_items_kernel(
   // the pairing plan (at most kNW * kNW segments), one thread
   if (t == 0) {
     int nxt[kNW + 1], left[kNW + 1];
-    for (int b = 0; b <= kNW; ++b) {
-      nxt[b] = bucket_at[b];
-      left[b] = b == 0 ? 0 : bucket_n[b];
+    nxt[0] = left[0] = 0;
+    for (int b = 1; b <= kNW; ++b) {
+      nxt[b] = nxt[b - 1] + left[b - 1];  // where the bucket starts
+      left[b] = bucket_n[b];
     }
     int ns = 0;
     for (int wa = kNW; wa >= 1; --wa) {
@@ -1076,15 +1093,15 @@ __global__ __launch_bounds__(1024) void attn_items_kernel(
     const int4 g = seg[s];
     const int j = i - seg_at[s];
     if (g.y < 0) {
-      put(full_tot + i, entry(ord[g.x + j]), none);
+      put(run + i, entry(ord[g.x + j]), none);
     } else if (g.w) {
-      put(full_tot + i, entry(ord[g.x + 2 * j]), entry(ord[g.x + 2 * j + 1]));
+      put(run + i, entry(ord[g.x + 2 * j]), entry(ord[g.x + 2 * j + 1]));
     } else {
-      put(full_tot + i, entry(ord[g.x + j]), entry(ord[g.y + j]));
+      put(run + i, entry(ord[g.x + j]), entry(ord[g.y + j]));
     }
   }
-  for (int slot = full_tot + total + t; slot < items_per_head; slot += 1024) put(slot, none, none);
-  emit_sorted(min(full_tot + total, items_per_head));
+  for (int slot = run + total + t; slot < items_per_head; slot += 1024) put(slot, none, none);
+  emit_sorted(min(run + total, items_per_head));
 }
 
 // Blocks that the chip holds at once (256 CUs; two blocks per CU at d = 64).
@@ -1187,7 +1204,7 @@ int attn_items_per_head(int n, int c_q) { return (n + kBM - 1) / kBM + c_q; }
 hipError_t attention_items(int heads, int n, int c_q, bool pair, const int32_t *offsets,
                            const int32_t *sel_counts, int4 *items, hipStream_t s) {
   hipLaunchKernelGGL(attn_items_kernel, dim3(heads), dim3(1024), 0, s, n, c_q,
-                     attn_items_per_head(n, c_q), pair ? 1 : 0, 1, offsets, sel_counts, items);
+                     attn_items_per_head(n, c_q), pair ? 1 : 0, 0, 1, offsets, sel_counts, items);
   return hipGetLastError();
 }
 
@@ -1233,10 +1250,11 @@ hipError_t attention_run(int heads, int n, int d, bool bf16, const void *q,
                          const int32_t *sel_counts, const int32_t *sel_idx,
                          float scale, const AttnScratch &w, hipStream_t s) {
   const int iph = attn_items_per_head(n, c_q);
-  // remainder chunks share blocks only in the LDS-DMA kernel
-  const int pair = bf16 || w.kv16 ? 1 : 0;
+  // remainder chunks share blocks only in the LDS-DMA kernel (with a block order
+  // always: fewer slots leave more of them room to run as halves)
+  const int pair = c_q > 1 && (bf16 || w.kv16) ? 1 : 0;
   hipLaunchKernelGGL(attn_items_kernel, dim3(heads), dim3(1024), 0, s, n, c_q,
-                     iph, pair, w.order ? 0 : 1, offsets, sel_counts, w.items);
+                     iph, pair, w.order ? 0 : d, w.order ? 0 : 1, offsets, sel_counts, w.items);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const float sl2 = scale * 1.4426950408889634f;

@@ -237,6 +237,19 @@ hipError_t attention_run(int heads, int n, int d, bool bf16, const void *q,
                          const int32_t *offsets, const int32_t *perm,
                          const int32_t *sel_counts, const int32_t *sel_idx,
                          float scale, const AttnScratch &w, hipStream_t s);
+// Whether the remainder chunks of a call without a block order run alone, given
+// its work slots and their waves if they do.  Pairs spare gathers and blocks, but
+// a pair's block takes longer than two that share a CU (d = 64) or have one each.
+// Alone is better while the slots are hardly more than the chip holds and the
+// waves few: two per SIMD at d = 64, one for every two SIMDs at d = 128.  Whole
+// calls, alone and paired: d = 64, 8 heads x 800 tokens x 13 clusters 14.5 and 19.6
+// us, 16 x 1372 x 22 24.3 and 32.7 us, 3 x 12512 x 211 (633 slots, 1460 waves) 176
+// and 224 us, on the other side 9 x 11628 x 42 (599, 3470) 271 and 237 us; d = 128,
+// fp32, 1 x 6417 x 106 (106, 420) 89 and 110 us, on the other side bf16 9 x 2835 x
+// 22 (201, 900) 75 and 61 us.
+inline __host__ __device__ bool attention_runs_alone(int d, long long slots, long long waves) {
+  return d == 64 ? slots <= 768 && waves <= 2048 : slots <= 256 && waves <= 512;
+}
 // Whether the workspace holds bf16 copies of K and V.  One head's copy is
 // addressed with 32-bit byte offsets.
 bool attention_copies_kv(int n, int d, int c_q, bool bf16);

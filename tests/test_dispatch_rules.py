@@ -50,6 +50,8 @@ int main(int argc, char **argv) {
   } else if (!strcmp(argv[1], "attention")) {  // heads n d c_q: copies of fp32 K and V, block order
     const int heads = atoi(argv[2]), n = atoi(argv[3]), d = atoi(argv[4]), c_q = atoi(argv[5]);
     printf("%d %d", scope::attention_copies_kv(n, d, c_q, false), scope::attention_ordered(heads, n, d, c_q));
+  } else if (!strcmp(argv[1], "alone")) {  // d slots waves
+    printf("%d", scope::attention_runs_alone(atoi(argv[2]), atoll(argv[3]), atoll(argv[4])));
   } else if (!strcmp(argv[1], "finish")) {  // heads n C nsub dx
     const int heads = atoi(argv[2]), n = atoi(argv[3]), nsub = atoi(argv[5]), w = atoi(argv[6]);
     int col0[8], dx[8], C[8];
@@ -175,6 +177,19 @@ def test_one_block_never_runs_alone_over_many_slices(probe):
 ])
 def test_attention_forms(probe, heads, n, d, c_q, want):
     assert tuple(probe("attention", heads, n, d, c_q)) == want
+
+
+@pytest.mark.parametrize("d,slots,waves,want", [
+    # measured on both sides: calls whose remainders are faster alone ...
+    (64, 57, 143, 1), (64, 351, 1194, 1), (64, 525, 1207, 1), (64, 633, 1456, 1), (64, 420, 2048, 1),
+    (128, 109, 229, 1), (128, 226, 452, 1), (128, 256, 512, 1),
+    # ... and paired
+    (64, 557, 3286, 0), (64, 799, 2317, 0), (64, 769, 1538, 0), (64, 600, 2049, 0),
+    (128, 201, 904, 0), (128, 226, 1446, 0), (128, 257, 500, 0), (128, 128, 513, 0),
+    (64, 1 << 40, 1 << 43, 0), (128, 1 << 40, 1 << 43, 0),
+])
+def test_remainders_alone(probe, d, slots, waves, want):
+    assert probe("alone", d, slots, waves) == [want]
 
 
 @pytest.mark.parametrize("heads,n,c,nsub,dx,want", [

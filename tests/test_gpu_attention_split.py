@@ -110,6 +110,36 @@ def test_split_slots(name):
     assert torch.equal(_bits(out[0]), _bits(out[1]))
 
 
+# few slots and waves run a block each, more of them in pairs: of these heads one
+# alone is on the one side and `heads` of them on the other
+@pytest.mark.parametrize("heads,sizes,d,dtype", [
+    (60, [100] * 13, 64, "bf16"),
+    (9, [300, 1, 0, 256, 33, 517, 64] * 2, 64, "bf16"),
+    (2, [3] * 700, 64, "bf16"),
+    (3, [2] * 1024, 64, "bf16"),                # paired either way
+    (6, [64] * 50, 128, "f32"),
+    (4, [300, 1, 0, 256, 33, 517, 64], 128, "bf16"),
+])
+def test_remainders_alone_or_paired(heads, sizes, d, dtype):
+    n, c_q = sum(sizes), len(sizes)
+    G.say(f"[split] alone or paired: heads={heads} n={n} clusters={c_q} d={d} {dtype}")
+    keys = [(37 * i + 5) % n + 1 for i in range(c_q)]
+    shape, q, k, v, offsets, perm, counts, sel = _problem(heads, sizes, keys, d, dtype)
+    many = _attend(shape, q, k, v, offsets, perm, counts, sel)
+    off = (0, d // 4, d // 2)
+    shape1 = B.make_shape(1, n, d, shape.dtype, (off, (d // 4, d // 4, d // 2)))
+    for h in (0, heads - 1):
+        one = _attend(shape1, *(x[h:h + 1].contiguous() for x in (q, k, v, offsets, perm, counts, sel)))
+        for o in one:
+            assert torch.equal(_bits(o[0]), _bits(many[0][h]))
+    qd, kd, vd = (x[0].to(torch.bfloat16).double() for x in (q, k, v))
+    for c in range(0, c_q, max(1, c_q // 20)):
+        rows, kk = perm[0, offsets[0, c]:offsets[0, c + 1]], sel[0, c, :keys[c]].long()
+        if rows.numel():
+            ref = torch.softmax(qd[rows] @ kd[kk].T / math.sqrt(d), 1) @ vd[kk]
+            assert float((many[0][0, rows].double() - ref).abs().max()) <= G.MAX_ABS
+
+
 @pytest.mark.parametrize("d,dtype", [(128, "bf16"), (64, "bf16"), (128, "f32")])
 def test_not_finite_values_stay_where_they_are(d, dtype):
     heads, n = 2, 4608
