@@ -1208,17 +1208,23 @@ hipError_t attention_items(int heads, int n, int c_q, bool pair, const int32_t *
   return hipGetLastError();
 }
 
-// The copies cost a pass over all of K and V and a launch, and save by the key:
-// in dense calls from 1,024 tokens on (one head of 1100, d = 128: 42 us with the
-// copies, 49 us without; d = 64: 33 and 34 us), in sparse ones, which keep from a
-// tenth to half of the keys, from where half of them pay at the latest (a tenth, a
-// quarter, half of the keys; d = 128, 2 x 3000: 29, 40, 58 us with, 26, 40, 62
-// without; 8 x 2200: 32, 40, 52 with, 27, 36, 52 without; d = 64, 8 x 6400: 45, 71,
-// 115 with, 40, 68, 117 without; 2 x 4000: 25, 35, 52 with, 21, 32, 51 without).
+// The copies cost a pass over all of K and V and a launch, and save by the gathered
+// key.  Dense calls make them from 1,024 tokens on (one head of 1100, d = 128: 42 us
+// with the copies, 49 us without; d = 64: 33 and 34 us).  Sparse ones keep from a
+// tenth to half of the keys and gather once per chunk of queries, at most n / kBM +
+// c_q of them; they make them
+// - from where half of the keys pay at the latest (a tenth, a quarter, half of the
+//   keys; d = 128, 2 x 3000: 29, 40, 58 us with, 26, 40, 62 without; d = 64, 8 x
+//   6400: 45, 71, 115 with, 40, 68, 117 without; 2 x 4000: 25, 35, 52 with, 21, 32,
+//   51 without);
+// - with so many chunks that few keys pay too (d = 128, an eighth of the keys, 15 x
+//   2688 tokens in 41 clusters 52 us with, 55 without, half of them, 6 x 2496 in 39
+//   59 and 70 us; on the other side 10 x 3420 in 11, a seventh, 44 and 39 us; d = 64,
+//   a fifth, 27 x 3861 in 89 82 and 105 us, half, 5 x 5022 in 225 95 and 140 us; on
+//   the other side 9 x 5016 in 49, a seventh, 43 and 40 us).
 bool attention_copies_kv(int n, int d, int c_q, bool bf16) {
-  const int from = c_q == 1 ? 1024 : d == 128 ? 3072 : 6144;
-  return !bf16 && (d == 64 || d == 128) && n >= from &&
-         static_cast<uint64_t>(n) * d * 2 < (1ull << 32);
+  if (bf16 || (d != 64 && d != 128) || n < 1024 || static_cast<uint64_t>(n) * d * 2 >= (1ull << 32)) return false;
+  return c_q == 1 || n >= (d == 128 ? 3072 : 6144) || n / kBM + c_q >= (d == 128 ? 48 : 96);
 }
 
 // Dense calls (one cluster) from 4,096 tokens on: one head of 4,224 tokens, d =

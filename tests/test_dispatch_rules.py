@@ -168,6 +168,8 @@ def test_one_block_never_runs_alone_over_many_slices(probe):
     (1, 1023, 128, 1, (0, 0)), (1, 1024, 128, 1, (1, 0)), (1, 1024, 64, 1, (1, 0)),   # dense
     (8, 3071, 128, 17, (0, 0)), (8, 3072, 128, 17, (1, 0)),                           # sparse
     (8, 6143, 64, 37, (0, 0)), (8, 6144, 64, 37, (1, 0)),
+    (8, 2304, 128, 38, (0, 0)), (8, 2304, 128, 39, (1, 0)),                           # many chunks
+    (8, 2304, 64, 86, (0, 0)), (8, 2304, 64, 87, (1, 0)), (8, 1023, 128, 512, (0, 0)),
     (1, 4095, 128, 1, (1, 0)), (1, 4096, 128, 1, (1, 1)),
     (4, 8192, 128, 1, (1, 1)), (4, 8193, 128, 1, (1, 0)),      # 128 slots, 132 ...
     (8, 8192, 128, 1, (1, 0)), (8, 8193, 128, 1, (1, 1)),      # ... 256, 264

@@ -118,6 +118,8 @@ def test_split_slots(name):
     (2, [3] * 700, 64, "bf16"),
     (3, [2] * 1024, 64, "bf16"),                # paired either way
     (6, [64] * 50, 128, "f32"),
+    (13, [24] * 45, 128, "f32"),                # copies of K and V for the many chunks
+    (9, [12] * 92, 64, "f32"),
     (4, [300, 1, 0, 256, 33, 517, 64], 128, "bf16"),
 ])
 def test_remainders_alone_or_paired(heads, sizes, d, dtype):
