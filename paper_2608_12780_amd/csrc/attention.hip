@@ -659,7 +659,7 @@ __device__ __forceinline__ void attn_dma_body(
 }
 
 // d = 128: 192 registers, one block (two waves per SIMD) per CU.  d = 64 is
-// bound by the softmax's vector instructions (per tile and wave about 880
+// bound by the softmax's vector instructions (per tile and wave about 950
 // cycles against 512 of MFMA), so two blocks share a CU.
 template <int D, bool BF16IO>
 __global__ __launch_bounds__(kNW * 64)
@@ -916,7 +916,8 @@ __global__ __launch_bounds__(1024) void attn_items_kernel(
       }
     }
   };
-  // the staged slots, largest estimated cost first.  The first `used` slots hold chunks; the empty ones after them stay in place.
+  // the staged slots, largest estimated cost first.  The first `used` slots hold
+  // chunks; the empty ones after them stay in place.
   auto emit_sorted = [&](int used) {
     if (!sorted) return;
     __syncthreads();

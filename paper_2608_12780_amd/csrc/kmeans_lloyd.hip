@@ -79,7 +79,7 @@ __device__ __host__ __forceinline__ size_t lloyd_lds(int C, int cpad, int dx, in
 // the lanes of a row holding a pair of channels each.
 template <int DXP, typename T>
 struct SliceRows {
-  static constexpr int kRowsPerStep = 128 / DXP < 64 / (DXP / 2) ? 128 / DXP : 64 / (DXP / 2);
+  static constexpr int kRowsPerStep = 128 / DXP;
   static constexpr int kSteps = 32 / kRowsPerStep;
   static constexpr int kWords = sizeof(T) == 2 ? 1 : 2;  // registers of a pair
   uint32_t v[kSteps][kWords];

@@ -15,8 +15,8 @@
 //   |-2 a_r - c_r| <= beta = 2|x| (E + 8 DXP 2^-24 Nmax)
 //                            + 2^-23 ((2 DXP + 1) numax + 2.02 |x| Nmax)
 // (E >= |u_r - hi_r - lo_r|, Nmax >= |hi_r| + |lo_r| and |u_r|, numax >=
-// |nu_r|; about twice the terms derived, for slack), inflated by 1%, and the
-// canonical argmin r* satisfies a_{r*} >= max_r a_r - beta.
+// |nu_r|; twice the terms derived in numax, more in the others, for slack),
+// inflated by 1%, and the canonical argmin r* satisfies a_{r*} >= max_r a_r - beta.
 //
 // One pass keeps, per point, the three largest a_r with the centroid index
 // packed into the low mantissa bits (IB bits; this moves a value by less
@@ -33,7 +33,8 @@
 // joins the two: xh hi + xh lo + xl hi.  What is left out is xl lo (at most
 // 2^-16 (1 + 2^-8)^2 |x| |u|) and xr u (2^-16 |x| |u|), so beta grows by
 // 2 * 2^-15 * 1.02 |x| Nmax, and by 2^-110 (|x| + Nmax) where tiny terms are
-// flushed; the constants above hold for 3 DXP products too.  Points or
+// flushed; the constants above hold for 3 DXP products too (4/3 of the terms
+// derived in numax, twice in |x| Nmax).  Points or
 // codebooks so large that this arithmetic could overflow, or that are not
 // finite, scan every centroid canonically.  With one thread per point and
 // fma chains on the vector units a pass over 8 heads x 6417 points x 64
@@ -254,8 +255,8 @@ constexpr float kNormLimit = 1e18f;      // |x|
 constexpr float kNuLimit = 1e30f;        // |u|^2
 
 // Canonical assignment of one fp32 point by a scan over every centroid:
-// strict comparisons in ascending order from +inf, so scores that are not
-// finite never win and a point without a finite score keeps centroid 0.
+// strict comparisons in ascending order from +inf, so NaN and +inf never win, the
+// first -inf does, and a point without a lower score keeps centroid 0.
 template <typename T>
 __device__ __forceinline__ int canon_scan(const T *xr, const float *u, const float *nu, int C, int dx) {
   float best = INFINITY;
