@@ -258,6 +258,7 @@ __global__ __launch_bounds__(64 * kWaves<T>) void km_assign_mfma_part_kernel(
 // value lies outside it has at most two candidates, both listed; the listed
 // candidates are re-scored canonically if there are several, and only a point
 // with three candidates in one chunk (or more) scans every centroid.
+constexpr int kOwnScans = 8;
 template <int DXP, typename T>
 __global__ __launch_bounds__(256) void km_assign_decide_kernel(
     const T *__restrict__ X, size_t x_hs, int ld, int col0, int dx, int n,
@@ -317,10 +318,18 @@ __global__ __launch_bounds__(256) void km_assign_decide_kernel(
     return (static_cast<unsigned long long>(asc_key(sc)) << 32) | static_cast<unsigned>(r);
   };
   const bool unsafe = sizeof(T) == 4 && !(nx < kNormLimit && B.numax < kNuLimit * 1.01f);
-  if (unsafe) {
-    // outside the filter's range: every centroid, canonically
-    arg = canon_scan(xr, Uh, nuh, C, dx);
-  } else if (!scan && near > 1) {
+  // every centroid, canonically: points outside the filter's range, and where a wave
+  // has several with three candidates in a chunk, each lane for its own
+  bool own_scan = unsafe;
+  if constexpr (sizeof(T) == 4) {
+    const int scans = __popcll(__ballot(valid && scan));
+    own_scan = unsafe || (scan && scans >= kOwnScans);
+    if (own_scan) {
+      const unsigned long long b = canon_scan(xr, Uh, nuh, C, dx, 0, 4);
+      arg = b == ~0ull ? 0 : static_cast<int>(b & 0xFFFFFFFFu);
+    }
+  }
+  if (!own_scan && !scan && near > 1) {
     unsigned long long b = ~0ull;
     for (int k = 0; k < nparts; ++k) {
       const float4 v = listed(k);
@@ -337,7 +346,7 @@ __global__ __launch_bounds__(256) void km_assign_decide_kernel(
   }
   // a scan takes the whole wave, each lane every 64th centroid (one thread
   // going through 300 centroids held its block up for 350 us)
-  for (uint64_t todo = __ballot(valid && scan && !unsafe); todo; todo &= todo - 1) {
+  for (uint64_t todo = __ballot(valid && scan && !own_scan); todo; todo &= todo - 1) {
     const int src = __ffsll(static_cast<long long>(todo)) - 1;
     const T *xs = X + h * x_hs + static_cast<size_t>(__shfl(i, src)) * ld + col0;
     unsigned long long b = ~0ull;

@@ -115,6 +115,29 @@ def test_fp32_exact_ties_take_the_lowest_centroid():
     _check(x, "f32", (16, 24, 24), 36, (36, 36, 36), 1, init, np.repeat(init[:, None], 3, 1))
 
 
+@pytest.mark.parametrize("share", [1.0, 0.5, 0.06])
+@pytest.mark.parametrize("n,split,c_q,c_m", [
+    (300, (16, 56, 56), 37, (8, 33, 70)),          # all iterations in one block
+    (1500, (17, 31, 33), 70, (33, 70, 32)),        # fused iterations, odd widths
+    (1100, (44, 42, 42), 300, (333, 130, 90)),     # separate launches, a chunked codebook
+])
+def test_fp32_rows_with_many_tied_centroids(n, split, c_q, c_m, share):
+    # a share of the rows are the same, and so are the centroids that start from
+    # them: few, many or all points of a wave need the canonical scan
+    rng = np.random.default_rng(n)
+    x = _rows(rng, 2, n, sum(split), "f32")
+    same = rng.random((2, n)) < share
+    x[same] = 0.0 if share < 1.0 else x[0, 0]
+    init_q, init_k = _init(rng, n, c_q, 2), _init(rng, n, max(c_m), 2, 3)
+    ties = np.flatnonzero(same[0])[:12]
+    init_q[:, :len(ties)] = ties      # a dozen centroids that tie, whatever the share
+    init_k[:, :, :min(len(ties), min(c_m))] = ties[:min(c_m)]
+    layer, q, k = _check(x, "f32", split, c_q, c_m, 3, init_q, init_k)
+    assert np.array_equal(layer.q_centroids.cpu().numpy().view(np.uint32), q["centroids"].view(np.uint32))
+    assert np.array_equal(layer.k_centroids.cpu().numpy().view(np.uint32).reshape(-1),
+                          k["centroids"].view(np.uint32).reshape(-1))
+
+
 @pytest.mark.parametrize("c_q", [20, 300])
 def test_fp32_values_outside_the_filter(c_q):
     # one assignment (the status word reports such inputs, and their sums are
