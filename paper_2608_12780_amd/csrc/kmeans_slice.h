@@ -280,7 +280,7 @@ __device__ __forceinline__ unsigned long long canon_scan(const float *xr, const 
       dot[j] = 0.0f;
     }
     if (vec) {
-#pragma unroll 4
+#pragma unroll 2
       for (int c = 0; c < dx; c += 4) {
         const float4 x = *reinterpret_cast<const float4 *>(xr + c);
 #pragma unroll
@@ -293,7 +293,7 @@ __device__ __forceinline__ unsigned long long canon_scan(const float *xr, const 
         }
       }
     } else {
-#pragma unroll 4
+#pragma unroll 2
       for (int c = 0; c < dx; ++c) {
         const float x = xr[c];
 #pragma unroll
