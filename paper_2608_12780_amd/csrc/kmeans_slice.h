@@ -266,7 +266,7 @@ __device__ __forceinline__ uint32_t asc_key(float f) {
 // chains at a time share the point's loads; one at a time, half-zero or equal rows,
 // whose centroids tie, made whole clusterings take several times as long (40 heads x
 // 3000 rows of 64 channels, queries and keys, 4 iterations, all rows equal: 9.6 ms
-// one at a time, 3.1 ms so).
+// one at a time, 2.9 ms so).
 __device__ __forceinline__ unsigned long long canon_scan(const float *xr, const float *u, const float *nu,
                                                          int C, int dx, int first, int stride) {
   const bool vec = ((reinterpret_cast<uintptr_t>(xr) | reinterpret_cast<uintptr_t>(u)) & 15) == 0 && (dx & 3) == 0;
